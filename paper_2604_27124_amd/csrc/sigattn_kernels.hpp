@@ -488,34 +488,29 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
     constexpr int RPI = C::THREADS / C::CH;        // rows per pass of the workgroup over a tile
     static_assert(C::THREADS % C::CH == 0 && (C::PER == 1 || RPI % 16 == 0), "a pass must keep the LDS row shift");
     const int r0 = tid / C::CH, col0 = (tid % C::CH) * 8;
-    const unsigned ld_off0 = (unsigned)r0 * (unsigned)row_stride + (unsigned)col0;
-    auto load_tile = [&](int t) {   // branch-free: rows beyond the valid length read a clamped row, then become 0
+    // A tile is read through a buffer descriptor that ends with its last valid row: the hardware returns zeros
+    // beyond it without touching memory.  So neither the ragged last tile nor the tiles requested past the end
+    // need a clamp, a select or a branch, and nothing waits for a load before its data is stored.  (With selects
+    // behind the load the last three requests of every workgroup waited for memory on the spot: forward of one
+    // 1000-token sequence 21.4 -> 19.6 us, d = 128 dK/dV at N = 2048 0.354 -> 0.337 ms.)  The descriptors advance
+    // tile by tile in scalar registers; the byte offset inside a tile is a lane constant.
+    const unsigned ld_off0 = ((unsigned)r0 * (unsigned)row_stride + (unsigned)col0) * 2u;
+    const unsigned pass_bytes = (unsigned)RPI * (unsigned)row_stride * 2u;
+    const bf16_t *next1 = y1 + slice_s, *next2 = y2 + slice_s;     // first row of the tile that is requested next
+    int rows_left = ns;                                             // valid rows from there on (negative past the end)
+    auto load_tile = [&]() {
+        const int rows = rows_left < 0 ? 0 : (rows_left > BN ? BN : rows_left);
+        const int bytes = rows * (int)row_stride * 2;
+        const auto d1 = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(next1), 0, bytes, 0x00027000);
+        const auto d2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(next2), 0, bytes, 0x00027000);
 #pragma unroll
         for (int it = 0; it < C::PER; ++it) {
-            const int r = t * BN + it * RPI + r0;
-            const bool ok = r < ns;
-            const size_t off = slice_s + (size_t)(ok ? r : ns - 1) * row_stride + col0;
-            const u32x4 a = *reinterpret_cast<const u32x4 *>(y1 + off);
-            const u32x4 b = *reinterpret_cast<const u32x4 *>(y2 + off);
-            const u32x4 z4 = {0u, 0u, 0u, 0u};
-            st1[it] = ok ? a : z4;
-            st2[it] = ok ? b : z4;
+            st1[it] = __builtin_amdgcn_raw_buffer_load_b128(d1, (int)ld_off0, it * (int)pass_bytes, 0);
+            st2[it] = __builtin_amdgcn_raw_buffer_load_b128(d2, (int)ld_off0, it * (int)pass_bytes, 0);
         }
-    };
-    // Tiles that lie wholly below the valid length need neither the clamp nor the zero fill: their
-    // addresses are a uniform base (scalar registers, advanced per tile and pass) plus the lane constant.
-    auto load_full_tile = [&](int t) {
-        const bf16_t *b1 = y1 + slice_s + (size_t)t * BN * row_stride;
-        const bf16_t *b2 = y2 + slice_s + (size_t)t * BN * row_stride;
-#pragma unroll
-        for (int it = 0; it < C::PER; ++it) {
-            st1[it] = *reinterpret_cast<const u32x4 *>(b1 + (size_t)it * RPI * row_stride + ld_off0);
-            st2[it] = *reinterpret_cast<const u32x4 *>(b2 + (size_t)it * RPI * row_stride + ld_off0);
-        }
-    };
-    auto load_next = [&](int t) {   // t * BN + BN <= ns exactly when t < ntiles - 1
-        if (t < ntiles - 1) load_full_tile(t);
-        else load_tile(t);
+        next1 += (size_t)BN * row_stride;
+        next2 += (size_t)BN * row_stride;
+        rows_left -= BN;
     };
     bf16_t *const w1 = y1s + r0 * LD1 + lds_shift<C::LM1>(r0) + col0;   // LDS home of this thread's chunk, pass 0, slot 0
     bf16_t *const w2 = y2s + r0 * LD2 + lds_shift<C::LM2>(r0) + col0;
@@ -715,15 +710,15 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
         *reinterpret_cast<u32x4 *>(y2s + (C::NBUF * BN - 32) * LD2 + cid * 8) = z4;
     }
     {   // the first three tiles are requested back to back, so their latencies overlap
-        load_tile(0);
+        load_tile();
         u32x4 a1[C::PER], a2[C::PER];
 #pragma unroll
         for (int it = 0; it < C::PER; ++it) { a1[it] = st1[it]; a2[it] = st2[it]; }
-        load_tile(1);
+        load_tile();
         u32x4 b1[C::PER], b2[C::PER];
 #pragma unroll
         for (int it = 0; it < C::PER; ++it) { b1[it] = st1[it]; b2[it] = st2[it]; }
-        load_tile(2);
+        load_tile();
         // every request of the prologue is in flight now; the owner rows, requested first, arrive first
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
@@ -803,13 +798,13 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
     int slot_rt = 0;
     while (true) {
         if (t >= last) { slot_rt = 0; break; }
-        tile_body(IntC<0>{}); load_next(t + 3); ++t;
+        tile_body(IntC<0>{}); load_tile(); ++t;
         if (t >= last) { slot_rt = 1; break; }
-        tile_body(IntC<1>{}); load_next(t + 3); ++t;
+        tile_body(IntC<1>{}); load_tile(); ++t;
         if (t >= last) { slot_rt = 2; break; }
-        tile_body(IntC<2>{}); load_next(t + 3); ++t;
+        tile_body(IntC<2>{}); load_tile(); ++t;
         if (t >= last) { slot_rt = 3; break; }
-        tile_body(IntC<3>{}); load_next(t + 3); ++t;
+        tile_body(IntC<3>{}); load_tile(); ++t;
     }
 
     // ---- last tile: rows >= n masked, its final block has no successor; then the output contractions
