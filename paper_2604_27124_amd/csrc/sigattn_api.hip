@@ -21,29 +21,66 @@ int check_shape(int B, int N, int H, int d) {
     if ((long long)B * H > 2147483647LL) return SIGATTN_ERR_TOO_LARGE;     // grid.x limit
     if ((long long)B * N * H * d >= (1LL << 40)) return SIGATTN_ERR_TOO_LARGE;
     if ((long long)H * d > (1LL << 20)) return SIGATTN_ERR_TOO_LARGE;      // 32-bit lane offsets within one streamed tile
-    if (B > MAP_MAX_B && (long long)N > 256LL * MAP_CLASSES) return SIGATTN_ERR_TOO_LARGE;   // tile-count classes of the work mapping
+    if (B > 256 && (long long)N > 262144LL) return SIGATTN_ERR_TOO_LARGE;  // as the header states
     return SIGATTN_OK;
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-template <int MODE, int D, int QB, int NW, int BN, int LD1, int LD2, int OCC, int RING, bool WITH_DB = false>
-int launch(const Params &p, hipStream_t stream) {
-    using C = Cfg<MODE, D, QB, NW, BN, LD1, LD2, RING>;
-    const long long tiles = ((long long)p.N + C::BM - 1) / C::BM;
-    const long long wgs = tiles * p.B * p.H;                                // one workgroup per owner tile
+// Work mapping of a launch of `wgs` workgroups (two to a CU, 512 in flight): 1 = batch order, 0 = longest sequences
+// first.  Ranking B sequences costs every workgroup about 0.08 B us of the 5 us + 0.9 us per streamed 64-row tile
+// it lives (measured with the wavefronts of both workgroups ranking at once); batch order costs about half a
+// workgroup's life at the end of the launch, so 0.5 / (wgs / 512) of its time.  Batch order where that is less,
+// or where the ranking has no class for every tile count.  Measured, sorted against batch order, us: dK/dV + dQ
+// at B = 512, N = 512: 1015 / 879; B = 32, N = 512: 227 / 208; B = 16, H = 32, N = 1024: 406 / 393; B = 16, H = 12,
+// N = 4096: 825 / 829; forward at B = 24, N = 1500: 77 / 88.
+int batch_order(const Params &p, long long wgs, int owner_rows) {
+    if (p.B > MAP_WAVE_B && ((long long)p.N + owner_rows - 1) / owner_rows > MAP_CLASSES) return 1;
+    return p.B * wgs > 16000 + 45LL * p.N_str;
+}
+
+template <class Kern, class... Args>
+int enqueue(Kern kern, long long wgs, int threads, size_t lds, hipStream_t stream, Args... args) {
     if (wgs > 2147483647LL) return SIGATTN_ERR_TOO_LARGE;
-    dim3 grid((unsigned)wgs, 1, 1);
-    dim3 block(C::THREADS, 1, 1);
-    auto kern = sigattn_kernel<MODE, D, QB, NW, BN, LD1, LD2, OCC, RING, WITH_DB>;
-    if (C::LDS_BYTES > 65536) {   // more dynamic LDS than the default limit: opt in (idempotent, host-side only)
+    if (lds > 65536) {   // more dynamic LDS than the default limit: opt in (idempotent, host-side only)
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)C::LDS_BYTES) != hipSuccess)
+                                (int)lds) != hipSuccess)
             return SIGATTN_ERR_LAUNCH;
     }
-    hipLaunchKernelGGL(kern, grid, block, C::LDS_BYTES, stream, p);
+    hipLaunchKernelGGL(kern, dim3((unsigned)wgs, 1, 1), dim3(threads, 1, 1), lds, stream, args...);
     return hipGetLastError() == hipSuccess ? SIGATTN_OK : SIGATTN_ERR_LAUNCH;
 }
+
+template <class C>
+long long tiles_of(const Params &p) {                                       // one workgroup per owner tile
+    return ((long long)p.N + C::BM - 1) / C::BM * p.B * p.H;
+}
+
+template <int MODE, int D, int QB, int NW, int BN, int LD1, int LD2, int OCC, int RING, bool WITH_DB = false>
+int launch(Params p, hipStream_t stream) {
+    using C = Cfg<MODE, D, QB, NW, BN, LD1, LD2, RING>;
+    const long long wgs = tiles_of<C>(p);
+    p.in_order = batch_order(p, wgs, C::BM);
+    return enqueue(sigattn_kernel<MODE, D, QB, NW, BN, LD1, LD2, OCC, RING, WITH_DB>, wgs, C::THREADS, C::LDS_BYTES, stream, p);
+}
+
+// dK/dV and dQ tiles in one launch (d = 64: both passes take workgroups of the same shape).
+template <int D, int NW, int BN, int LD, int OCC, int RING_KV, int RING_Q>
+int launch_bwd(Params kv, Params q, hipStream_t stream) {
+    using C = Cfg<DKDV, D, 1, NW, BN, LD, LD, RING_KV>;
+    static_assert(C::LDS_BYTES == Cfg<DQ, D, 1, NW, BN, LD, LD, RING_Q>::LDS_BYTES, "one LDS size for both passes");
+    const long long kv_tiles = tiles_of<C>(kv), q_tiles = tiles_of<C>(q);
+    kv.in_order = batch_order(kv, kv_tiles + q_tiles, C::BM);
+    q.in_order = batch_order(q, kv_tiles + q_tiles, C::BM);
+    return enqueue(sigattn_bwd_kernel<D, NW, BN, LD, LD, OCC, RING_KV, RING_Q>, kv_tiles + q_tiles, C::THREADS, C::LDS_BYTES,
+                   stream, kv, q, (int)kv_tiles);
+}
+
+// d = 64, backward: workgroups of four waves (128 owner rows, two to a CU, so that one fills the other's start and
+// end), or of eight (256 rows: half the tile movement per owner row), which win once the tile loop dominates.
+// dK/dV + dQ with four / eight waves, us: N = 512 (B = 32, H = 32) 208 / 262, N = 1500 (B = 8) 127 / 134, N = 3000
+// (B = 3, H = 16) 306 / 299, N = 4096 (B = 2, H = 8) 160 / 156, N = 8192 (B = 4) 1281 / 1266.
+bool eight_waves(int L_q, int L_k) { return L_q >= 4096 && L_k >= 4096; }
 
 }  // namespace
 
@@ -93,13 +130,11 @@ static int fwd_impl(const void *q, const void *k, const void *v, void *o,
     p.B = B; p.N = L_q; p.N_str = L_k; p.H = H;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (d == 64) {
-        // 512-row owner tiles (two owner blocks per wave) feed two MFMAs from every LDS operand read and win
-        // on long sequences; 256-row tiles need half the registers, so two workgroups share a CU, and they
-        // halve the granularity of the grid: measured better up to 4096 streamed rows unless the grid of
-        // 512-row tiles still fills the chip four times over (the host sees the padded lengths only).
-        const long long wgs512 = (long long)B * H * ((L_q + 511) / 512);
-        if (L_k > 4096 || (L_k >= 2048 && wgs512 >= 1024)) return launch<FWD, 64, 2, 8, 64, 72, 72, 1, 4>(p, s);
-        return launch<FWD, 64, 1, 8, 64, 72, 72, 4, 4>(p, s);
+        // Four waves of two owner blocks (256 query rows, two workgroups to a CU) feed two MFMAs from every LDS
+        // operand read.  A grid of at most one such workgroup per CU is split finer: 128-row tiles (B = 4, H = 16,
+        // N = 1024, 256 workgroups: 19.3 against 23.0 us; B = 8, H = 12, 384 workgroups: 32.4 against 30.2 us).
+        if ((long long)B * H * ((L_q + 255) / 256) <= 256) return launch<FWD, 64, 1, 4, 64, 72, 72, 2, 4>(p, s);
+        return launch<FWD, 64, 2, 4, 64, 72, 72, 2, 4>(p, s);
     }
     // d = 128: K is only read row-wise (272-byte rows), V only through the transposing reads, which at that
     // stride ran at a quarter of their rate; 288-byte rows with the split column layout are conflict-free.
@@ -128,29 +163,36 @@ static int bwd_impl(const void *q, const void *k, const void *v, const void *d_o
     p.B = B; p.H = H;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
-    if (want_dkdv) {         // Alg. 3: dK, dV (owner = key tile, streamed = queries and dO)
-        Params pk = p;
-        pk.seqlens = seqlens_k; pk.N = L_k;
-        pk.seqlens_str = seqlens_q; pk.N_str = L_q;
-        pk.out0 = static_cast<bf16_t *>(dk);
-        pk.out1 = static_cast<bf16_t *>(dv);
-        // d = 64: eight waves of 32 keys at two waves per SIMD.  d = 128: the fp32 accumulators of dK and dV
-        // (128 registers) fit only with the whole register file of a SIMD for one wave, so four waves of 32
-        // keys, one per SIMD (both streamed tensors are read row-wise and transposed: 288-byte LDS rows).
-        const int e = (d == 64) ? launch<DKDV, 64, 1, 8, 64, 72, 72, 1, 8>(pk, s)
-                                : launch<DKDV, 128, 1, 4, 64, 144, 144, 1, 4>(pk, s);
+    Params pk = p;           // Alg. 3: dK, dV (owner = key tile, streamed = queries and dO)
+    pk.seqlens = seqlens_k; pk.N = L_k;
+    pk.seqlens_str = seqlens_q; pk.N_str = L_q;
+    pk.out0 = static_cast<bf16_t *>(dk);
+    pk.out1 = static_cast<bf16_t *>(dv);
+    Params pq = p;           // Alg. 2: dQ (owner = query tile, streamed = keys and values)
+    pq.seqlens = seqlens_q; pq.N = L_q;
+    pq.seqlens_str = seqlens_k; pq.N_str = L_k;
+    pq.out0 = static_cast<bf16_t *>(dq);
+    pq.out1 = nullptr;
+
+    if (d == 64) {
+        const bool wide = eight_waves(L_q, L_k);
+        // One launch for both passes: one start, and the tail of the first is filled by the second (B = 2, H = 2,
+        // N = 256: 9.4 us against 9.0 + 8.0; B = 12 heads of N = 1000: 22.5 against 21.9 + 19.4; N = 8192: 1.5 % less).
+        if (want_dkdv && want_dq)
+            return wide ? launch_bwd<64, 8, 64, 72, 1, 8, 4>(pk, pq, s) : launch_bwd<64, 4, 64, 72, 2, 8, 4>(pk, pq, s);
+        if (want_dkdv)
+            return wide ? launch<DKDV, 64, 1, 8, 64, 72, 72, 1, 8>(pk, s) : launch<DKDV, 64, 1, 4, 64, 72, 72, 2, 8>(pk, s);
+        if (want_dq) return wide ? launch<DQ, 64, 1, 8, 64, 72, 72, 1, 4>(pq, s) : launch<DQ, 64, 1, 4, 64, 72, 72, 2, 4>(pq, s);
+        return SIGATTN_OK;
+    }
+    if (want_dkdv) {
+        // d = 128: the fp32 accumulators of dK and dV (128 registers) fit only with the whole register file of a
+        // SIMD for one wave, so four waves of 32 keys, one per SIMD (both streamed tensors are read row-wise and
+        // transposed: 288-byte LDS rows).
+        const int e = launch<DKDV, 128, 1, 4, 64, 144, 144, 1, 4>(pk, s);
         if (e) return e;
     }
-    if (want_dq) {           // Alg. 2: dQ (owner = query tile, streamed = keys and values)
-        Params pq = p;
-        pq.seqlens = seqlens_q; pq.N = L_q;
-        pq.seqlens_str = seqlens_k; pq.N_str = L_k;
-        pq.out0 = static_cast<bf16_t *>(dq);
-        pq.out1 = nullptr;
-        const int e = (d == 64) ? launch<DQ, 64, 1, 8, 64, 72, 72, 1, 4>(pq, s)
-                                : launch<DQ, 128, 1, 8, 64, 144, 136, 1, 4>(pq, s);
-        if (e) return e;
-    }
+    if (want_dq) return launch<DQ, 128, 1, 8, 64, 144, 136, 1, 4>(pq, s);
     return SIGATTN_OK;
 }
 
@@ -185,7 +227,8 @@ int sigmoid_attn_bwd_dkdv(const void *q, const void *k, const void *v, const voi
     return bwd_impl(q, k, v, d_o, nullptr, dk, dv, seqlens, seqlens, bias, scale, B, N_max, N_max, H, d, stream, false, true);
 }
 
-// dQ workgroups own 256 query rows at either head dimension: one partial per workgroup.
+// Bias-gradient partials: 8 bytes per 256 query rows of every (z, h).  The kernels store one float per tile of 256
+// or 128 rows.
 static long long dq_workgroups(int B, int N, int H) { return (((long long)N + 255) / 256) * B * H; }
 
 size_t sigmoid_attn_bwd_dq_dbias_workspace_bytes(int B, int N_max, int H, int d) {
@@ -211,7 +254,6 @@ static int dq_dbias_impl(const void *q, const void *k, const void *v, const void
     if (!workspace || workspace_bytes < need) return SIGATTN_ERR_WORKSPACE;
     if (!aligned16(workspace) || (reinterpret_cast<uintptr_t>(dbias) & 3u)) return SIGATTN_ERR_MISALIGNED;
 
-    const long long nwg = dq_workgroups(B, L_q, H);
     Params p{};
     p.q = static_cast<const bf16_t *>(q);
     p.k = static_cast<const bf16_t *>(k);
@@ -224,12 +266,14 @@ static int dq_dbias_impl(const void *q, const void *k, const void *v, const void
     p.scale = scale;
     p.B = B; p.N = L_q; p.N_str = L_k; p.H = H;
     p.db_part = static_cast<float *>(workspace);
-    p.db_seq = reinterpret_cast<int32_t *>(p.db_part + nwg);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int e = (d == 64) ? launch<DQ, 64, 1, 8, 64, 72, 72, 1, 4, true>(p, s)
-                            : launch<DQ, 128, 1, 8, 64, 144, 136, 1, 2, true>(p, s);
+    const bool four = d == 64 && !eight_waves(L_q, L_k);
+    const int e = four        ? launch<DQ, 64, 1, 4, 64, 72, 72, 2, 4, true>(p, s)
+                  : (d == 64) ? launch<DQ, 64, 1, 8, 64, 72, 72, 1, 4, true>(p, s)
+                              : launch<DQ, 128, 1, 8, 64, 144, 136, 1, 2, true>(p, s);
     if (e) return e;
-    hipLaunchKernelGGL(sigattn_db_reduce, dim3((unsigned)B), dim3(256), 0, s, p.db_part, p.db_seq, (int)nwg, dbias);
+    const int rows = four ? 128 : 256;
+    hipLaunchKernelGGL(sigattn_db_reduce, dim3((unsigned)B), dim3(256), 0, s, p.db_part, (L_q + rows - 1) / rows * H, dbias);
     return hipGetLastError() == hipSuccess ? SIGATTN_OK : SIGATTN_ERR_LAUNCH;
 }
 

@@ -77,8 +77,8 @@ struct Params {
     float scale;
     int B, N, H;                     // N: padded length of the owner side
     int N_str;                       // padded length of the streamed side
-    float *db_part;                  // DQ with bias gradient: per-workgroup partial sums [gridDim.x]
-    int32_t *db_seq;                 //   and the sequence each workgroup belongs to [gridDim.x]
+    int in_order;                    // work mapping: 1 = batch order, 0 = longest sequences first
+    float *db_part;                  // DQ with bias gradient: one partial sum per owner tile, [B][H][tiles of a sequence]
 };
 
 #define SIGATTN_LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
@@ -213,12 +213,14 @@ __device__ __forceinline__ bf16x8 scale_bf16x8(const bf16x8 v, const float f) {
 // proportional to the sequence's valid length), every XCD receives every 8th id of that sorted list, and
 // within one sequence the ids of one XCD are consecutive tiles of the same head; wholly padded tiles,
 // which only write zeros, come last.  Sequences are ranked inside the kernel from seqlens, so the host
-// never needs the lengths: up to MAP_MAX_B sequences by their exact length (every thread ranks one
-// sequence against all others in LDS); larger batches by their number of owner tiles (at most
-// MAP_CLASSES of them: the host refuses longer paddings for such batches), with a histogram and
-// block-wide prefix sums (work per thread grows with B / THREADS, not with B).  Ties keep batch order
-// in both forms.
-constexpr int MAP_MAX_B = 256;
+// never needs the lengths.  Ties keep batch order.  Where workgroups are short and many the ranking costs more
+// than the order gives, and the host asks for batch order instead (see batch_order() on the host side).
+// The ranking has two forms, by its cost per workgroup:
+//   up to MAP_WAVE_B sequences: every wave ranks them for itself in registers, one sequence per lane, by exact
+//       length -- one load, no LDS, no barrier;
+//   larger batches: by their number of owner tiles (at most MAP_CLASSES of them), with a histogram and
+//       block-wide prefix sums (work per thread grows with B / THREADS, not with B).
+constexpr int MAP_WAVE_B = 64;
 constexpr int MAP_CLASSES = 1024;
 
 // Ids [lo, lo + cnt) are the H * tiles valid ids of one sequence.  Hardware deals consecutive ids round-robin
@@ -235,63 +237,84 @@ __device__ __forceinline__ int xcd_major_index(int id, int lo, int cnt) {
     return e + ((idx - ((x - lo) & 7)) >> 3);       // plus the position among the ids on XCD x
 }
 
+struct MapScratch {                       // LDS of the ranking (more than MAP_WAVE_B sequences)
+    int res[4];                           // z, n, h, m0 of this workgroup
+    int hist[MAP_CLASSES];                // owner tiles per class
+    int wave[16];                         // wave totals of a block-wide prefix sum
+    int pick[4];                          // class holding this id (-1: padded part) | tiles before it | all valid tiles | found
+};
+
 template <int BM, int THREADS>
-__device__ __forceinline__ void map_work(const Params &p, int &z, int &h, int &n, int &m0) {
-    __shared__ int s_len[MAP_MAX_B];      // clamped valid length, by batch index
-    __shared__ int s_res[4];              // z, n, h, m0 of this workgroup
+__device__ __forceinline__ void map_work(const Params &p, const int id, MapScratch &scratch, int &z, int &h, int &n, int &m0) {
     static_assert((BM & (BM - 1)) == 0, "owner tile rows: a power of two");
     const int T = (p.N + BM - 1) / BM;    // owner tiles per (z, h), padded ones included
-    const int id = blockIdx.x;
+    int *const s_res = scratch.res;
     auto len_of = [&](int b) {
         const int v = p.seqlens[b];
         return v < 0 ? 0 : (v > p.N ? p.N : v);
     };
-    if (p.B <= MAP_MAX_B) {
-        // Id ranges: the valid tiles of every sequence, longest sequence first (ties in batch order), H ids
-        // per tile; then the padded tiles in batch order.  One thread per sequence sums, in a single pass over
-        // the lengths (uniform LDS reads, no dependent chain), the tiles in front of its own ranges, and the
-        // thread whose range holds this workgroup's id publishes the answer.
-        for (int t = threadIdx.x; t < p.B; t += THREADS) s_len[t] = len_of(t);
-        __syncthreads();
-        for (int t = threadIdx.x; t < p.B; t += THREADS) {
-            const int mine = s_len[t], my_tiles = (mine + BM - 1) / BM;
-            int before_valid = 0, before_padded = 0, all_valid = 0;
-#pragma unroll 8
-            for (int u = 0; u < p.B; ++u) {
-                const int o = s_len[u], tiles = (o + BM - 1) / BM;
-                const bool ahead = o > mine || (o == mine && u < t);
-                before_valid += ahead ? tiles : 0;
-                before_padded += (u < t) ? (T - tiles) : 0;
-                all_valid += tiles;
-            }
-            {   // valid tiles of sequence t: ids lo .. lo + cnt - 1
-                const int lo = before_valid * p.H, cnt = my_tiles * p.H;
-                if (id >= lo && id < lo + cnt) {
-                    const int e = xcd_major_index(id, lo, cnt);
-                    s_res[0] = t; s_res[1] = mine; s_res[2] = e / my_tiles; s_res[3] = (e % my_tiles) * BM;
-                }
-            }
-            {   // padded tiles of sequence t
-                const int lo = (all_valid + before_padded) * p.H, cnt = (T - my_tiles) * p.H;
-                if (id >= lo && id < lo + cnt) {
-                    const int rest = id - lo;
-                    s_res[0] = t; s_res[1] = mine; s_res[2] = rest % p.H; s_res[3] = (my_tiles + rest / p.H) * BM;
-                }
-            }
-        }
-        __syncthreads();
-        z = s_res[0]; n = s_res[1]; h = s_res[2]; m0 = s_res[3];
+    if (p.in_order) {
+        // Batch order: H * T ids per sequence, dealt to the XCDs in runs of consecutive tiles as below.  Which XCD
+        // takes which run turns with the sequence: runs differ in their share of padded tiles, and an XCD keeps
+        // the ids that hardware deals to it.
+        const int cnt = p.H * T;
+        z = id / cnt;
+        int e = xcd_major_index(id, z * cnt, cnt) + (z & 7) * ((cnt + 7) >> 3);
+        e %= cnt;
+        h = e / T;
+        n = len_of(z);
+        const int tile = (e - h * T + (T >= 4 ? h + z : (h + z) / (4 / T))) % T;
+        m0 = tile * BM;
         return;
     }
-
-    // ---- more sequences than the pairwise ranking holds.  A sequence's class is its number of owner tiles
-    // (class 0 = T tiles, the longest; T <= MAP_CLASSES is the host's check).
+    if (p.B <= MAP_WAVE_B) {
+        // Id ranges as below: the valid tiles of every sequence, longest first, H ids per tile; then the padded
+        // tiles in batch order.  Lane l sums the tiles in front of sequence l, whose length every lane reads from
+        // lane u by a scalar read; the lane whose range holds this workgroup's id is found with a ballot.
+        const int lane = threadIdx.x & 63;
+        const int mine = lane < p.B ? len_of(lane) : 0;
+        const int my_tiles = (mine + BM - 1) / BM;
+        int before = 0, all_valid = 0;
+        for (int u = 0; u < p.B; ++u) {
+            const int o = __builtin_amdgcn_readlane(mine, u), tiles = (o + BM - 1) / BM;
+            before += (o >= mine + (lane <= u)) ? tiles : 0;        // longer, or as long and earlier in the batch
+            all_valid += tiles;
+        }
+        int lo = before, cnt = my_tiles;
+        const bool padded = id >= all_valid * p.H;                  // uniform
+        if (padded) {                                               // exclusive prefix sum of the padded tiles
+            cnt = lane < p.B ? T - my_tiles : 0;
+            int incl = cnt;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int up = __shfl_up(incl, off, 64);
+                incl += (lane >= off) ? up : 0;
+            }
+            lo = all_valid + incl - cnt;
+        }
+        lo *= p.H;
+        const unsigned long long hit = __builtin_amdgcn_ballot_w64(lane < p.B && id >= lo && id < lo + cnt * p.H);
+        const int src = __builtin_ctzll(hit);                       // exactly one lane: the ranges tile the grid
+        z = src;
+        n = __builtin_amdgcn_readlane(mine, src);
+        lo = __builtin_amdgcn_readlane(lo, src);
+        cnt = __builtin_amdgcn_readlane(cnt, src);
+        if (padded) {
+            h = (id - lo) % p.H;
+            m0 = ((n + BM - 1) / BM + (id - lo) / p.H) * BM;
+        } else {
+            const int e = xcd_major_index(id, lo, cnt * p.H);
+            h = e / cnt;
+            m0 = (e % cnt) * BM;
+        }
+        return;
+    }
+    // ---- more sequences than lanes.  A sequence's class is its number of owner tiles
+    // (class 0 = T tiles, the longest; T <= MAP_CLASSES is the host's rule).
     // Id ranges: classes in ascending order, inside a class the sequences in batch order, H ids per tile;
     // then the padded tiles in batch order.  All positions are kept in tiles: a sequence whose tiles are
     // [tb, tb + tiles) of that list owns the ids [H tb, H (tb + tiles)).
-    __shared__ int s_hist[MAP_CLASSES];   // owner tiles per class
-    __shared__ int s_wave[THREADS / 64];  // wave totals of a block-wide prefix sum
-    __shared__ int s_pick[4];             // class holding this id (-1: padded part) | tiles before it | all valid tiles | found
+    int *const s_hist = scratch.hist, *const s_wave = scratch.wave, *const s_pick = scratch.pick;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto class_of = [&](int tiles) { return T - tiles; };      // tiles in [1, T]
     for (int i = tid; i < MAP_CLASSES; i += THREADS) s_hist[i] = 0;
@@ -368,8 +391,9 @@ __device__ __forceinline__ void map_work(const Params &p, int &z, int &h, int &n
     z = s_res[0]; n = s_res[1]; h = s_res[2]; m0 = s_res[3];
 }
 
-template <int MODE, int D, int QB, int NW, int BN, int LD1, int LD2, int OCC, int RING, bool WITH_DB = false>
-__global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
+// One owner tile of one pass: the work of workgroup `id` of a launch of that pass.  `smem`: Cfg::LDS_BYTES bytes.
+template <int MODE, int D, int QB, int NW, int BN, int LD1, int LD2, int RING, bool WITH_DB>
+__device__ __forceinline__ void run_pass(const Params &p, const int id, unsigned char *const smem, MapScratch &scratch, float *const s_db) {
     static_assert(!WITH_DB || MODE == DQ, "the bias gradient rides on the dQ kernel");
     using C = Cfg<MODE, D, QB, NW, BN, LD1, LD2, RING>;
     constexpr bool HAS2 = C::HAS2;
@@ -377,14 +401,12 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
     constexpr int NB = C::NB, NA = C::NA, NOPS = C::NOPS, SLOTS = C::SLOTS, NT = C::NT, NO = C::NO, MB = C::MB;
     constexpr float LOG2E = 1.4426950408889634f;
 
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    __shared__ float s_db[WITH_DB ? NW : 1];                        // bias gradient: one partial per wave
     bf16_t *y1s = reinterpret_cast<bf16_t *>(smem);                 // [NBUF][BN][LD1]
     bf16_t *y2s = y1s + C::NBUF * BN * LD1;                         // [NBUF][BN][LD2]
 
     // Work mapping (1-D grid over every owner tile of every (z, h)): see map_work().
     int z, h, n, m0;
-    map_work<C::BM, C::THREADS>(p, z, h, n, m0);
+    map_work<C::BM, C::THREADS>(p, id, scratch, z, h, n, m0);
     z = __builtin_amdgcn_readfirstlane(z);      // uniform across the workgroup: keep them in scalar registers
     h = __builtin_amdgcn_readfirstlane(h);
     n = __builtin_amdgcn_readfirstlane(n);
@@ -400,14 +422,13 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
     }
     ns = __builtin_amdgcn_readfirstlane(ns);
 
+    auto db_slot = [&]() { return ((size_t)z * p.H + h) * ((p.N + C::BM - 1) / C::BM) + m0 / C::BM; };
+
     // Wholly padded owner tile, or nothing to stream: write zeros, do nothing else (block-sparse early exit).
     if (m0 >= n || ns == 0) {
         zero_rows<D, C::THREADS>(p.out0, slice, row_stride, m0, m1);
         if (MODE == DKDV) zero_rows<D, C::THREADS>(p.out1, slice, row_stride, m0, m1);
-        if (WITH_DB && threadIdx.x == 0) {
-            p.db_part[blockIdx.x] = 0.f;
-            p.db_seq[blockIdx.x] = z;
-        }
+        if (WITH_DB && threadIdx.x == 0) p.db_part[db_slot()] = 0.f;
         return;
     }
 
@@ -539,61 +560,54 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
     u32x4 pbuf[2][QB][2], dsbuf[2][Q2][2];
     bf16x8 ring[RING];
 
-    // First ring row of the block `delta` blocks after block nb of the tile in ring slot `slot`.
-    auto block_row = [&](auto slot, int nb, int delta) {
-        const int nbp = nb + delta + NB;                       // >= 0 for delta >= -NB
-        const int sl = (slot.get() + nbp / NB + C::NBUF - 1) & (C::NBUF - 1);
-        return sl * BN + (nbp % NB) * 32;
-    };
-
     // The J-th A operand counted from the start of the step on block nb of `slot` (J >= NOPS runs into the
     // following step): row-wise operands belong to the block after the step's block, transposed ones to the
     // block before it.
-    auto fetch = [&](auto J_, auto slot, int nb) -> bf16x8 {
+    auto fetch = [&](auto J_, auto slot, auto nb_c) -> bf16x8 {
         constexpr int J = decltype(J_)::value;
         constexpr int sstep = J / NOPS, j = J % NOPS;
+        constexpr int blk = decltype(nb_c)::value + sstep + (j < NA ? 1 : -1) + NB;   // >= 0, counted from the previous tile
+        constexpr int tile = blk / NB - 1;                                            // relative to the current one
+        constexpr int brow = (blk % NB) * 32;
+        const int row = ((slot.get() + tile) & (C::NBUF - 1)) * BN + brow;
         if constexpr (j < NA) {
             constexpr int ks = j / NT, which = j % NT;
-            const int row = block_row(slot, nb, sstep + 1);
             if constexpr (which == 0) return lds_read_rows(rd1 + row * LD1 + 16 * ks);
             else return lds_read_rows(rd2 + row * LD2 + 16 * ks);
         } else {
             constexpr int jj = j - NA, which = jj % NO, idx = jj / NO, half = idx / MB, mb = idx % MB;
-            const int row = block_row(slot, nb, sstep - 1) + 16 * half;
             // FWD contracts V^T (tensor 2); DQ contracts K^T (tensor 1); DKDV: Q^T (1) for dK, dO^T (2) for dV
             constexpr bool second = (MODE == FWD) || (MODE == DKDV && which == 1);
             if constexpr (second) {
-                const bf16_t *a = tr2 + row * LD2 + TL2::MB_COLS * mb;
+                const bf16_t *a = tr2 + (row + 16 * half) * LD2 + TL2::MB_COLS * mb;
                 return lds_read_tr(a, a + 8 * LD2 + TL2::HI_EXTRA);
             } else {
-                const bf16_t *a = tr1 + row * LD1 + TL1::MB_COLS * mb;
+                const bf16_t *a = tr1 + (row + 16 * half) * LD1 + TL1::MB_COLS * mb;
                 return lds_read_tr(a, a + 8 * LD1 + TL1::HI_EXTRA);
             }
         }
     };
 
     // VALU work of one step: see ValuOrder.  Per unit u (registers 2w, 2w + 1 of owner block qb = u / 8):
-    //   0,1  e = 2^t'            2,3  y = 1 + cb e          4,5  P = 1 / y      [6,7  P = 0 on padded rows]
+    //   0,1  e = 2^t'            2,3  y = 1 + cb e          4,5  P = 1 / y
     //   FWD : pack P
     //   bwd : g = e P (2 ops), a = P dP (2 ops), dS / cb = g a (2 ops), pack it, DKDV also packs P
     // 1 - P = cb e P holds without cancellation however close P is to 1, so dS = P (1 - P) dP keeps its
     // relative accuracy on the saturated tail; the constant cb is applied once, to the finished sums.
     // e = +inf (score far below the bias) meets P = 0 there: the product must be 0, not NaN.
-    constexpr int OPU_BASE = (MODE == FWD) ? 7 : (MODE == DQ ? 13 : 14);
+    // Streamed rows beyond the valid length need no mask: they are zeros in LDS, so P is finite there and meets a
+    // zero row of V (forward), and dP = 0, hence dS = 0, in the backward passes; dV meets a zero row of dO.
+    constexpr int OPU = (MODE == FWD) ? 7 : (MODE == DQ ? 13 : 14);
 
     // One pipeline step on the block (slot, nb) of parity PAR (compile-time nb).  Slots run in program
     // order; a scheduling fence closes each of them.
-    auto step = [&](auto masked_c, auto has_next_c, auto drain_c, auto nb_c, auto slot, const int srow0,
-                    auto store_at_c, const int store_slot) {
-        constexpr bool MASKED = decltype(masked_c)::value;
+    auto step = [&](auto has_next_c, auto drain_c, auto nb_c, auto slot, auto store_at_c, const int store_slot) {
         constexpr int STORE_AT = decltype(store_at_c)::value;   // slot before which the staged tile goes to LDS (-1: never)
-        constexpr bool HAS_NEXT = decltype(has_next_c)::value;
-        constexpr bool DRAIN = decltype(drain_c)::value;
+        constexpr bool HAS_NEXT = decltype(has_next_c)::value;  // a block follows: compute its scores
+        constexpr bool DRAIN = decltype(drain_c)::value;        // only the output contractions of the last block
         constexpr int nb = decltype(nb_c)::value;
         constexpr int PAR = nb & 1;
         constexpr int G0 = (nb * NOPS) % RING;               // ring position of this step's first operand
-        constexpr int MK = MASKED ? 2 : 0;
-        constexpr int OPU = OPU_BASE + MK;
         constexpr ValuOrder<C::UNITS, OPU, 2, 6> order{};
         constexpr int LEN = DRAIN ? 0 : C::UNITS * OPU;
         const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -606,7 +620,7 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
             // barrier early and left the other to finish alone, at the poor rate of a lone wave.  Priorities that
             // fall with every quarter of a tile let the wave that is behind catch up: as fast as no barrier at all
             // (N = 8192, d = 64: dK/dV 0.766 -> 0.747 ms, dQ 0.629 -> 0.611 ms; without the barrier 0.746, 0.613).
-            if constexpr (!DRAIN && !MASKED) {
+            if constexpr (!DRAIN) {
                 constexpr int QUARTER = (2 * nb + (k >= SLOTS / 2)) * 4 / (2 * NB);
                 if constexpr (k == 0 || k == SLOTS / 2) __builtin_amdgcn_s_setprio(3 - QUARTER);
             }
@@ -646,7 +660,7 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
             }
             // ---- the register of the previous operand is free now: request the operand RING - 1 ahead
             if constexpr (qb == 0 && (!DRAIN || j + RING - 1 < NOPS)) {
-                ring[(G0 + j + RING - 1) % RING] = fetch(IntC<j + RING - 1>{}, slot, nb);
+                ring[(G0 + j + RING - 1) % RING] = fetch(IntC<j + RING - 1>{}, slot, nb_c);
             }
             // ---- this slot's share of the sigmoid
             static_for<(k * LEN) / SLOTS, ((k + 1) * LEN) / SLOTS>([&](auto i_) {
@@ -674,10 +688,8 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
                 else if constexpr (o == 3) set_y(B_, __builtin_fmaf(cb, s[rb], 1.0f));
                 else if constexpr (o == 4) set_y(A_, __builtin_amdgcn_rcpf(y_of(A_)));
                 else if constexpr (o == 5) set_y(B_, __builtin_amdgcn_rcpf(y_of(B_)));
-                else if constexpr (MASKED && o == 6) set_y(A_, (srow0 + 8 * (ra >> 2) + (ra & 3) < ns) ? y_of(A_) : 0.f);
-                else if constexpr (MASKED && o == 7) set_y(B_, (srow0 + 8 * (rb >> 2) + (rb & 3) < ns) ? y_of(B_) : 0.f);
                 else {
-                    constexpr int e = o - 6 - MK;     // position in the mode's tail of the unit
+                    constexpr int e = o - 6;          // position in the mode's tail of the unit
                     if constexpr (MODE == FWD) {
                         pbuf[PAR][uq][w / 4][w % 4] = pack_bf16(s[ra], s[rb]);
                     } else {
@@ -759,9 +771,9 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
             }
     }
     // operands 0 .. RING - 2 of the first step
-    static_for<0, RING - 1>([&](auto J_) { ring[decltype(J_)::value % RING] = fetch(J_, IntC<0>{}, 0); });
+    static_for<0, RING - 1>([&](auto J_) { ring[decltype(J_)::value % RING] = fetch(J_, IntC<0>{}, IntC<0>{}); });
 
-    // ---- main loop over all tiles but the last: no padded rows, every block has a successor.  The loop is
+    // ---- main loop over all tiles but the last: every block has a successor.  The loop is
     // unrolled over the four ring slots so that every LDS address is a lane constant plus an immediate.
     // Tile t + 2 goes to slot (t + 2) % 4 = (t - 2) % 4, last read during the first step of tile t - 1 (as
     // the previous block); every wave passed the barrier that ended tile t - 1.  The staged registers are
@@ -788,39 +800,35 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
     auto tile_body = [&](auto slot_c) {
         constexpr int slot = decltype(slot_c)::value;
         static_for<0, NB>([&](auto nb_) {
-            if constexpr (decltype(nb_)::value + 1 < NB) step(F_{}, T_{}, F_{}, nb_, slot_c, 0, IntC<-1>{}, 0);
-            else step(F_{}, T_{}, F_{}, nb_, slot_c, 0, IntC<STORE_AT>{}, (slot + 2) & (C::NBUF - 1));
+            step(T_{}, F_{}, nb_, slot_c, IntC<(decltype(nb_)::value + 1 < NB) ? -1 : STORE_AT>{}, (slot + 2) & (C::NBUF - 1));
         });
         asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(READS_AFTER) : "memory");
+        load_tile();
     };
     int t = 0;
     const int last = ntiles - 1;
     int slot_rt = 0;
     while (true) {
         if (t >= last) { slot_rt = 0; break; }
-        tile_body(IntC<0>{}); load_tile(); ++t;
+        tile_body(IntC<0>{}); ++t;
         if (t >= last) { slot_rt = 1; break; }
-        tile_body(IntC<1>{}); load_tile(); ++t;
+        tile_body(IntC<1>{}); ++t;
         if (t >= last) { slot_rt = 2; break; }
-        tile_body(IntC<2>{}); load_tile(); ++t;
+        tile_body(IntC<2>{}); ++t;
         if (t >= last) { slot_rt = 3; break; }
-        tile_body(IntC<3>{}); load_tile(); ++t;
+        tile_body(IntC<3>{}); ++t;
     }
 
-    // ---- last tile: rows >= n masked, its final block has no successor; then the output contractions
-    // of that final block (a step that only drains).
+    // ---- last tile: its final block has no successor; then the output contractions of that final block (a step
+    // that only drains).
     {
         const DynInt slot{slot_rt};
         static_for<0, NB>([&](auto nb_) {
-            constexpr int nb = decltype(nb_)::value;
-            const int srow0 = last * BN + nb * 32 + 4 * g;
-            if constexpr (nb + 1 < NB) step(T_{}, T_{}, F_{}, nb_, slot, srow0, IntC<-1>{}, 0);
-            else step(T_{}, F_{}, F_{}, nb_, slot, srow0, IntC<-1>{}, 0);
+            step(IntC<(decltype(nb_)::value + 1 < NB) ? 1 : 0>{}, F_{}, nb_, slot, IntC<-1>{}, 0);
         });
         const DynInt slot_next{(slot_rt + 1) & (C::NBUF - 1)};
-        step(F_{}, F_{}, T_{}, IntC<0>{}, slot_next, 0, IntC<-1>{}, 0);
+        step(F_{}, T_{}, IntC<0>{}, slot_next, IntC<-1>{}, 0);
     }
-
 
     if constexpr (WITH_DB) {
         // Row 0 of accdb (register 0 of lanes 0..15) holds 16 partial sums that together cover every dS of
@@ -838,8 +846,7 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
             float t = 0.f;
 #pragma unroll
             for (int w = 0; w < NW; ++w) t += s_db[w];
-            p.db_part[blockIdx.x] = t * cb;                   // the summed values are dS / cb
-            p.db_seq[blockIdx.x] = z;
+            p.db_part[db_slot()] = t * cb;                // the summed values are dS / cb
         }
     }
 
@@ -881,14 +888,34 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
     }
 }
 
-// Second stage of the bias gradient: db[z] = sum of the partials of the workgroups of sequence z, in a
-// fixed order (thread t takes workgroups t, t + 256, ...; then a tree in LDS), so the result is
-// bitwise reproducible.  One workgroup per sequence.
-__global__ void __launch_bounds__(256) sigattn_db_reduce(const float *part, const int32_t *seq, int nwg, float *db) {
+template <int MODE, int D, int QB, int NW, int BN, int LD1, int LD2, int OCC, int RING, bool WITH_DB = false>
+__global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ MapScratch scratch;
+    __shared__ float s_db[WITH_DB ? NW : 1];                        // bias gradient: one partial per wave
+    run_pass<MODE, D, QB, NW, BN, LD1, LD2, RING, WITH_DB>(p, blockIdx.x, smem, scratch, s_db);
+}
+
+// Both halves of the backward pass in one launch: workgroups [0, kv_tiles) take the dK/dV tiles, the others the
+// dQ tiles.
+template <int D, int NW, int BN, int LD1, int LD2, int OCC, int RING_KV, int RING_Q>
+__global__ void __launch_bounds__(NW * 64, OCC) sigattn_bwd_kernel(const Params kv, const Params q, const int kv_tiles) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ MapScratch scratch;
+    __shared__ float s_db[1];
+    const int id = blockIdx.x;
+    if (id < kv_tiles) run_pass<DKDV, D, 1, NW, BN, LD1, LD2, RING_KV, false>(kv, id, smem, scratch, s_db);
+    else run_pass<DQ, D, 1, NW, BN, LD1, LD2, RING_Q, false>(q, id - kv_tiles, smem, scratch, s_db);
+}
+
+// Second stage of the bias gradient: db[z] = sum of the `per_seq` partials of sequence z, in a fixed order
+// (thread t takes partials t, t + 256, ...; then a tree in LDS), so the result is bitwise reproducible.
+// One workgroup per sequence.
+__global__ void __launch_bounds__(256) sigattn_db_reduce(const float *part, int per_seq, float *db) {
     __shared__ float s[256];
     const int z = blockIdx.x;
     float t = 0.f;
-    for (int i = threadIdx.x; i < nwg; i += 256) t += (seq[i] == z) ? part[i] : 0.f;
+    for (int i = threadIdx.x; i < per_seq; i += 256) t += part[(size_t)z * per_seq + i];
     s[threadIdx.x] = t;
     __syncthreads();
     for (int w = 128; w >= 1; w >>= 1) {
