@@ -70,8 +70,7 @@ int launch_bwd(Params kv, Params q, hipStream_t stream) {
     using C = Cfg<DKDV, D, 1, NW, BN, LD, LD, RING_KV>;
     static_assert(C::LDS_BYTES == Cfg<DQ, D, 1, NW, BN, LD, LD, RING_Q>::LDS_BYTES, "one LDS size for both passes");
     const long long kv_tiles = tiles_of<C>(kv), q_tiles = tiles_of<C>(q);
-    kv.in_order = batch_order(kv, kv_tiles + q_tiles, C::BM);
-    q.in_order = batch_order(q, kv_tiles + q_tiles, C::BM);
+    kv.in_order = q.in_order = batch_order(kv, kv_tiles + q_tiles, C::BM) || batch_order(q, kv_tiles + q_tiles, C::BM);
     return enqueue(sigattn_bwd_kernel<D, NW, BN, LD, LD, OCC, RING_KV, RING_Q>, kv_tiles + q_tiles, C::THREADS, C::LDS_BYTES,
                    stream, kv, q, (int)kv_tiles);
 }
@@ -131,9 +130,10 @@ static int fwd_impl(const void *q, const void *k, const void *v, void *o,
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (d == 64) {
         // Four waves of two owner blocks (256 query rows, two workgroups to a CU) feed two MFMAs from every LDS
-        // operand read.  A grid of at most one such workgroup per CU is split finer: 128-row tiles (B = 4, H = 16,
-        // N = 1024, 256 workgroups: 19.3 against 23.0 us; B = 8, H = 12, 384 workgroups: 32.4 against 30.2 us).
-        if ((long long)B * H * ((L_q + 255) / 256) <= 256) return launch<FWD, 64, 1, 4, 64, 72, 72, 2, 4>(p, s);
+        // operand read.  A grid of at most one such workgroup per CU is split finer, into 128-row tiles (B = 4,
+        // H = 16, N = 1024, 256 workgroups: 19.3 against 23.0 us; B = 8, H = 12, 384 workgroups: 32.4 against
+        // 30.2 us), and sequences that fit one 128-row tile take it (B = 200, H = 8, N = 100: 19.2 against 25.1 us).
+        if (L_q <= 128 || (long long)B * H * ((L_q + 255) / 256) <= 256) return launch<FWD, 64, 1, 4, 64, 72, 72, 2, 4>(p, s);
         return launch<FWD, 64, 2, 4, 64, 72, 72, 2, 4>(p, s);
     }
     // d = 128: K is only read row-wise (272-byte rows), V only through the transposing reads, which at that

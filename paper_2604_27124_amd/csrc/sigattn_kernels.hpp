@@ -244,28 +244,40 @@ struct MapScratch {                       // LDS of the ranking (more than MAP_W
     int pick[4];                          // class holding this id (-1: padded part) | tiles before it | all valid tiles | found
 };
 
+struct Work { int z, h, n, m0; };          // one owner tile: sequence, head, valid owner rows of the sequence, first row
+
+// Batch order: H * T ids per sequence, dealt to the XCDs in runs of consecutive tiles as above.  Which XCD takes
+// which run turns with the sequence, and where the tiles of a head begin turns with the head: runs and tiles
+// differ in their share of padding, and an XCD keeps the ids that hardware deals to it, a shader engine every
+// fourth of those, while the others wait for the slowest.  (Without the second turn 280 of the 512 workgroups
+// that fit were running in a launch of 24576: dK/dV at B = 512, N = 512 took 608 us instead of 488.)
+__device__ __forceinline__ void batch_order_work(const int id, const int H, const int T, int &z, int &h, int &tile) {
+    const int cnt = H * T;
+    z = id / cnt;
+    const int e = (xcd_major_index(id, z * cnt, cnt) + (z & 7) * ((cnt + 7) >> 3)) % cnt;
+    h = e / T;
+    tile = (e - h * T + (T >= 4 ? h + z : (h + z) / (4 / T))) % T;
+}
+
+template <int BM>
+__device__ __forceinline__ int owner_tiles(const Params &p) { return (p.N + BM - 1) / BM; }    // per (z, h), padded ones included
+
+__device__ __forceinline__ int owner_length(const Params &p, int b) {
+    const int v = p.seqlens[b];
+    return v < 0 ? 0 : (v > p.N ? p.N : v);
+}
+
 template <int BM, int THREADS>
-__device__ __forceinline__ void map_work(const Params &p, const int id, MapScratch &scratch, int &z, int &h, int &n, int &m0) {
+__device__ __forceinline__ Work map_work(const Params &p, const int id, MapScratch &scratch) {
     static_assert((BM & (BM - 1)) == 0, "owner tile rows: a power of two");
-    const int T = (p.N + BM - 1) / BM;    // owner tiles per (z, h), padded ones included
+    const int T = owner_tiles<BM>(p);
+    int z, h, n, m0;
     int *const s_res = scratch.res;
-    auto len_of = [&](int b) {
-        const int v = p.seqlens[b];
-        return v < 0 ? 0 : (v > p.N ? p.N : v);
-    };
+    auto len_of = [&](int b) { return owner_length(p, b); };
     if (p.in_order) {
-        // Batch order: H * T ids per sequence, dealt to the XCDs in runs of consecutive tiles as below.  Which XCD
-        // takes which run turns with the sequence: runs differ in their share of padded tiles, and an XCD keeps
-        // the ids that hardware deals to it.
-        const int cnt = p.H * T;
-        z = id / cnt;
-        int e = xcd_major_index(id, z * cnt, cnt) + (z & 7) * ((cnt + 7) >> 3);
-        e %= cnt;
-        h = e / T;
-        n = len_of(z);
-        const int tile = (e - h * T + (T >= 4 ? h + z : (h + z) / (4 / T))) % T;
-        m0 = tile * BM;
-        return;
+        int tile;
+        batch_order_work(id, p.H, T, z, h, tile);
+        return {z, h, len_of(z), tile * BM};
     }
     if (p.B <= MAP_WAVE_B) {
         // Id ranges as below: the valid tiles of every sequence, longest first, H ids per tile; then the padded
@@ -307,7 +319,7 @@ __device__ __forceinline__ void map_work(const Params &p, const int id, MapScrat
             h = e / cnt;
             m0 = (e % cnt) * BM;
         }
-        return;
+        return {z, h, n, m0};
     }
     // ---- more sequences than lanes.  A sequence's class is its number of owner tiles
     // (class 0 = T tiles, the longest; T <= MAP_CLASSES is the host's rule).
@@ -388,12 +400,12 @@ __device__ __forceinline__ void map_work(const Params &p, const int id, MapScrat
         if (s_pick[3]) break;
         running += total;
     }
-    z = s_res[0]; n = s_res[1]; h = s_res[2]; m0 = s_res[3];
+    return {s_res[0], s_res[2], s_res[1], s_res[3]};
 }
 
-// One owner tile of one pass: the work of workgroup `id` of a launch of that pass.  `smem`: Cfg::LDS_BYTES bytes.
+// One owner tile of one pass.  `smem`: Cfg::LDS_BYTES bytes.
 template <int MODE, int D, int QB, int NW, int BN, int LD1, int LD2, int RING, bool WITH_DB>
-__device__ __forceinline__ void run_pass(const Params &p, const int id, unsigned char *const smem, MapScratch &scratch, float *const s_db) {
+__device__ __forceinline__ void run_pass(const Params &p, const Work work, unsigned char *const smem, float *const s_db) {
     static_assert(!WITH_DB || MODE == DQ, "the bias gradient rides on the dQ kernel");
     using C = Cfg<MODE, D, QB, NW, BN, LD1, LD2, RING>;
     constexpr bool HAS2 = C::HAS2;
@@ -404,13 +416,10 @@ __device__ __forceinline__ void run_pass(const Params &p, const int id, unsigned
     bf16_t *y1s = reinterpret_cast<bf16_t *>(smem);                 // [NBUF][BN][LD1]
     bf16_t *y2s = y1s + C::NBUF * BN * LD1;                         // [NBUF][BN][LD2]
 
-    // Work mapping (1-D grid over every owner tile of every (z, h)): see map_work().
-    int z, h, n, m0;
-    map_work<C::BM, C::THREADS>(p, id, scratch, z, h, n, m0);
-    z = __builtin_amdgcn_readfirstlane(z);      // uniform across the workgroup: keep them in scalar registers
-    h = __builtin_amdgcn_readfirstlane(h);
-    n = __builtin_amdgcn_readfirstlane(n);
-    m0 = __builtin_amdgcn_readfirstlane(m0);
+    const int z = __builtin_amdgcn_readfirstlane(work.z);      // uniform across the workgroup: keep them in scalar registers
+    const int h = __builtin_amdgcn_readfirstlane(work.h);
+    const int n = __builtin_amdgcn_readfirstlane(work.n);
+    const int m0 = __builtin_amdgcn_readfirstlane(work.m0);
     const int m1 = (m0 + C::BM < p.N) ? m0 + C::BM : p.N;
     const size_t row_stride = (size_t)p.H * D;
     const size_t slice = ((size_t)z * p.N * p.H + h) * D;           // owner side: element offset of row 0 of (z, h)
@@ -893,19 +902,35 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ MapScratch scratch;
     __shared__ float s_db[WITH_DB ? NW : 1];                        // bias gradient: one partial per wave
-    run_pass<MODE, D, QB, NW, BN, LD1, LD2, RING, WITH_DB>(p, blockIdx.x, smem, scratch, s_db);
+    using C = Cfg<MODE, D, QB, NW, BN, LD1, LD2, RING>;
+    run_pass<MODE, D, QB, NW, BN, LD1, LD2, RING, WITH_DB>(p, map_work<C::BM, C::THREADS>(p, blockIdx.x, scratch), smem, s_db);
 }
 
-// Both halves of the backward pass in one launch: workgroups [0, kv_tiles) take the dK/dV tiles, the others the
-// dQ tiles.
+// Both halves of the backward pass in one launch.  Longest sequences first: workgroups [0, kv_tiles) take the dK/dV
+// tiles, the others the dQ tiles.  Batch order: the tiles of both passes of a head follow each other, so that the
+// second pass finds the head's rows in the XCD's L2.
 template <int D, int NW, int BN, int LD1, int LD2, int OCC, int RING_KV, int RING_Q>
 __global__ void __launch_bounds__(NW * 64, OCC) sigattn_bwd_kernel(const Params kv, const Params q, const int kv_tiles) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ MapScratch scratch;
     __shared__ float s_db[1];
+    using C = Cfg<DKDV, D, 1, NW, BN, LD1, LD2, RING_KV>;
     const int id = blockIdx.x;
-    if (id < kv_tiles) run_pass<DKDV, D, 1, NW, BN, LD1, LD2, RING_KV, false>(kv, id, smem, scratch, s_db);
-    else run_pass<DQ, D, 1, NW, BN, LD1, LD2, RING_Q, false>(q, id - kv_tiles, smem, scratch, s_db);
+    Work w;
+    bool is_kv;
+    if (kv.in_order) {
+        const int t_kv = owner_tiles<C::BM>(kv), t_q = owner_tiles<C::BM>(q);
+        int tile;
+        batch_order_work(id, kv.H, t_kv + t_q, w.z, w.h, tile);
+        is_kv = tile < t_kv;
+        w.n = owner_length(is_kv ? kv : q, w.z);
+        w.m0 = (is_kv ? tile : tile - t_kv) * C::BM;
+    } else {
+        is_kv = id < kv_tiles;
+        w = is_kv ? map_work<C::BM, C::THREADS>(kv, id, scratch) : map_work<C::BM, C::THREADS>(q, id - kv_tiles, scratch);
+    }
+    if (is_kv) run_pass<DKDV, D, 1, NW, BN, LD1, LD2, RING_KV, false>(kv, w, smem, s_db);
+    else run_pass<DQ, D, 1, NW, BN, LD1, LD2, RING_Q, false>(q, w, smem, s_db);
 }
 
 // Second stage of the bias gradient: db[z] = sum of the `per_seq` partials of sequence z, in a fixed order
