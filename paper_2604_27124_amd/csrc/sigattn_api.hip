@@ -71,8 +71,12 @@ int launch_bwd(Params kv, Params q, hipStream_t stream) {
     static_assert(C::LDS_BYTES == Cfg<DQ, D, 1, NW, BN, LD, LD, RING_Q>::LDS_BYTES, "one LDS size for both passes");
     const long long kv_tiles = tiles_of<C>(kv), q_tiles = tiles_of<C>(q);
     kv.in_order = q.in_order = batch_order(kv, kv_tiles + q_tiles, C::BM) || batch_order(q, kv_tiles + q_tiles, C::BM);
+    // Longest first holds between the passes too: the one whose workgroups stream more rows starts.  (Cross-attention,
+    // 513 queries against 3001 keys: the dQ tiles, 47 streamed tiles each, had started behind all dK/dV tiles of 9
+    // and ran alone at the end; forward + backward 139 us, 111 us now.)
+    const int q_first = kv.N_str < q.N_str;
     return enqueue(sigattn_bwd_kernel<D, NW, BN, LD, LD, OCC, RING_KV, RING_Q>, kv_tiles + q_tiles, C::THREADS, C::LDS_BYTES,
-                   stream, kv, q, (int)kv_tiles);
+                   stream, kv, q, q_first, (int)(q_first ? q_tiles : kv_tiles));
 }
 
 // d = 64, backward: workgroups of four waves (128 owner rows, two to a CU, so that one fills the other's start and

@@ -906,11 +906,12 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_kernel(const Params p) {
     run_pass<MODE, D, QB, NW, BN, LD1, LD2, RING, WITH_DB>(p, map_work<C::BM, C::THREADS>(p, blockIdx.x, scratch), smem, s_db);
 }
 
-// Both halves of the backward pass in one launch.  Longest sequences first: workgroups [0, kv_tiles) take the dK/dV
-// tiles, the others the dQ tiles.  Batch order: the tiles of both passes of a head follow each other, so that the
+// Both halves of the backward pass in one launch.  Longest sequences first: workgroups [0, first_tiles) take the dK/dV
+// tiles, or with `q_first` the dQ tiles, the others those of the other pass.  Batch order: the tiles of both passes of a head follow each other, so that the
 // second pass finds the head's rows in the XCD's L2.
 template <int D, int NW, int BN, int LD1, int LD2, int OCC, int RING_KV, int RING_Q>
-__global__ void __launch_bounds__(NW * 64, OCC) sigattn_bwd_kernel(const Params kv, const Params q, const int kv_tiles) {
+__global__ void __launch_bounds__(NW * 64, OCC) sigattn_bwd_kernel(const Params kv, const Params q, const int q_first,
+                                                                        const int first_tiles) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ MapScratch scratch;
     __shared__ float s_db[1];
@@ -926,8 +927,9 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_bwd_kernel(const Params 
         w.n = owner_length(is_kv ? kv : q, w.z);
         w.m0 = (is_kv ? tile : tile - t_kv) * C::BM;
     } else {
-        is_kv = id < kv_tiles;
-        w = is_kv ? map_work<C::BM, C::THREADS>(kv, id, scratch) : map_work<C::BM, C::THREADS>(q, id - kv_tiles, scratch);
+        is_kv = (id < first_tiles) != (q_first != 0);
+        const int rest = id < first_tiles ? id : id - first_tiles;
+        w = is_kv ? map_work<C::BM, C::THREADS>(kv, rest, scratch) : map_work<C::BM, C::THREADS>(q, rest, scratch);
     }
     if (is_kv) run_pass<DKDV, D, 1, NW, BN, LD1, LD2, RING_KV, false>(kv, w, smem, s_db);
     else run_pass<DQ, D, 1, NW, BN, LD1, LD2, RING_Q, false>(q, w, smem, s_db);
