@@ -56,11 +56,46 @@ long long tiles_of(const Params &p) {                                       // o
     return ((long long)p.N + C::BM - 1) / C::BM * p.B * p.H;
 }
 
+// Batch order: owner tiles of a workgroup.  From the second on a tile costs no start (mapping, first loads: about 5 us of
+// a workgroup's life), while the last workgroups of the launch leave CUs idle for about half their life.  With R tiles
+// for each of the `slots` workgroups in flight and about 2 us per streamed 64-row tile the sum of both is least near a
+// multiple of the square root of R / (streamed tiles); below R = 5 the end of the launch counts for more.  Forward +
+// backward with 1 / 2 / 3 / 4 / 6 tiles, us: B = 512, H = 12, N = 512 1092 / 1061 / 1036 / 1028 / 1048; B = 200, H = 8,
+// N = 100 64 / 58 / 57 / 57 / 58; B = 128, H = 12, N = 1024 857 / 840 / 828 / 841 / 839; B = 64, H = 16, N = 700, d = 128
+// 815 / 763 / 755 / 774 / 768; B = 24, H = 12, N = 1500 391 / 388 / 389 / 395 / 403; B = 100, H = 4, N = 300 (R < 5) 64 / 68 /
+// 73 / 78 / 96.
+int tiles_per_workgroup(const Params &p, long long tiles, int slots) {
+    if (tiles < 5LL * slots) return 1;
+    const double j = std::sqrt(4.5 * (double)tiles / slots / ((p.N_str + 63) / 64));
+    return j >= 4.0 ? 4 : (int)(j + 0.5);
+}
+
+// Deals the owner tiles of every sequence to workgroups of `chain` tiles each, a quarter of that for the last quarter
+// of the sequences, so that the launch ends with short ones (B = 64, H = 16, N = 700, d = 128: 751 us; all alike 769).
+// At most 16384 workgroups per sequence and pass: products of two such counts stay below 2^31.
+template <class C>
+void deal(Params &p, int chain) {
+    const long long per_seq = ((long long)p.N + C::BM - 1) / C::BM * p.H;
+    auto groups = [&](int tiles) { const long long g = (per_seq + tiles - 1) / tiles; return (int)(g > 16384 ? 16384 : g); };
+    p.wide_groups = groups(chain);
+    p.groups = groups((chain + 3) / 4);
+    p.wide_seqs = (int)(p.B * 3LL / 4);
+}
+long long dealt(const Params &p) { return (long long)p.wide_seqs * p.wide_groups + (long long)(p.B - p.wide_seqs) * p.groups; }
+
 template <int MODE, int D, int QB, int NW, int BN, int LD1, int LD2, int OCC, int RING, bool WITH_DB = false>
 int launch(Params p, hipStream_t stream) {
     using C = Cfg<MODE, D, QB, NW, BN, LD1, LD2, RING>;
-    const long long wgs = tiles_of<C>(p);
-    p.in_order = batch_order(p, wgs, C::BM);
+    const long long tiles = tiles_of<C>(p);
+    long long wgs = tiles;
+    p.in_order = batch_order(p, tiles, C::BM);
+    if (p.in_order) {
+        const int chain = tiles_per_workgroup(p, tiles, 256 * OCC);
+        if (chain > 1) {
+            deal<C>(p, chain);
+            wgs = dealt(p);
+        }
+    }
     return enqueue(sigattn_kernel<MODE, D, QB, NW, BN, LD1, LD2, OCC, RING, WITH_DB>, wgs, C::THREADS, C::LDS_BYTES, stream, p);
 }
 
@@ -69,13 +104,23 @@ template <int D, int NW, int BN, int LD, int OCC, int RING_KV, int RING_Q>
 int launch_bwd(Params kv, Params q, hipStream_t stream) {
     using C = Cfg<DKDV, D, 1, NW, BN, LD, LD, RING_KV>;
     static_assert(C::LDS_BYTES == Cfg<DQ, D, 1, NW, BN, LD, LD, RING_Q>::LDS_BYTES, "one LDS size for both passes");
-    const long long kv_tiles = tiles_of<C>(kv), q_tiles = tiles_of<C>(q);
-    kv.in_order = q.in_order = batch_order(kv, kv_tiles + q_tiles, C::BM) || batch_order(q, kv_tiles + q_tiles, C::BM);
+    const long long kv_tiles = tiles_of<C>(kv), q_tiles = tiles_of<C>(q), tiles = kv_tiles + q_tiles;
+    long long wgs = tiles;
+    kv.in_order = q.in_order = batch_order(kv, tiles, C::BM) || batch_order(q, tiles, C::BM);
+    if (kv.in_order) {
+        const int a = tiles_per_workgroup(kv, tiles, 256 * OCC), b = tiles_per_workgroup(q, tiles, 256 * OCC);
+        const int chain = a < b ? a : b;
+        if (chain > 1) {
+            deal<C>(kv, chain);
+            deal<C>(q, chain);
+            wgs = dealt(kv) + dealt(q);
+        }
+    }
     // Longest first holds between the passes too: the one whose workgroups stream more rows starts.  (Cross-attention,
     // 513 queries against 3001 keys: the dQ tiles, 47 streamed tiles each, had started behind all dK/dV tiles of 9
     // and ran alone at the end; forward + backward 139 us, 111 us now.)
     const int q_first = kv.N_str < q.N_str;
-    return enqueue(sigattn_bwd_kernel<D, NW, BN, LD, LD, OCC, RING_KV, RING_Q>, kv_tiles + q_tiles, C::THREADS, C::LDS_BYTES,
+    return enqueue(sigattn_bwd_kernel<D, NW, BN, LD, LD, OCC, RING_KV, RING_Q>, wgs, C::THREADS, C::LDS_BYTES,
                    stream, kv, q, q_first, (int)(q_first ? q_tiles : kv_tiles));
 }
 

@@ -78,6 +78,9 @@ struct Params {
     int B, N, H;                     // N: padded length of the owner side
     int N_str;                       // padded length of the streamed side
     int in_order;                    // work mapping: 1 = batch order, 0 = longest sequences first
+    int groups;                      // batch order: 0 = a workgroup per owner tile, else this many for the owner tiles of
+                                     // a sequence, and `wide_groups` for those of each of the first `wide_seqs`
+    int wide_groups, wide_seqs;
     float *db_part;                  // DQ with bias gradient: one partial sum per owner tile, [B][H][tiles of a sequence]
 };
 
@@ -244,19 +247,45 @@ struct MapScratch {                       // LDS of the ranking (more than MAP_W
     int pick[4];                          // class holding this id (-1: padded part) | tiles before it | all valid tiles | found
 };
 
-struct Work { int z, h, n, m0; };          // one owner tile: sequence, head, valid owner rows of the sequence, first row
+// What one workgroup does: `count` owner tiles of one sequence, starting with the tile at row m0 of head h and going on
+// through the valid tiles of that head and of the heads behind it.  shares = 0: the tile alone, which may be padding.
+// Else the workgroup also writes its share of the zeros behind the sequence's valid tiles.
+struct Work { int z, n, h, m0, count, share, shares; };
 
-// Batch order: H * T ids per sequence, dealt to the XCDs in runs of consecutive tiles as above.  Which XCD takes
-// which run turns with the sequence, and where the tiles of a head begin turns with the head: runs and tiles
-// differ in their share of padding, and an XCD keeps the ids that hardware deals to it, a shader engine every
-// fourth of those, while the others wait for the slowest.  (Without the second turn 280 of the 512 workgroups
-// that fit were running in a launch of 24576: dK/dV at B = 512, N = 512 took 608 us instead of 488.)
-__device__ __forceinline__ void batch_order_work(const int id, const int H, const int T, int &z, int &h, int &tile) {
+// Batch order: position of `id` among the `cnt` ids [lo, lo + cnt) of sequence z, dealt to the XCDs in runs as above.
+// Which XCD takes which run turns with the sequence: runs differ in their share of padding, and an XCD keeps the ids
+// that hardware deals to it while the others wait for the slowest.
+__device__ __forceinline__ int batch_order_pos(const int id, const int lo, const int cnt, const int turn) {
+    return (xcd_major_index(id, lo, cnt) + turn % cnt) % cnt;
+}
+
+// A workgroup per owner tile: H * T ids per sequence, consecutive tiles of a head in a run.  Where the tiles of a head
+// begin turns with the head, since a shader engine gets every fourth id of an XCD's.  (Without this second turn 280 of
+// the 512 workgroups that fit were running in a launch of 24576: dK/dV at B = 512, N = 512 took 608 us instead of 488.)
+__device__ __forceinline__ void batch_order_tile(const int id, const int H, const int T, int &z, int &h, int &tile) {
     const int cnt = H * T;
     z = id / cnt;
-    const int e = (xcd_major_index(id, z * cnt, cnt) + (z & 7) * ((cnt + 7) >> 3)) % cnt;
+    const int e = batch_order_pos(id, z * cnt, cnt, (z & 7) * ((cnt + 7) >> 3));
     h = e / T;
     tile = (e - h * T + (T >= 4 ? h + z : (h + z) / (4 / T))) % T;
+}
+
+// Several owner tiles per workgroup: the last workgroups of a sequence have one tile less, so the turn is by one id more
+// than a run.
+__device__ __forceinline__ int shared_turn(const int z, const int cnt) {
+    return (int)((unsigned)z * (unsigned)(((cnt + 7) >> 3) + 1) % (unsigned)cnt);
+}
+
+// The sequence of an id and the ids of that sequence, [lo, lo + cnt).
+__device__ __forceinline__ void batch_order_range(const int id, const int wide_seqs, const int wide_groups, const int groups,
+                                                  int &z, int &lo, int &cnt) {
+    const int wide = wide_seqs * wide_groups;
+    const bool w = id < wide;
+    const int first = w ? 0 : wide;
+    cnt = w ? wide_groups : groups;
+    const int k = (id - first) / cnt;
+    z = (w ? 0 : wide_seqs) + k;
+    lo = first + k * cnt;
 }
 
 template <int BM>
@@ -267,6 +296,17 @@ __device__ __forceinline__ int owner_length(const Params &p, int b) {
     return v < 0 ? 0 : (v > p.N ? p.N : v);
 }
 
+// Workgroup `g` of the `groups` that share the valid owner tiles of sequence z (all heads, tile by tile).
+template <int BM>
+__device__ __forceinline__ Work batch_order_share(const Params &p, const int z, const int g, const int groups) {
+    const int n = owner_length(p, z);
+    const int tiles = (n + BM - 1) / BM, jobs = tiles * p.H;
+    const int each = jobs / groups, extra = jobs % groups;
+    const int first = g * each + (g < extra ? g : extra), count = each + (g < extra ? 1 : 0);
+    const int h = count > 0 ? first / tiles : 0;
+    return {z, n, h, (first - h * tiles) * BM, count, g, groups};
+}
+
 template <int BM, int THREADS>
 __device__ __forceinline__ Work map_work(const Params &p, const int id, MapScratch &scratch) {
     static_assert((BM & (BM - 1)) == 0, "owner tile rows: a power of two");
@@ -274,10 +314,15 @@ __device__ __forceinline__ Work map_work(const Params &p, const int id, MapScrat
     int z, h, n, m0;
     int *const s_res = scratch.res;
     auto len_of = [&](int b) { return owner_length(p, b); };
+    if (p.groups) {
+        int lo, cnt;
+        batch_order_range(id, p.wide_seqs, p.wide_groups, p.groups, z, lo, cnt);
+        return batch_order_share<BM>(p, z, batch_order_pos(id, lo, cnt, shared_turn(z, cnt)), cnt);
+    }
     if (p.in_order) {
         int tile;
-        batch_order_work(id, p.H, T, z, h, tile);
-        return {z, h, len_of(z), tile * BM};
+        batch_order_tile(id, p.H, T, z, h, tile);
+        return {z, len_of(z), h, tile * BM, 1, 0, 0};
     }
     if (p.B <= MAP_WAVE_B) {
         // Id ranges as below: the valid tiles of every sequence, longest first, H ids per tile; then the padded
@@ -319,7 +364,7 @@ __device__ __forceinline__ Work map_work(const Params &p, const int id, MapScrat
             h = e / cnt;
             m0 = (e % cnt) * BM;
         }
-        return {z, h, n, m0};
+        return {z, n, h, m0, 1, 0, 0};
     }
     // ---- more sequences than lanes.  A sequence's class is its number of owner tiles
     // (class 0 = T tiles, the longest; T <= MAP_CLASSES is the host's rule).
@@ -400,10 +445,25 @@ __device__ __forceinline__ Work map_work(const Params &p, const int id, MapScrat
         if (s_pick[3]) break;
         running += total;
     }
-    return {s_res[0], s_res[2], s_res[1], s_res[3]};
+    return {s_res[0], s_res[1], s_res[2], s_res[3], 1, 0, 0};
 }
 
-// One owner tile of one pass.  `smem`: Cfg::LDS_BYTES bytes.
+// The lane, worked out anew: what is computed from it is computed again for every owner tile instead of holding
+// registers through the main loop, which has none to spare.
+__device__ __forceinline__ int fresh_lane() {
+    int all = -1;
+    asm volatile("" : "+s"(all));
+    return __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
+}
+
+// A pointer that is the same in all lanes, in scalar registers.
+__device__ __forceinline__ bf16_t *uniform_ptr(const bf16_t *p) {
+    const unsigned long long a = reinterpret_cast<unsigned long long>(p);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+    return reinterpret_cast<bf16_t *>((unsigned long long)hi << 32 | lo);
+}
+
+// The owner tiles of one workgroup, one pass.  `smem`: Cfg::LDS_BYTES bytes.
 template <int MODE, int D, int QB, int NW, int BN, int LD1, int LD2, int RING, bool WITH_DB>
 __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsigned char *const smem, float *const s_db) {
     static_assert(!WITH_DB || MODE == DQ, "the bias gradient rides on the dQ kernel");
@@ -417,13 +477,14 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
     bf16_t *y2s = y1s + C::NBUF * BN * LD1;                         // [NBUF][BN][LD2]
 
     const int z = __builtin_amdgcn_readfirstlane(work.z);      // uniform across the workgroup: keep them in scalar registers
-    const int h = __builtin_amdgcn_readfirstlane(work.h);
     const int n = __builtin_amdgcn_readfirstlane(work.n);
-    const int m0 = __builtin_amdgcn_readfirstlane(work.m0);
-    const int m1 = (m0 + C::BM < p.N) ? m0 + C::BM : p.N;
+    int h = __builtin_amdgcn_readfirstlane(work.h);                 // owner tile in hand, and how many are left with it
+    int m0 = __builtin_amdgcn_readfirstlane(work.m0);
+    int left = __builtin_amdgcn_readfirstlane(work.count);
+    const int share = __builtin_amdgcn_readfirstlane(work.share), shares = __builtin_amdgcn_readfirstlane(work.shares);
     const size_t row_stride = (size_t)p.H * D;
-    const size_t slice = ((size_t)z * p.N * p.H + h) * D;           // owner side: element offset of row 0 of (z, h)
-    const size_t slice_s = ((size_t)z * p.N_str * p.H + h) * D;     // streamed side
+    const size_t seq_base = (size_t)z * p.N * row_stride;           // owner side: element offset of row 0 of sequence z
+    const size_t seq_base_s = (size_t)z * p.N_str * row_stride;     // streamed side
     int ns = n;                                                     // valid rows of the streamed side
     if (p.seqlens_str != p.seqlens || p.N_str != p.N) {             // self-attention: the mapping already has it
         ns = p.seqlens_str[z];
@@ -431,13 +492,40 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
     }
     ns = __builtin_amdgcn_readfirstlane(ns);
 
-    auto db_slot = [&]() { return ((size_t)z * p.H + h) * ((p.N + C::BM - 1) / C::BM) + m0 / C::BM; };
+    const int T = owner_tiles<C::BM>(p);
+    auto db_slot = [&](int head, int row) { return ((size_t)z * p.H + head) * T + row / C::BM; };
 
-    // Wholly padded owner tile, or nothing to stream: write zeros, do nothing else (block-sparse early exit).
-    if (m0 >= n || ns == 0) {
-        zero_rows<D, C::THREADS>(p.out0, slice, row_stride, m0, m1);
-        if (MODE == DKDV) zero_rows<D, C::THREADS>(p.out1, slice, row_stride, m0, m1);
-        if (WITH_DB && threadIdx.x == 0) p.db_part[db_slot()] = 0.f;
+    // Padding (block-sparse early exit): owner rows in tiles that are wholly padded, or all rows if there is nothing to
+    // stream, are zeros and nothing else.
+    const int valid_tiles = ns == 0 ? 0 : (n + C::BM - 1) / C::BM;  // per head
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (shares == 0) {
+        if (m0 >= n || ns == 0) {
+            const int m1 = (m0 + C::BM < p.N) ? m0 + C::BM : p.N;
+            zero_rows<D, C::THREADS>(p.out0, seq_base + (size_t)h * D, row_stride, m0, m1);
+            if (MODE == DKDV) zero_rows<D, C::THREADS>(p.out1, seq_base + (size_t)h * D, row_stride, m0, m1);
+            if (WITH_DB && tid == 0) p.db_part[db_slot(h, m0)] = 0.f;
+            return;
+        }
+    }
+    auto zero_share = [&]() {                                       // this workgroup's share of them, all heads together
+        if (shares == 0 || valid_tiles == T) return;
+        const u32x4 z4 = {0u, 0u, 0u, 0u};
+        const int me = share * C::THREADS + wave * 64 + fresh_lane();
+        const size_t from = seq_base + (size_t)valid_tiles * C::BM * row_stride;
+        const size_t chunks = (size_t)(p.N - valid_tiles * C::BM) * (row_stride / 8);
+        for (size_t i = (size_t)me; i < chunks; i += (size_t)shares * C::THREADS) {
+            *reinterpret_cast<u32x4 *>(p.out0 + from + i * 8) = z4;
+            if (MODE == DKDV) *reinterpret_cast<u32x4 *>(p.out1 + from + i * 8) = z4;
+        }
+        if (WITH_DB) {
+            const int padded = T - valid_tiles;
+            for (int i = me; i < padded * p.H; i += shares * C::THREADS)
+                p.db_part[db_slot(i / padded, (valid_tiles + i % padded) * C::BM)] = 0.f;
+        }
+    };
+    if (left == 0 || ns == 0) {
+        zero_share();
         return;
     }
 
@@ -446,54 +534,60 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
     const bf16_t *y1 = (MODE == DKDV) ? p.q : p.k;                  // streamed tensors
     const bf16_t *y2 = (MODE == DKDV) ? p.d_o : p.v;
 
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int lane = tid & 63;
     const int c = lane & 31, g = lane >> 5;
-    const int wrow0 = m0 + wave * 32 * QB;                          // first owner row of this wave
 
     // sigma(x) = 1 / (1 + cb 2^t') with t' = c1 <q, k>, c1 = -scale log2 e, cb = 2^(-bias log2 e).
     // c1 is folded into the owner operand of the score contraction (one extra bf16 rounding of that
     // operand), so t' leaves the MFMA ready for exp2; cb rides on the FMA that forms the denominator.
     // The exponent of cb is clamped to +-126 (|bias| <= 87.3 is exact; beyond that sigma is saturated).
     // cb is finite and non-zero, so cb 2^t' is 0, finite or +inf but never NaN, and P lands in [0, 1].
-    const float c1 = -p.scale * LOG2E;
-    const float cb = __builtin_amdgcn_exp2f(__builtin_fminf(__builtin_fmaxf(-p.bias[z] * LOG2E, -126.0f), 126.0f));
+    const float c1 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, -p.scale * LOG2E)));
+    const float cb = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int,
+        __builtin_amdgcn_exp2f(__builtin_fminf(__builtin_fmaxf(-p.bias[z] * LOG2E, -126.0f), 126.0f)))));
 
-    // ---- owner rows -> registers (B operands): lane holds row c of each 32-block, d = 16 ks + 8 g + 0..7
+    // ---- owner rows -> registers (B operands): lane holds row c of each 32-block, d = 16 ks + 8 g + 0..7.  Read through
+    // a buffer descriptor that ends with the sequence's last valid row (see load_tile below): rows behind it are zeros.
     bf16x8 xa[QB][C::KS];
     bf16x8 xb[Q2][HAS2 ? C::KS : 1];
+    auto row_offset = [&]() {                                       // bytes from an owner tile's first row to this lane's
+        const int l = fresh_lane();
+        return ((unsigned)(wave * 32 * QB + (l & 31)) * (unsigned)row_stride + 8u * (l >> 5)) * 2u;
+    };
+    const int block_bytes = 32 * (int)row_stride * 2;
+    auto load_owner = [&](const int head, const int row0) {
+        const int rows = n - row0 < C::BM ? n - row0 : C::BM;
+        const size_t base = seq_base + (size_t)row0 * row_stride + (size_t)head * D;
+        const int bytes = __builtin_amdgcn_readfirstlane(rows * (int)row_stride * 2);
+        const auto d1 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(x1 + base), 0, bytes, 0x00027000);
+        const auto d2 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr((HAS2 ? x2 : x1) + base), 0, bytes, 0x00027000);
+        const int off = (int)row_offset();
+        // the rows that are scaled come last: a wait for them is a wait for all
+        if (HAS2)
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int r = wrow0 + 32 * qb + c;
-        const bool ok = r < n;
-        const size_t off = slice + (size_t)(ok ? r : 0) * row_stride + 8 * g;
+            for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) {
-            u32x4 t = {0u, 0u, 0u, 0u};
-            if (ok) t = *reinterpret_cast<const u32x4 *>(x1 + off + 16 * ks);
-            xa[qb][ks] = __builtin_bit_cast(bf16x8, t);      // scaled by c1 once the streamed tiles are requested
-            if (HAS2) {
-                u32x4 t2 = {0u, 0u, 0u, 0u};
-                if (ok) t2 = *reinterpret_cast<const u32x4 *>(x2 + off + 16 * ks);
-                xb[qb][ks] = __builtin_bit_cast(bf16x8, t2);
-            }
-        }
-    }
+                for (int ks = 0; ks < C::KS; ++ks)
+                    xb[HAS2 ? qb : 0][HAS2 ? ks : 0] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(d2, off + 32 * ks, qb * block_bytes, 0));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int ks = 0; ks < C::KS; ++ks)
+                xa[qb][ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(d1, off + 32 * ks, qb * block_bytes, 0));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto scale_owner = [&]() {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int ks = 0; ks < C::KS; ++ks) xa[qb][ks] = scale_bf16x8(xa[qb][ks], c1);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load_owner(h, m0);                                        // scaled by c1 once the streamed tiles are requested
 
     f32x16 acc0[QB][MB];                           // FWD: O^T;  DQ: dQ^T;  DKDV: dK^T
     f32x16 acc1[MODE == DKDV ? QB : 1][MODE == DKDV ? MB : 1];   // DKDV: dV^T
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc0[qb][mb][i] = 0.f;
-            if (MODE == DKDV) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc1[qb][mb][i] = 0.f;
-            }
-        }
-
     // Bias gradient db = sum of dS over all valid pairs: one more (small) MFMA per 16 streamed rows with an
     // all-ones A operand sums the bf16 values that also feed dQ.  v_mfma_f32_16x16x32_bf16 reads the B operand
     // of the 32-wide shape as 16 columns x 32 contraction slots: column j of its result is the sum over the
@@ -502,10 +596,6 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
     f32x4 accdb[WITH_DB ? QB : 1];
     bf16x8 ones;
     if (WITH_DB) {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) accdb[qb][i] = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) ones[i] = (bf16_t)1.0f;
     }
@@ -526,13 +616,18 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
     // tile by tile in scalar registers; the byte offset inside a tile is a lane constant.
     const unsigned ld_off0 = ((unsigned)r0 * (unsigned)row_stride + (unsigned)col0) * 2u;
     const unsigned pass_bytes = (unsigned)RPI * (unsigned)row_stride * 2u;
-    const bf16_t *next1 = y1 + slice_s, *next2 = y2 + slice_s;     // first row of the tile that is requested next
-    int rows_left = ns;                                             // valid rows from there on (negative past the end)
+    // The stream goes on from one owner tile to the next: behind the last tile of a pass over the streamed rows
+    // comes the first tile of the next pass, of the next head where the owner tiles of this one are done.
+    const bf16_t *head1 = y1 + seq_base_s + (size_t)h * D, *head2 = y2 + seq_base_s + (size_t)h * D;
+    const bf16_t *next1 = head1, *next2 = head2;                    // first row of the tile that is requested next
+    int rows_left = ns;                                             // valid rows from there on (none past the end)
+    int passes_left = left, tiles_of_head = valid_tiles - m0 / C::BM;   // passes with this one; those of this head
     auto load_tile = [&]() {
-        const int rows = rows_left < 0 ? 0 : (rows_left > BN ? BN : rows_left);
-        const int bytes = rows * (int)row_stride * 2;
-        const auto d1 = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(next1), 0, bytes, 0x00027000);
-        const auto d2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(next2), 0, bytes, 0x00027000);
+        // readfirstlane: without it the compiler moved some of this uniform state to vector registers and wrapped
+        // every load in a loop over the "different" descriptors of the lanes
+        const int bytes = __builtin_amdgcn_readfirstlane((rows_left < BN ? rows_left : BN) * (int)row_stride * 2);
+        const auto d1 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(next1), 0, bytes, 0x00027000);
+        const auto d2 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(next2), 0, bytes, 0x00027000);
 #pragma unroll
         for (int it = 0; it < C::PER; ++it) {
             st1[it] = __builtin_amdgcn_raw_buffer_load_b128(d1, (int)ld_off0, it * (int)pass_bytes, 0);
@@ -540,7 +635,33 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
         }
         next1 += (size_t)BN * row_stride;
         next2 += (size_t)BN * row_stride;
-        rows_left -= BN;
+        rows_left = rows_left > BN ? rows_left - BN : 0;
+        // d = 64: a branch that is rarely taken (N = 8192, forward + backward: 1533 us; with selects 1557).  d = 128:
+        // selects, since the forward pass comes here inside a tile (12 x 1537 rows, H = 16: 162 us; with the branch 165).
+        if constexpr (D == 64) {
+            if (rows_left == 0 && passes_left > 1) {
+                --passes_left;
+                if (--tiles_of_head == 0) {
+                    tiles_of_head = valid_tiles;
+                    head1 += D;
+                    head2 += D;
+                }
+                next1 = head1;
+                next2 = head2;
+                rows_left = ns;
+            }
+        } else {
+            const int wrap = (rows_left == 0) & (passes_left > 1);
+            passes_left -= wrap;
+            tiles_of_head -= wrap;
+            const int turn = wrap & (tiles_of_head == 0);
+            tiles_of_head = turn ? valid_tiles : tiles_of_head;
+            head1 += turn ? D : 0;
+            head2 += turn ? D : 0;
+            next1 = wrap ? head1 : next1;
+            next2 = wrap ? head2 : next2;
+            rows_left = wrap ? ns : rows_left;
+        }
     };
     bf16_t *const w1 = y1s + r0 * LD1 + lds_shift<C::LM1>(r0) + col0;   // LDS home of this thread's chunk, pass 0, slot 0
     bf16_t *const w2 = y2s + r0 * LD2 + lds_shift<C::LM2>(r0) + col0;
@@ -610,8 +731,13 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
 
     // One pipeline step on the block (slot, nb) of parity PAR (compile-time nb).  Slots run in program
     // order; a scheduling fence closes each of them.
-    auto step = [&](auto has_next_c, auto drain_c, auto nb_c, auto slot, auto store_at_c, const int store_slot) {
+    // When the next tile is requested: behind the barrier that ends a tile, or right behind the stores of the one before
+    // (a quarter of a tile earlier), which only the d = 128 forward pass gains from (12 x 1537 rows, H = 16: 172 -> 167 us;
+    // d = 64, N = 8192, forward + backward 1543 -> 1559 us).
+    constexpr bool LOAD_EARLY = MODE == FWD && D == 128;
+    auto step = [&](auto has_prev_c, auto has_next_c, auto drain_c, auto nb_c, auto slot, auto store_at_c, const int store_slot) {
         constexpr int STORE_AT = decltype(store_at_c)::value;   // slot before which the staged tile goes to LDS (-1: never)
+        constexpr bool HAS_PREV = decltype(has_prev_c)::value;  // a block went before: its output contractions
         constexpr bool HAS_NEXT = decltype(has_next_c)::value;  // a block follows: compute its scores
         constexpr bool DRAIN = decltype(drain_c)::value;        // only the output contractions of the last block
         constexpr int nb = decltype(nb_c)::value;
@@ -635,6 +761,7 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
             }
             if constexpr (k == STORE_AT) {
                 store_tile(store_slot);
+                if constexpr (LOAD_EARLY) load_tile();
                 __builtin_amdgcn_sched_barrier(0);
             }
             // ---- the MFMA of this slot
@@ -649,7 +776,7 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
                             ring[(G0 + j) % RING], xb[HAS2 ? qb : 0][HAS2 ? ks : 0],
                             ks == 0 ? zero : dbuf[PAR ^ 1][HAS2 ? qb : 0], 0, 0, 0);
                 }
-            } else {
+            } else if constexpr (HAS_PREV) {
                 constexpr int jj = j - NA, which = jj % NO, idx = jj / NO, half = idx / MB, mb = idx % MB;
                 const bf16x8 a = ring[(G0 + j) % RING];
                 if constexpr (MODE == FWD) {            // O^T += V^T P^T
@@ -668,7 +795,9 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
                 }
             }
             // ---- the register of the previous operand is free now: request the operand RING - 1 ahead
-            if constexpr (qb == 0 && (!DRAIN || j + RING - 1 < NOPS)) {
+            constexpr int ahead = j + RING - 1;         // those of contractions that are not made are not read
+            constexpr bool wanted = ahead < NA ? HAS_NEXT : (ahead < NOPS ? HAS_PREV : !DRAIN && (HAS_NEXT || ahead >= NOPS + NA));
+            if constexpr (qb == 0 && wanted) {
                 ring[(G0 + j + RING - 1) % RING] = fetch(IntC<j + RING - 1>{}, slot, nb_c);
             }
             // ---- this slot's share of the sigmoid
@@ -719,17 +848,7 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
     using T_ = IntC<1>;
     using F_ = IntC<0>;
 
-    // ---- prologue: tiles 0 and 1 into the ring, tile 2 into registers, scores of block 0 computed.
-    // The step on block 0 contracts its (zero) "previous" operands with the last block of ring slot 3:
-    // that block is cleared first, so that 0 x stale LDS bits can never be 0 x NaN.
-    for (int cid = tid; cid < 32 * (LD1 / 8); cid += C::THREADS) {
-        const u32x4 z4 = {0u, 0u, 0u, 0u};
-        *reinterpret_cast<u32x4 *>(y1s + (C::NBUF * BN - 32) * LD1 + cid * 8) = z4;
-    }
-    for (int cid = tid; cid < 32 * (LD2 / 8); cid += C::THREADS) {
-        const u32x4 z4 = {0u, 0u, 0u, 0u};
-        *reinterpret_cast<u32x4 *>(y2s + (C::NBUF * BN - 32) * LD2 + cid * 8) = z4;
-    }
+    // ---- prologue: tiles 0 and 1 of the stream into the ring, tile 2 into registers
     {   // the first three tiles are requested back to back, so their latencies overlap
         load_tile();
         u32x4 a1[C::PER], a2[C::PER];
@@ -740,11 +859,7 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
 #pragma unroll
         for (int it = 0; it < C::PER; ++it) { b1[it] = st1[it]; b2[it] = st2[it]; }
         load_tile();
-        // every request of the prologue is in flight now; the owner rows, requested first, arrive first
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int ks = 0; ks < C::KS; ++ks) xa[qb][ks] = scale_bf16x8(xa[qb][ks], c1);
+        scale_owner();                             // the owner rows, requested first, arrive first
 #pragma unroll
         for (int it = 0; it < C::PER; ++it) {
             *reinterpret_cast<u32x4 *>(w1 + (it * RPI) * LD1) = a1[it];
@@ -753,36 +868,9 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
             *reinterpret_cast<u32x4 *>(w2 + (BN + it * RPI) * LD2) = b2[it];
         }
     }
-    __syncthreads();
 
-    {
-        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) {
-            const bf16x8 a1 = lds_read_rows(rd1 + 16 * ks);
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-                sbuf[0][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, xa[qb][ks], ks == 0 ? zero : sbuf[0][qb], 0, 0, 0);
-            if (HAS2) {
-                const bf16x8 a2 = lds_read_rows(rd2 + 16 * ks);
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb)
-                    dbuf[0][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, xb[qb][ks], ks == 0 ? zero : dbuf[0][qb], 0, 0, 0);
-            }
-        }
-        const u32x4 z4 = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                pbuf[1][qb][half] = z4;
-                if (HAS2) dsbuf[1][qb][half] = z4;
-            }
-    }
-    // operands 0 .. RING - 2 of the first step
-    static_for<0, RING - 1>([&](auto J_) { ring[decltype(J_)::value % RING] = fetch(J_, IntC<0>{}, IntC<0>{}); });
-
-    // ---- main loop over all tiles but the last: every block has a successor.  The loop is
+    // ---- the steps of an owner tile: block 0, which has no block before it; all blocks up to the last tile's first
+    // one; the last tile's other blocks, the last of which has no successor; a step that only drains.  The loop is
     // unrolled over the four ring slots so that every LDS address is a lane constant plus an immediate.
     // Tile t + 2 goes to slot (t + 2) % 4 = (t - 2) % 4, last read during the first step of tile t - 1 (as
     // the previous block); every wave passed the barrier that ended tile t - 1.  The staged registers are
@@ -790,7 +878,8 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
     // those writes have left the LDS queue: LDS operations of a wave complete in order, so it is enough to
     // let the READS_AFTER operand reads issued behind them stay in flight.  The tile becomes visible at
     // that barrier, most of a tile before its first read near the end of tile t + 1.
-    // (Past the end the writes are harmless: the registers then hold zeros and the slot is not live.)
+    // Here t counts through all owner tiles of the workgroup: at the last tile of one the first ones of the next are
+    // on their way (past the end zeros, which are not stored), so that the next one starts without waiting for memory.
     constexpr auto reads_from = [](int first_slot) {
         int cnt = 0;
         for (int k = first_slot; k < SLOTS; k += QB) {
@@ -806,95 +895,150 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
     }();
     constexpr int READS_AFTER = reads_from(STORE_AT);
     static_assert(READS_AFTER <= 15 && STORE_AT < SLOTS, "more reads behind the tile store than the LDS counter can express");
-    auto tile_body = [&](auto slot_c) {
+    using StoreAt = IntC<STORE_AT>;
+    using NoStore = IntC<-1>;
+    auto tile_body = [&](auto slot_c) {            // from the second block of a tile through the first of the next
         constexpr int slot = decltype(slot_c)::value;
-        static_for<0, NB>([&](auto nb_) {
-            step(T_{}, F_{}, nb_, slot_c, IntC<(decltype(nb_)::value + 1 < NB) ? -1 : STORE_AT>{}, (slot + 2) & (C::NBUF - 1));
+        static_for<1, NB>([&](auto nb_) {
+            if constexpr (decltype(nb_)::value + 1 < NB) step(T_{}, T_{}, F_{}, nb_, slot_c, NoStore{}, 0);
+            else step(T_{}, T_{}, F_{}, nb_, slot_c, StoreAt{}, (slot + 2) & (C::NBUF - 1));
         });
         asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(READS_AFTER) : "memory");
-        load_tile();
+        if constexpr (!LOAD_EARLY) load_tile();
+        step(T_{}, T_{}, F_{}, IntC<0>{}, IntC<(slot + 1) & (C::NBUF - 1)>{}, NoStore{}, 0);
     };
-    int t = 0;
-    const int last = ntiles - 1;
-    int slot_rt = 0;
-    while (true) {
-        if (t >= last) { slot_rt = 0; break; }
-        tile_body(IntC<0>{}); ++t;
-        if (t >= last) { slot_rt = 1; break; }
-        tile_body(IntC<1>{}); ++t;
-        if (t >= last) { slot_rt = 2; break; }
-        tile_body(IntC<2>{}); ++t;
-        if (t >= last) { slot_rt = 3; break; }
-        tile_body(IntC<3>{}); ++t;
-    }
-
-    // ---- last tile: its final block has no successor; then the output contractions of that final block (a step
-    // that only drains).
-    {
-        const DynInt slot{slot_rt};
-        static_for<0, NB>([&](auto nb_) {
-            step(IntC<(decltype(nb_)::value + 1 < NB) ? 1 : 0>{}, F_{}, nb_, slot, IntC<-1>{}, 0);
-        });
-        const DynInt slot_next{(slot_rt + 1) & (C::NBUF - 1)};
-        step(F_{}, T_{}, IntC<0>{}, slot_next, IntC<-1>{}, 0);
-    }
-
-    if constexpr (WITH_DB) {
-        // Row 0 of accdb (register 0 of lanes 0..15) holds 16 partial sums that together cover every dS of
-        // this wave.  Owner rows beyond the valid length carry dO = 0, hence dS = 0.  Fixed-order sums: lanes
-        // by butterfly, waves through LDS, workgroups in a second kernel.
-        float v = 0.f;
+    int slot_rt = 0;                               // ring slot of the tile in hand
+    for (;;) {
+        // the tiles stored last are visible, and nobody reads the slot that is written next
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) v += accdb[qb][0];
-        v = (lane < 16) ? v : 0.f;
+        for (int qb = 0; qb < QB; ++qb) {
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0) s_db[wave] = v;
-        __syncthreads();
-        if (tid == 0) {
-            float t = 0.f;
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int w = 0; w < NW; ++w) t += s_db[w];
-            p.db_part[db_slot()] = t * cb;                // the summed values are dS / cb
+                for (int i = 0; i < 16; ++i) {
+                    acc0[qb][mb][i] = 0.f;
+                    if (MODE == DKDV) acc1[MODE == DKDV ? qb : 0][MODE == DKDV ? mb : 0][i] = 0.f;
+                }
+            if (WITH_DB)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) accdb[WITH_DB ? qb : 0][i] = 0.f;
         }
-    }
-
-    // ---- epilogue: transposed fp32 accumulators -> bf16 rows.  Lane (c, g) holds owner row c of each block;
-    // registers 4 q4 .. 4 q4 + 3 of output block mb hold head-dim columns out_col(mb, q4) + 4 g + 0..3 of the
-    // layout the transposed operand was read with (plain: 32 mb + 8 q4).  The two lanes of a row (32 apart)
-    // exchange halves -- lane g = 0 takes the even q4, lane g = 1 the odd ones -- so that each lane stores
-    // whole 16-byte chunks: a quarter of the store instructions and write requests of 8-byte stores.
-    using TL_ACC0 = TrLayout<(MODE == FWD) ? C::LM2 : C::LM1>;      // FWD contracts V^T; DQ K^T; DKDV Q^T (acc0), dO^T (acc1)
-    using TL_ACC1 = TrLayout<C::LM2>;
-    const float oscale = (MODE == FWD) ? 1.0f : p.scale * cb;       // dQ and dK carry the factor `scale`; their sums are over dS / cb
-    auto chunk = [&](const f32x16 &a, const int pr, const float f) {   // columns of q4 = 2 pr + g
-        const unsigned e0 = pack_bf16(a[8 * pr + 0] * f, a[8 * pr + 1] * f), e1 = pack_bf16(a[8 * pr + 2] * f, a[8 * pr + 3] * f);
-        const unsigned o0 = pack_bf16(a[8 * pr + 4] * f, a[8 * pr + 5] * f), o1 = pack_bf16(a[8 * pr + 6] * f, a[8 * pr + 7] * f);
-        const auto s0 = __builtin_amdgcn_permlane32_swap(e0, o0, false, false);   // {lower half: e0 | o0 of g = 0, upper: of g = 1}
-        const auto s1 = __builtin_amdgcn_permlane32_swap(e1, o1, false, false);
-        const u32x4 w = {s0[0], s1[0], s0[1], s1[1]};
-        return w;
-    };
+        {
+            const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int r = wrow0 + 32 * qb + c;
-        const bool inside = r < p.N;                                 // both lanes of a row agree on these two
-        const bool ok = r < n;                                       // padded owner rows are written as zero
-        const size_t off = slice + (size_t)(inside ? r : 0) * row_stride + 8 * g;
-        const u32x4 z4 = {0u, 0u, 0u, 0u};
+            for (int ks = 0; ks < C::KS; ++ks) {
+                const bf16x8 a1 = lds_read_rows(rd1 + slot_rt * BN * LD1 + 16 * ks);
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
+                for (int qb = 0; qb < QB; ++qb)
+                    sbuf[0][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, xa[qb][ks], ks == 0 ? zero : sbuf[0][qb], 0, 0, 0);
+                if (HAS2) {
+                    const bf16x8 a2 = lds_read_rows(rd2 + slot_rt * BN * LD2 + 16 * ks);
 #pragma unroll
-            for (int pr = 0; pr < 2; ++pr) {
-                const u32x4 w0 = chunk(acc0[qb][mb], pr, oscale);
-                if (inside) *reinterpret_cast<u32x4 *>(p.out0 + off + TL_ACC0::out_col(mb, 2 * pr)) = ok ? w0 : z4;
-                if (MODE == DKDV) {
-                    const u32x4 w1 = chunk(acc1[MODE == DKDV ? qb : 0][MODE == DKDV ? mb : 0], pr, 1.0f);
-                    if (inside) *reinterpret_cast<u32x4 *>(p.out1 + off + TL_ACC1::out_col(mb, 2 * pr)) = ok ? w1 : z4;
+                    for (int qb = 0; qb < QB; ++qb)
+                        dbuf[0][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, xb[qb][ks], ks == 0 ? zero : dbuf[0][qb], 0, 0, 0);
                 }
             }
         }
+        // operands 0 .. RING - 2 of the first step
+        static_for<0, RING - 1>([&](auto J_) {
+            if constexpr (decltype(J_)::value < NA) ring[decltype(J_)::value % RING] = fetch(J_, DynInt{slot_rt}, IntC<0>{});
+        });
+        step(F_{}, T_{}, F_{}, IntC<0>{}, DynInt{slot_rt}, NoStore{}, 0);
+
+        int t = ntiles - 1;
+        while (t > 0) {
+            if (slot_rt == 0) { tile_body(IntC<0>{}); slot_rt = 1; --t; }
+            if (t > 0 && slot_rt == 1) { tile_body(IntC<1>{}); slot_rt = 2; --t; }
+            if (t > 0 && slot_rt == 2) { tile_body(IntC<2>{}); slot_rt = 3; --t; }
+            if (t > 0 && slot_rt == 3) { tile_body(IntC<3>{}); slot_rt = 0; --t; }
+        }
+
+        // ---- last tile.  The owner rows are not needed any more: request those of the next owner tile.
+        const int h_done = h, m0_done = m0;
+        const bool more = left > 1;
+        m0 += C::BM;
+        if (m0 >= n) { m0 = 0; ++h; }
+        if (more) load_owner(h, m0);
+        {
+            const DynInt slot{slot_rt};
+            static_for<1, NB>([&](auto nb_) {
+                step(T_{}, IntC<(decltype(nb_)::value + 1 < NB) ? 1 : 0>{}, F_{}, nb_, slot, NoStore{}, 0);
+            });
+            const DynInt slot_next{(slot_rt + 1) & (C::NBUF - 1)};
+            step(T_{}, F_{}, T_{}, IntC<0>{}, slot_next, NoStore{}, 0);
+            if (more) {
+                store_tile((slot_rt + 2) & (C::NBUF - 1));
+                load_tile();
+            }
+        }
+
+        if constexpr (WITH_DB) {
+            // Row 0 of accdb (register 0 of lanes 0..15) holds 16 partial sums that together cover every dS of
+            // this wave.  Owner rows beyond the valid length carry dO = 0, hence dS = 0.  Fixed-order sums: lanes
+            // by butterfly, waves through LDS, workgroups in a second kernel.
+            float v = 0.f;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) v += accdb[qb][0];
+            v = (lane < 16) ? v : 0.f;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+            if (lane == 0) s_db[wave] = v;
+            __syncthreads();
+            if (tid == 0) {
+                float t = 0.f;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) t += s_db[w];
+                p.db_part[db_slot(h_done, m0_done)] = t * cb;                // the summed values are dS / cb
+            }
+        }
+
+        // ---- epilogue: transposed fp32 accumulators -> bf16 rows.  Lane (c, g) holds owner row c of each block;
+        // registers 4 q4 .. 4 q4 + 3 of output block mb hold head-dim columns out_col(mb, q4) + 4 g + 0..3 of the
+        // layout the transposed operand was read with (plain: 32 mb + 8 q4).  The two lanes of a row (32 apart)
+        // exchange halves -- lane g = 0 takes the even q4, lane g = 1 the odd ones -- so that each lane stores
+        // whole 16-byte chunks: a quarter of the store instructions and write requests of 8-byte stores.
+        using TL_ACC0 = TrLayout<(MODE == FWD) ? C::LM2 : C::LM1>;      // FWD contracts V^T; DQ K^T; DKDV Q^T (acc0), dO^T (acc1)
+        using TL_ACC1 = TrLayout<C::LM2>;
+        const float oscale = (MODE == FWD) ? 1.0f : p.scale * cb;       // dQ and dK carry the factor `scale`; their sums are over dS / cb
+        auto chunk = [&](const f32x16 &a, const int pr, const float f) {   // columns of q4 = 2 pr + g
+            const unsigned e0 = pack_bf16(a[8 * pr + 0] * f, a[8 * pr + 1] * f), e1 = pack_bf16(a[8 * pr + 2] * f, a[8 * pr + 3] * f);
+            const unsigned o0 = pack_bf16(a[8 * pr + 4] * f, a[8 * pr + 5] * f), o1 = pack_bf16(a[8 * pr + 6] * f, a[8 * pr + 7] * f);
+            const auto s0 = __builtin_amdgcn_permlane32_swap(e0, o0, false, false);   // {lower half: e0 | o0 of g = 0, upper: of g = 1}
+            const auto s1 = __builtin_amdgcn_permlane32_swap(e1, o1, false, false);
+            const u32x4 w = {s0[0], s1[0], s0[1], s1[1]};
+            return w;
+        };
+        // Stores go through descriptors that end with the padded length: rows behind it are dropped, and no branch
+        // keeps the compiler from counting what is in flight when the next tile's owner rows are waited for.
+        const int rows = p.N - m0_done < C::BM ? p.N - m0_done : C::BM;
+        const size_t base = seq_base + (size_t)m0_done * row_stride + (size_t)h_done * D;
+        const int off = (int)row_offset(), valid = (n - m0_done) * (int)row_stride * 2;   // lanes beyond store zeros
+        const int bytes = __builtin_amdgcn_readfirstlane(rows * (int)row_stride * 2);
+        const auto d0 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(p.out0 + base), 0, bytes, 0x00027000);
+        const auto d1 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr((MODE == DKDV ? p.out1 : p.out0) + base), 0, bytes, 0x00027000);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const bool ok = off + qb * block_bytes < valid;
+            const u32x4 z4 = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+                for (int pr = 0; pr < 2; ++pr) {
+                    const u32x4 w0 = chunk(acc0[qb][mb], pr, oscale);
+                    __builtin_amdgcn_raw_buffer_store_b128(ok ? w0 : z4, d0, off + 2 * TL_ACC0::out_col(mb, 2 * pr), qb * block_bytes, 0);
+                    if (MODE == DKDV) {
+                        const u32x4 w1 = chunk(acc1[MODE == DKDV ? qb : 0][MODE == DKDV ? mb : 0], pr, 1.0f);
+                        __builtin_amdgcn_raw_buffer_store_b128(ok ? w1 : z4, d1, off + 2 * TL_ACC1::out_col(mb, 2 * pr), qb * block_bytes, 0);
+                    }
+                }
+            }
+        }
+        if (--left == 0) break;
+        slot_rt = (slot_rt + 1) & (C::NBUF - 1);
+        scale_owner();
     }
+    zero_share();
 }
 
 template <int MODE, int D, int QB, int NW, int BN, int LD1, int LD2, int OCC, int RING, bool WITH_DB = false>
@@ -919,13 +1063,24 @@ __global__ void __launch_bounds__(NW * 64, OCC) sigattn_bwd_kernel(const Params 
     const int id = blockIdx.x;
     Work w;
     bool is_kv;
-    if (kv.in_order) {
+    if (kv.groups) {
+        int z, lo, cnt;
+        batch_order_range(id, kv.wide_seqs, kv.wide_groups + q.wide_groups, kv.groups + q.groups, z, lo, cnt);
+        const int pos = batch_order_pos(id, lo, cnt, shared_turn(z, cnt));
+        const int kv_groups = z < kv.wide_seqs ? kv.wide_groups : kv.groups;
+        const int g_kv = pos * kv_groups / cnt;                     // dK/dV workgroups in front of this one, evenly spread
+        is_kv = (pos + 1) * kv_groups / cnt > g_kv;
+        w = is_kv ? batch_order_share<C::BM>(kv, z, g_kv, kv_groups)
+                  : batch_order_share<C::BM>(q, z, pos - g_kv, cnt - kv_groups);
+    } else if (kv.in_order) {
         const int t_kv = owner_tiles<C::BM>(kv), t_q = owner_tiles<C::BM>(q);
         int tile;
-        batch_order_work(id, kv.H, t_kv + t_q, w.z, w.h, tile);
+        batch_order_tile(id, kv.H, t_kv + t_q, w.z, w.h, tile);
         is_kv = tile < t_kv;
         w.n = owner_length(is_kv ? kv : q, w.z);
         w.m0 = (is_kv ? tile : tile - t_kv) * C::BM;
+        w.count = 1;
+        w.share = w.shares = 0;
     } else {
         is_kv = (id < first_tiles) != (q_first != 0);
         const int rest = id < first_tiles ? id : id - first_tiles;

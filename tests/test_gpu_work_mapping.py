@@ -36,3 +36,59 @@ def test_every_tile_is_taken_once(B, N, H, d):
         assert bool(got.isfinite().all())
         nonzero = (got != 0).any(dim=3).any(dim=2).cpu().numpy()        # [B, N]; a valid row is never all zero
         assert np.array_equal(nonzero, np.arange(N)[None, :] < lens[:, None])
+
+
+@pytest.mark.parametrize("B,Lq,Lk,H,d", [
+    (400, 257, 257, 4, 64),      # several owner tiles a workgroup in every launch, three or two tiles a head
+    (300, 100, 100, 12, 64),     # one tile a head: workgroups go on with the next head
+    (240, 300, 300, 4, 128),     # d = 128, 128- and 256-row owner tiles
+    (200, 130, 700, 8, 64),      # cross-attention: more key tiles than query tiles
+    (2, 130, 130, 16384, 64),    # more owner tiles per sequence than workgroups are dealt to one
+])
+def test_workgroups_of_several_tiles(B, Lq, Lk, H, d):
+    """The joint calls of a large batch against calls on single sequences (or, for one long list of heads, on a part of
+    them), where every workgroup has one tile: the same arithmetic, so the same bits.  The first sequences hold an Inf
+    or NaN: it may not reach the tiles of another sequence or head."""
+    import torch
+    from paper_2604_27124_amd import binding as A
+    gen = torch.Generator(device="cuda").manual_seed(B + H)
+    normal = lambda n: torch.empty(B, n, H, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    q, k, v, g = normal(Lq), normal(Lk), normal(Lk), normal(Lq)
+    rng = np.random.default_rng(B + d)
+    nq, nk = rng.integers(0, Lq + 1, size=B), rng.integers(0, Lk + 1, size=B)
+    if B > 2:
+        edges = (0, 1, 127, 128, 129, 255, 256, 257)
+        nq[:8], nk[4:12] = np.minimum(edges, Lq), np.minimum(edges, Lk)
+        v[1, 0, 1, 3], k[3, 0, 0, 5], g[6, 0, 2, 1] = float("inf"), float("nan"), float("-inf")
+    else:
+        nq[:], nk[:] = (130, 70), (130, 70)
+        v[0, 5, 7, 3] = float("inf")
+    if Lq == Lk:
+        nk = nq
+    dev = lambda a: torch.from_numpy(a.astype(np.int32)).cuda()
+    nq, nk, bias = dev(nq), dev(nk), torch.full((B,), -5.0, device="cuda")
+    scale = d ** -0.5
+
+    def calls(q, k, v, g, nq, nk, bias):
+        poison = lambda t: torch.full_like(t, 7.0)
+        o = A.sigmoid_attn_cross_fwd(q, k, v, nq, nk, bias, scale, out=poison(q))
+        grads = A.sigmoid_attn_cross_bwd(q, k, v, g, nq, nk, bias, scale, dq=poison(q), dk=poison(k), dv=poison(v))
+        dq, db = A.sigmoid_attn_cross_bwd_dq_dbias(q, k, v, g, nq, nk, bias, scale, dq=poison(q))
+        return (o, *grads, dq), db
+
+    bits = lambda t: t.view(torch.int16)
+    whole, db = calls(q, k, v, g, nq, nk, bias)
+    if B == 2:
+        for h0 in (0, 7, 8190, 16376):
+            part, _ = calls(*(t[:, :, h0:h0 + 8].contiguous() for t in (q, k, v, g)), nq, nk, bias)
+            for got, want in zip(whole, part):
+                assert torch.equal(bits(got[:, :, h0:h0 + 8].contiguous()), bits(want)), (h0, "heads")
+        for got in whole:       # heads that were not compared: every row written, zeros exactly in the padding
+            nonzero = (got != 0).any(dim=3)
+            assert bool(nonzero[0, :130].all()) and bool(nonzero[1, :70].all()) and not bool(nonzero[1, 70:].any())
+        return
+    for z in list(range(16)) + list(range(16, B, 7)) + [B - 1]:
+        part, db1 = calls(*(t[z:z + 1] for t in (q, k, v, g, nq, nk, bias)))
+        for i, (got, want) in enumerate(zip(whole, part)):
+            assert torch.equal(bits(got[z:z + 1]), bits(want)), (z, i)
+        assert torch.allclose(db[z:z + 1], db1, rtol=1e-4, atol=1e-4, equal_nan=True), z   # fp32 sums in another order
