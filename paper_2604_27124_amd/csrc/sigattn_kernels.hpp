@@ -1013,7 +1013,8 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
         // keeps the compiler from counting what is in flight when the next tile's owner rows are waited for.
         const int rows = p.N - m0_done < C::BM ? p.N - m0_done : C::BM;
         const size_t base = seq_base + (size_t)m0_done * row_stride + (size_t)h_done * D;
-        const int off = (int)row_offset(), valid = (n - m0_done) * (int)row_stride * 2;   // lanes beyond store zeros
+        const int valid_rows = n - m0_done < C::BM ? n - m0_done : C::BM;       // lanes beyond store zeros
+        const int off = (int)row_offset(), valid = valid_rows * (int)row_stride * 2;
         const int bytes = __builtin_amdgcn_readfirstlane(rows * (int)row_stride * 2);
         const auto d0 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(p.out0 + base), 0, bytes, 0x00027000);
         const auto d1 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr((MODE == DKDV ? p.out1 : p.out0) + base), 0, bytes, 0x00027000);

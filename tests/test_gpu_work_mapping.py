@@ -92,3 +92,19 @@ def test_workgroups_of_several_tiles(B, Lq, Lk, H, d):
         for i, (got, want) in enumerate(zip(whole, part)):
             assert torch.equal(bits(got[z:z + 1]), bits(want)), (z, i)
         assert torch.allclose(db[z:z + 1], db1, rtol=1e-4, atol=1e-4, equal_nan=True), z   # fp32 sums in another order
+
+
+def test_rows_behind_a_tile_span_more_than_2_gib():
+    """1100 rows of 16384 heads: from a head's first tile to its last valid row it is more than 2^31 bytes."""
+    import torch
+    from paper_2604_27124_amd import binding as A
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v, g = (torch.empty(1, 1100, 16384, 64, dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in range(4))
+    n, bias = torch.tensor([1090], dtype=torch.int32, device="cuda"), torch.tensor([-7.0], device="cuda")
+    whole = (A.sigmoid_attn_fwd(q, k, v, n, bias, 0.125), *A.sigmoid_attn_bwd(q, k, v, g, n, bias, 0.125))
+    for h in (0, 9000, 16380):
+        q1, k1, v1, g1 = (t[:, :, h:h + 4].contiguous() for t in (q, k, v, g))
+        part = (A.sigmoid_attn_fwd(q1, k1, v1, n, bias, 0.125), *A.sigmoid_attn_bwd(q1, k1, v1, g1, n, bias, 0.125))
+        for got, want in zip(whole, part):
+            assert bool(want[0, :1090].any()) and not bool(want[0, 1090:].any())
+            assert torch.equal(got[:, :, h:h + 4].contiguous().view(torch.int16), want.view(torch.int16)), h
