@@ -39,6 +39,7 @@ typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -725,8 +726,7 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
     // 1 - P = cb e P holds without cancellation however close P is to 1, so dS = P (1 - P) dP keeps its
     // relative accuracy on the saturated tail; the constant cb is applied once, to the finished sums.
     // e = +inf (score far below the bias) meets P = 0 there: the product must be 0, not NaN.
-    // Streamed rows beyond the valid length need no mask: they are zeros in LDS, so P is finite there and meets a
-    // zero row of V (forward), and dP = 0, hence dS = 0, in the backward passes; dV meets a zero row of dO.
+    // Streamed rows beyond the valid length are zeros in LDS; their P and dS are set to 0 once per owner tile (mask_block).
     constexpr int OPU = (MODE == FWD) ? 7 : (MODE == DQ ? 13 : 14);
 
     // One pipeline step on the block (slot, nb) of parity PAR (compile-time nb).  Slots run in program
@@ -907,6 +907,30 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
         if constexpr (!LOAD_EARLY) load_tile();
         step(T_{}, T_{}, F_{}, IntC<0>{}, IntC<(slot + 1) & (C::NBUF - 1)>{}, NoStore{}, 0);
     };
+    // P and dS of the streamed rows behind the valid length, in block nb of the last tile: exact zeros, as packed for the
+    // output contractions.  Against a finite owner row they would add zeros anyway (the rows are zeros in LDS), but an Inf
+    // in the owner row makes their scores 0 x Inf = NaN.  Two instructions a mask and one or two to apply it, on eight
+    // packed pairs a block, once per owner tile and none of them in the loop.  A block without such rows is passed over,
+    // but not the first one of dK/dV: with that branch the four-wave kernel reloaded four spilled registers in every tile.
+    const int tail = ns - (ntiles - 1) * BN;       // valid rows of the last tile
+    auto mask_block = [&](auto nb_c) {
+        constexpr int nb = decltype(nb_c)::value, PAR = nb & 1;
+        if ((nb > 0 || MODE != DKDV) && tail >= 32 * (nb + 1)) return;           // uniform
+        const short valid = (short)(tail - 32 * nb - 4 * (fresh_lane() >> 5));   // rows of this lane, counted as below
+        const s16x2 limit = {valid, valid};
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {              // pair w holds rows 8 (w / 2) + 2 (w % 2) and the one behind it (+ 4 g)
+            const short row = (short)(8 * (w / 2) + 2 * (w % 2));
+            const s16x2 rows = {row, (short)(row + 1)};
+            const unsigned keep = __builtin_bit_cast(unsigned, (s16x2)((rows - limit) >> 15));
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                if (MODE != DQ) pbuf[PAR][qb][w / 4][w % 4] &= keep;
+                if (HAS2) dsbuf[PAR][HAS2 ? qb : 0][w / 4][w % 4] &= keep;
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
     int slot_rt = 0;                               // ring slot of the tile in hand
     for (;;) {
         // the tiles stored last are visible, and nobody reads the slot that is written next
@@ -962,8 +986,10 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
         if (more) load_owner(h, m0);
         {
             const DynInt slot{slot_rt};
+            mask_block(IntC<0>{});
             static_for<1, NB>([&](auto nb_) {
                 step(T_{}, IntC<(decltype(nb_)::value + 1 < NB) ? 1 : 0>{}, F_{}, nb_, slot, NoStore{}, 0);
+                mask_block(nb_);
             });
             const DynInt slot_next{(slot_rt + 1) & (C::NBUF - 1)};
             step(T_{}, F_{}, T_{}, IntC<0>{}, slot_next, NoStore{}, 0);

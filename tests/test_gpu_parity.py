@@ -127,6 +127,33 @@ def test_nan_and_inf_in_padded_rows_are_never_read(d):
         assert np.array_equal(x, y)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_infinite_inputs_saturate_at_every_length(d):
+    # One Inf in a query row (head 0) or a key row (head 1): its scores are +-Inf, its weights exactly 0 or 1 and its dS
+    # 0, so O, dV and the gradient that is not multiplied by the Inf itself stay finite, as the oracle has them, however
+    # far the valid length is from a whole number of 64-row streamed tiles or 32-row blocks.  NaN exactly where the
+    # oracle has NaN (0 x Inf in the one column of the other gradient).  Head 2 has no Inf; padded rows are zeros.
+    lens = (1, 31, 32, 33, 63, 64, 65, 96, 97, 150, 193)
+    B, N = len(lens), 200
+    w = W.make(B, N, 3, d, lens, seed=17 + d)
+    for z, n in enumerate(lens):
+        w.q[z, n // 2, 0, 5 + z] = np.inf
+        w.k[z, n - 1, 1, 7 + z] = -np.inf
+    dev = Dev(w)
+    got = [to_host(dev.fwd())] + [to_host(t) for t in dev.bwd()]
+    with np.errstate(invalid="ignore"):
+        ref = [oracle.fwd(w.q, w.k, w.v, w.seqlens, w.bias, w.scale, slices=all_slices(w))]
+        ref += list(oracle.bwd(w.q, w.k, w.v, w.d_o, w.seqlens, w.bias, w.scale, slices=all_slices(w)))
+    for name, a, r, tol in zip(("O", "dQ", "dK", "dV"), got, ref, (FWD_TOL, BWD_TOL, BWD_TOL, BWD_TOL)):
+        for z, h in all_slices(w):
+            n = lens[z]
+            x, y = a[z, :n, h], r[z, :n, h]
+            assert np.all(a[z, n:, h] == 0.0), (name, z, h)
+            assert np.array_equal(np.isnan(x), np.isnan(y)), (name, n, h, "NaN pattern")
+            assert np.all(np.isfinite(x[~np.isnan(x)])), (name, n, h)
+            assert slice_err(np.where(np.isnan(x), 0, x), np.where(np.isnan(y), 0, y)) <= tol, (name, n, h)
+
+
 # ---- the 512-row forward instance (two owner blocks per wave), selected when the key side is padded to
 # more than 4096 rows: edge lengths, NaN padding, and agreement with the 256-row instance
 
