@@ -94,6 +94,52 @@ def test_workgroups_of_several_tiles(B, Lq, Lk, H, d):
         assert torch.allclose(db[z:z + 1], db1, rtol=1e-4, atol=1e-4, equal_nan=True), z   # fp32 sums in another order
 
 
+@pytest.mark.parametrize("B,Lq,Lk,H,d", [
+    (3, 333, 333, 50, 64),       # forward: 300 workgroups of 256 rows (two owner blocks a wave), one tile each
+    (3, 100, 77, 3, 64),         # fewer rows than one pass over a tile or one owner block
+    (300, 300, 300, 12, 64),     # several owner tiles a workgroup, two owner blocks a wave in the forward pass
+    (240, 300, 140, 4, 128),     # several owner tiles a workgroup, d = 128
+])
+def test_padding_is_never_read_or_written(B, Lq, Lk, H, d):
+    """Padded rows hold NaN and Inf: every load ends with the last valid row of its tile and every store with the last
+    row of its sequence, in each pass over a tile and each owner block (the bits are those of zeros in the padding)."""
+    import torch
+    from paper_2604_27124_amd import binding as A
+    gen = torch.Generator(device="cuda").manual_seed(B * H + d)
+    rng = np.random.default_rng(B + Lq)
+    nq, nk = rng.integers(0, Lq + 1, size=B), rng.integers(0, Lk + 1, size=B)
+    edges = (Lq, 1, 33, 257, 270, 288, 289, 0)[:B]
+    nq[:len(edges)] = np.minimum(edges, Lq)
+    nk[B - len(edges):] = np.minimum(edges, Lk)
+    if Lq == Lk:
+        nk = nq
+    dev = lambda a: torch.from_numpy(a.astype(np.int32)).cuda()
+    sq, sk, bias = dev(nq), dev(nk), torch.full((B,), -4.0, device="cuda")
+
+    def tensor(L, n, bad):
+        clean = torch.empty(B, L, H, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+        pad = (torch.arange(L, device="cuda")[None, :] >= n[:, None])[:, :, None, None]
+        return clean.masked_fill(pad, 0.0), clean.masked_fill(pad, bad)
+
+    inf, nan = float("inf"), float("nan")
+    pairs = [tensor(L, n, bad) for L, n, bad in ((Lq, sq, nan), (Lk, sk, inf), (Lk, sk, -inf), (Lq, sq, nan))]
+    results = []
+    for q, k, v, g in zip(*pairs):
+        poison = lambda t: torch.full_like(t, 7.0)
+        o = A.sigmoid_attn_cross_fwd(q, k, v, sq, sk, bias, d ** -0.5, out=poison(q))
+        grads = A.sigmoid_attn_cross_bwd(q, k, v, g, sq, sk, bias, d ** -0.5, dq=poison(q), dk=poison(k), dv=poison(v))
+        dq, db = A.sigmoid_attn_cross_bwd_dq_dbias(q, k, v, g, sq, sk, bias, d ** -0.5, dq=poison(q))
+        results.append((o, *grads, dq, db))
+    for n, clean, bad in zip((sq, sq, sk, sk, sq, None), *results):
+        assert bool(bad.isfinite().all())
+        assert torch.equal(clean, bad)
+        if n is not None:
+            nonzero = (bad != 0).any(dim=3).any(dim=2)
+            other = sk if n is sq else sq                       # a row with nothing to stream is zero
+            valid = (torch.arange(bad.shape[1], device="cuda")[None, :] < n[:, None]) & (other > 0)[:, None]
+            assert torch.equal(nonzero, valid)
+
+
 def test_rows_behind_a_tile_span_more_than_2_gib():
     """1100 rows of 16384 heads: from a head's first tile to its last valid row it is more than 2^31 bytes."""
     import torch
