@@ -148,7 +148,9 @@ struct Cfg {
     static_assert(LM1 != 2 || LD1 >= D + 8, "mode 2 shifts a row by up to 16 bytes");
     static_assert(LM2 != 2 || LD2 >= D + 8, "mode 2 shifts a row by up to 16 bytes");
     static_assert((BN * CH) % THREADS == 0, "tile does not split evenly over the workgroup");
-    static_assert(D % 32 == 0 && BN % 64 == 0, "tile shape (an even number of 32-row blocks per tile)");
+    // Two blocks, not any even number: once the last tile's first block has been through, no score contraction reads the
+    // owner rows any more, and those of the next owner tile are requested into their registers.
+    static_assert(D % 32 == 0 && NB == 2, "tile shape (two 32-row blocks per streamed tile)");
     static_assert(LD1 % 8 == 0 && LD2 % 8 == 0 && LD1 >= D && LD2 >= D, "LDS row stride");
     static_assert((NB * NOPS) % RING == 0 && RING >= 2 && RING <= NOPS, "operand ring does not close over a tile");
 };

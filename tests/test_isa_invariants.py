@@ -103,3 +103,17 @@ def test_hot_loops_use_the_matrix_and_transcendental_pipes(kernels):
         assert ops.count("v_mfma_f32_32x32x16_bf16") > 64, name
         assert any(o.startswith("v_exp_f32") for o in ops) and any(o.startswith("v_rcp_f32") for o in ops), name
         assert any(o == "ds_read_b64_tr_b16" for o in ops), name
+
+
+@pytest.mark.parametrize("rows,compiles", [(64, True), (128, False)])
+def test_only_tiles_of_two_blocks_compile(tmp_path, rows, compiles):
+    """At the last tile of an owner tile the next owner rows are loaded behind the first 32-row block: with more than two
+    blocks the scores of the later ones would be computed from them, so such a shape must not compile."""
+    src = tmp_path / "shape.hip"
+    src.write_text('#include "sigattn_kernels.hpp"\n'
+                   f"template __global__ void sigattn::sigattn_kernel<sigattn::FWD, 64, 1, 8, {rows}, 72, 72, 1, 4>(const sigattn::Params);\n")
+    flags = [f for f in B.HIPCC_FLAGS if f not in ("-shared", "-fPIC", "-O3")]
+    r = subprocess.run([B.hipcc(), *flags, "-I", B.CSRC, "-fsyntax-only", "--cuda-device-only", str(src)],
+                       capture_output=True, text=True)
+    assert (r.returncode == 0) == compiles, r.stderr[-2000:]
+    assert compiles or "two 32-row blocks" in r.stderr
