@@ -10,8 +10,6 @@ import ctypes
 import os
 from typing import Tuple
 
-import torch
-
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libsigattn.so")
 
@@ -31,6 +29,19 @@ EXPORTS = ("sigmoid_attn_version", "sigmoid_attn_strerror", "sigmoid_attn_fwd", 
            "sigmoid_attn_bwd_dq_dbias_static")
 
 _lib = None
+
+
+class _Torch:
+    """Stands for torch until a call on tensors first asks it for something, and is then replaced by it: loading this
+    module, sizes and error texts need no torch, and later calls pay for no import statement."""
+
+    def __getattr__(self, name):
+        global torch
+        import torch
+        return getattr(torch, name)
+
+
+torch = _Torch()
 
 
 class SigAttnError(RuntimeError):

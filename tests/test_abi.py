@@ -173,6 +173,23 @@ def test_binding_refuses_cpu_tensors():
         B.sigmoid_attn_fwd(x, x, x, torch.zeros(1, dtype=torch.int32), torch.zeros(1), 0.125)
 
 
+def test_library_and_sizes_are_usable_without_torch():
+    """Loading the binding, the version, error texts and workspace sizes need no torch (a process that only plans)."""
+    import subprocess
+    import sys
+    code = ("import sys; sys.modules['torch'] = None\n"          # any import of torch raises ImportError
+            "from paper_2604_27124_amd import binding as A\n"
+            "assert A.sigmoid_attn_version() >= 100 and A.sigmoid_attn_strerror(0) == 'success'\n"
+            "assert A.sigmoid_attn_bwd_workspace_bytes(2, 256, 2, 64) == 0\n"
+            "assert A.sigmoid_attn_bwd_dq_dbias_workspace_bytes(2, 300, 3, 64) == 96\n"
+            "try:\n"
+            "    raise A.SigAttnError(-2)\n"
+            "except RuntimeError as e:\n"
+            "    assert 'head dimension' in str(e)\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+
+
 def test_header_is_plain_c_and_links_from_c(tmp_path):
     """The boundary is usable from C: the header compiles as C99 with warnings as errors, and a C
     program linked against the library reaches the host-only entry points (no GPU call is made)."""
