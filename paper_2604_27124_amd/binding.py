@@ -128,7 +128,8 @@ def _output(t, name: str, like):
 
 def _stream_ptr(stream) -> int:
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # internal: not every torch need have it
+        return raw(torch.cuda.current_device()) if raw else int(torch.cuda.current_stream().cuda_stream)
     return int(stream.cuda_stream)
 
 

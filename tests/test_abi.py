@@ -190,6 +190,19 @@ def test_library_and_sizes_are_usable_without_torch():
     assert r.returncode == 0, r.stderr
 
 
+def test_current_stream_is_found_without_the_short_cut(monkeypatch):
+    """The current stream's handle comes from an internal function of torch where it has one, else from the public call."""
+    import torch
+    from types import SimpleNamespace
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: SimpleNamespace(cuda_stream=0x77))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x1000 + device, raising=False)
+    assert B._stream_ptr(None) == 0x1003
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert B._stream_ptr(None) == 0x77
+    assert B._stream_ptr(SimpleNamespace(cuda_stream=0x55)) == 0x55
+
+
 def test_header_is_plain_c_and_links_from_c(tmp_path):
     """The boundary is usable from C: the header compiles as C99 with warnings as errors, and a C
     program linked against the library reaches the host-only entry points (no GPU call is made)."""
