@@ -106,8 +106,8 @@ def test_padded_inputs_do_not_influence_valid_outputs():
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_nan_and_inf_in_padded_rows_are_never_read(d):
-    # Stronger than the contract (finite padding): padded streamed rows are never fetched (the loader
-    # re-reads the last valid row and zeroes it) and padded owner rows are replaced by zeros at load, so
+    # Stronger than the contract (finite padding): padded rows are never fetched, on either side (every load goes
+    # through a buffer descriptor that ends with the last valid row; behind it the hardware returns zeros), so
     # even NaN / Inf bit patterns in the padding leave every output bit unchanged.
     lens = (333, 150, 0)
     w = W.make(3, 333, 2, d, lens, seed=23)
@@ -154,58 +154,41 @@ def test_infinite_inputs_saturate_at_every_length(d):
             assert slice_err(np.where(np.isnan(x), 0, x), np.where(np.isnan(y), 0, y)) <= tol, (name, n, h)
 
 
-# ---- the 512-row forward instance (two owner blocks per wave), selected when the key side is padded to
-# more than 4096 rows: edge lengths, NaN padding, and agreement with the 256-row instance
+# ---- the two owner tiles of the d = 64 forward pass: 256 query rows (two owner blocks per wave) where that gives more
+# than 256 workgroups, else 128 rows (one block)
 
-WIDE_TILE_N = 4160          # just above 4096: the forward launch takes 512-row owner tiles
-
-
-@pytest.mark.parametrize("seqlens", [(511, 512, 513, 4097), (544, 545, 32, 4160), (0, 1, 1025, 3000)])
-def test_wide_forward_tile_edge_lengths(seqlens):
-    # lengths on and around the 512-row owner tile, a wave whose second 32-row block is wholly padded
-    # (544 = 512 + 32), a single valid row, an empty sequence, the full padded length
-    w = W.make(4, WIDE_TILE_N, 2, 64, seqlens, seed=sum(seqlens) % 1000 + 3)
-    say("512-row forward tile", seqlens, check_against_oracle(w, bwd=False))
+TALL = dict(B=4, N=1100, H=14)      # 4 x 14 x 5 = 280 workgroups of 256 rows
 
 
-def test_wide_forward_tile_nan_padding():
-    lens = (513, 4097, 0)
-    w = W.make(3, WIDE_TILE_N, 1, 64, lens, seed=91)
-    ref = to_host(Dev(w).fwd())
-    b = Dev(W.make(3, WIDE_TILE_N, 1, 64, lens, seed=91))
-    for nm, pat in {"q": 0x7FC0, "k": 0x7F80, "v": 0xFF80}.items():
-        raw = getattr(b, nm).view(torch.int16)
-        for z, n in enumerate(lens):
-            raw[z, n:] = pat - 65536 if pat >= 32768 else pat
-    torch.cuda.synchronize()
-    new = to_host(b.fwd())
-    assert np.all(np.isfinite(new)) and np.array_equal(ref, new)
+@pytest.mark.parametrize("seqlens", [(255, 256, 257, 1025), (288, 289, 32, 1100), (0, 1, 513, 1000)])
+def test_two_block_forward_tile_edge_lengths(seqlens):
+    # lengths on and around the 256-row owner tile, a wave whose second 32-row block is wholly padded
+    # (288 = 256 + 32), a single valid row, an empty sequence, the full padded length
+    w = W.make(TALL["B"], TALL["N"], TALL["H"], 64, seqlens, seed=sum(seqlens) % 1000 + 3)
+    slices = [(z, h) for z in range(4) for h in (0, 5 + z, 13)]
+    say("256-row forward tile", seqlens, check_against_oracle(w, bwd=False, slices=slices))
 
 
 def test_forward_tile_shapes_agree():
-    # the same sequences under N_max = 4096 (256-row owner tiles) and N_max = 4160 (512-row owner tiles):
-    # both match the oracle, and they agree with each other under the parity norm (the order of the fp32
-    # sums over key tiles is the same, so in fact bit for bit)
-    lens = (4096, 1300, 513)
-    a = W.make(3, 4096, 2, 64, lens, seed=92)
-    b = W.make(3, WIDE_TILE_N, 2, 64, lens, seed=93)
+    # the same heads among few (3 x 2 x 5 = 30 workgroups of 256 rows, so 128-row tiles) and among many (3 x 30 x 5 =
+    # 450, so 256-row tiles): both match the oracle, and they agree bit for bit, since a row's sums run over the key
+    # tiles in the same order
+    lens = (1030, 513, 300)
+    a = W.make(3, 1030, 2, 64, lens, seed=92)
+    b = W.make(3, 1030, 30, 64, lens, seed=93)
     for nm in ("q", "k", "v", "d_o"):
-        getattr(b, nm)[:, :4096] = getattr(a, nm)
-    b.bias[:] = a.bias
-    say("256-row tiles", check_against_oracle(a, bwd=False, slices=[(0, 0), (1, 1), (2, 0)]))
-    say("512-row tiles", check_against_oracle(b, bwd=False, slices=[(0, 0), (1, 1), (2, 0)]))
+        getattr(b, nm)[:, :, 11:13] = getattr(a, nm)
+    say("128-row tiles", check_against_oracle(a, bwd=False, slices=[(0, 0), (1, 1), (2, 0)]))
+    say("256-row tiles", check_against_oracle(b, bwd=False, slices=[(0, 11), (1, 12), (2, 11)]))
     oa, ob = to_host(Dev(a).fwd()), to_host(Dev(b).fwd())
-    for z, n in enumerate(lens):
-        for h in range(2):
-            assert slice_err(ob[z, :n, h], oa[z, :n, h].astype(np.float64)) < FWD_TOL
-    say("tile shapes bitwise equal:", bool(np.array_equal(oa, ob[:, :4096])))
+    assert np.array_equal(oa, ob[:, :, 11:13])
 
 
 @pytest.mark.parametrize("B,N,H", [(300, 96, 1), (2000, 300, 2), (1100, 530, 1)])
-def test_more_sequences_than_the_pairwise_ranking_holds(B, N, H):
-    # B > 256: sequences are ranked by tile count with a histogram and block-wide prefix sums; every owner
-    # tile of every (z, h) must still be produced exactly once (outputs are NaN-poisoned before the call,
-    # so a tile that no workgroup took shows), and sampled slices must match the oracle.
+def test_many_short_sequences(B, N, H):
+    # Large batches of short sequences go in batch order: every owner tile of every (z, h) must be produced exactly
+    # once (outputs are NaN-poisoned before the call, so a tile that no workgroup took shows), and sampled slices must
+    # match the oracle.  (Ranked batches of more sequences than a workgroup has threads: test_gpu_work_mapping.py.)
     rng = np.random.default_rng(3 + B)
     lens = rng.integers(0, N + 1, size=B)
     lens[:4] = (N, 0, 1, 257 if N > 257 else N - 1)
