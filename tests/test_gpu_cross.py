@@ -89,8 +89,8 @@ def test_cross_equals_self_when_lengths_agree():
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_cross_many_sequences(d):
-    # more than 256 sequences (tile-count ranking of the work mapping) with different lengths on the two
-    # sides: the owner side is ranked, the streamed length is looked up per sequence
+    # more than 256 sequences with different lengths on the two sides, in batch order: the owner side's tiles are
+    # dealt, the streamed length is looked up per sequence
     B = 300
     rng = np.random.default_rng(7)
     nq = rng.integers(0, 291, size=B); nk = rng.integers(0, 151, size=B)
@@ -99,7 +99,7 @@ def test_cross_many_sequences(d):
 
 
 def test_dq_dbias_many_sequences():
-    # the bias-gradient entry point over more than 256 sequences: one partial per workgroup, summed per sequence
+    # the bias-gradient entry point over more than 256 sequences: one partial per owner tile, summed per sequence
     B = 300
     rng = np.random.default_rng(8)
     lens = rng.integers(0, 301, size=B)

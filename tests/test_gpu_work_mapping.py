@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
     (64, 300, 4, 64),      # batch order: runs of a multiple of 8 ids per sequence, three 128-row tiles
     (70, 257, 3, 64),      # batch order: ids per sequence not a multiple of 8, one row in the last tile
     (90, 100, 5, 64),      # batch order, one tile per head
-    (33, 513, 8, 128),     # batch order at d = 128
+    (33, 513, 8, 128),     # d = 128: dK/dV in batch order, forward and dQ ranked in registers
+    (48, 513, 8, 128),     # batch order at d = 128
     (64, 130, 1, 64),      # ranked in registers, every lane in use
     (65, 300, 1, 64),      # ranked by histogram
     (65, 250, 2, 128),     # ranked by histogram, d = 128
@@ -42,7 +43,8 @@ def test_every_tile_is_taken_once(B, N, H, d):
     (400, 257, 257, 4, 64),      # several owner tiles a workgroup in every launch, three or two tiles a head
     (300, 100, 100, 12, 64),     # one tile a head: workgroups go on with the next head
     (240, 300, 300, 4, 128),     # d = 128, 128- and 256-row owner tiles
-    (200, 130, 700, 8, 64),      # cross-attention: more key tiles than query tiles
+    (200, 130, 700, 8, 64),      # cross-attention: more key tiles than query tiles (forward: one tile a workgroup)
+    (40, 4096, 4096, 16, 64),    # eight-wave backward, 256-row owner tiles: two tiles a workgroup
     (2, 130, 130, 16384, 64),    # more owner tiles per sequence than workgroups are dealt to one
 ])
 def test_workgroups_of_several_tiles(B, Lq, Lk, H, d):
@@ -59,6 +61,8 @@ def test_workgroups_of_several_tiles(B, Lq, Lk, H, d):
     if B > 2:
         edges = (0, 1, 127, 128, 129, 255, 256, 257)
         nq[:8], nk[4:12] = np.minimum(edges, Lq), np.minimum(edges, Lk)
+        if Lq > 1000:                                            # all edges on both sides, and a few full tiles more
+            nq[8:16] = (511, 512, 513, 768, 769, Lq - 1, Lq, 1024)
         v[1, 0, 1, 3], k[3, 0, 0, 5], g[6, 0, 2, 1] = float("inf"), float("nan"), float("-inf")
     else:
         nq[:], nk[:] = (130, 70), (130, 70)
@@ -92,6 +96,39 @@ def test_workgroups_of_several_tiles(B, Lq, Lk, H, d):
         for i, (got, want) in enumerate(zip(whole, part)):
             assert torch.equal(bits(got[z:z + 1]), bits(want)), (z, i)
         assert torch.allclose(db[z:z + 1], db1, rtol=1e-4, atol=1e-4, equal_nan=True), z   # fp32 sums in another order
+
+
+@pytest.mark.parametrize("B,Lk,d", [
+    (300, 3000, 64),       # two passes of 256 threads over the sequences
+    (520, 6000, 64),       # three passes
+    (520, 6000, 128),      # two passes of 512 threads
+])
+def test_ranking_of_more_sequences_than_threads(B, Lk, d):
+    """Few query rows against many keys, one head: the forward pass and dQ + dbias rank these batches (by histogram, the
+    sequences of a class in several passes of the workgroup over the batch).  Against calls on single sequences, bit
+    for bit; the outputs hold 7 before the call, so an owner tile that no workgroup took shows."""
+    import torch
+    from paper_2604_27124_amd import binding as A
+    Lq = 100
+    gen = torch.Generator(device="cuda").manual_seed(B + d)
+    normal = lambda n: torch.empty(B, n, 1, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    q, k, v, g = normal(Lq), normal(Lk), normal(Lk), normal(Lq)
+    rng = np.random.default_rng(B)
+    nq, nk = rng.integers(0, Lq + 1, size=B), rng.integers(0, 200, size=B)
+    nq[[0, 255, 256, 257, B - 1]] = (0, 1, 100, 0, 33)
+    nk[[5, 256, B - 1]] = (0, Lk, 64)
+    dev = lambda a: torch.from_numpy(a.astype(np.int32)).cuda()
+    sq, sk, bias = dev(nq), dev(nk), torch.full((B,), -4.0, device="cuda")
+    seven = lambda t: torch.full_like(t, 7.0)
+    bits = lambda t: t.view(torch.int16)
+    o = A.sigmoid_attn_cross_fwd(q, k, v, sq, sk, bias, d ** -0.5, out=seven(q))
+    dq, db = A.sigmoid_attn_cross_bwd_dq_dbias(q, k, v, g, sq, sk, bias, d ** -0.5, dq=seven(q))
+    for z in range(B):
+        one = [t[z:z + 1] for t in (q, k, v, g, sq, sk, bias)]
+        o1 = A.sigmoid_attn_cross_fwd(*one[:3], *one[4:], d ** -0.5)
+        dq1, db1 = A.sigmoid_attn_cross_bwd_dq_dbias(*one, d ** -0.5)
+        assert torch.equal(bits(o[z:z + 1]), bits(o1)), (z, "o")
+        assert torch.equal(bits(dq[z:z + 1]), bits(dq1)) and torch.equal(db[z:z + 1], db1), (z, "dq, dbias")
 
 
 @pytest.mark.parametrize("B,Lq,Lk,H,d", [
