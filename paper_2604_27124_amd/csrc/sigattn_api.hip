@@ -32,8 +32,9 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // it lives (measured with the wavefronts of both workgroups ranking at once); batch order costs about half a
 // workgroup's life at the end of the launch, so 0.5 / (wgs / 512) of its time.  Batch order where that is less,
 // or where the ranking has no class for every tile count.  Measured, sorted against batch order, us: dK/dV + dQ
-// at B = 512, N = 512: 1015 / 879; B = 32, N = 512: 227 / 208; B = 16, H = 32, N = 1024: 406 / 393; B = 16, H = 12,
-// N = 4096: 825 / 829; forward at B = 24, N = 1500: 77 / 88.
+// at B = 512, N = 512: 2106 / 1850; B = 32, H = 32, N = 512: 225 / 191; B = 16, H = 32, N = 1024: 326 / 309; B = 16, H = 12,
+// N = 4096 (just below the line): 951 / 946; B = 24, H = 12, N = 4096: 2179 / 2182; B = 4, H = 32, N = 4096: 953 / 972;
+// B = 8, H = 12, N = 2048: 125 / 132; forward at B = 24, H = 12, N = 1500: 72 / 78.
 int batch_order(const Params &p, long long wgs, int owner_rows) {
     if (p.B > MAP_WAVE_B && ((long long)p.N + owner_rows - 1) / owner_rows > MAP_CLASSES) return 1;
     return p.B * wgs > 16000 + 45LL * p.N_str;
@@ -123,12 +124,6 @@ int launch_bwd(Params kv, Params q, hipStream_t stream) {
     return enqueue(sigattn_bwd_kernel<D, NW, BN, LD, LD, OCC, RING_KV, RING_Q>, wgs, C::THREADS, C::LDS_BYTES,
                    stream, kv, q, q_first, (int)(q_first ? q_tiles : kv_tiles));
 }
-
-// d = 64, backward: workgroups of four waves (128 owner rows, two to a CU, so that one fills the other's start and
-// end), or of eight (256 rows: half the tile movement per owner row), which win once the tile loop dominates.
-// dK/dV + dQ with four / eight waves, us: N = 512 (B = 32, H = 32) 208 / 262, N = 1500 (B = 8) 127 / 134, N = 3000
-// (B = 3, H = 16) 306 / 299, N = 4096 (B = 2, H = 8) 160 / 156, N = 8192 (B = 4) 1281 / 1266.
-bool eight_waves(int L_q, int L_k) { return L_q >= 4096 && L_k >= 4096; }
 
 }  // namespace
 
@@ -224,14 +219,17 @@ static int bwd_impl(const void *q, const void *k, const void *v, const void *d_o
     pq.out1 = nullptr;
 
     if (d == 64) {
-        const bool wide = eight_waves(L_q, L_k);
+        // Four waves (128 owner rows), two workgroups to a CU, so that one fills the other's start and end.  Eight waves
+        // and 256 rows, one to a CU, halve the tile movement per owner row and still gain nothing: dK/dV + dQ with four /
+        // eight, us, all rows valid: B = 1, H = 2, N = 4096 71 / 99; B = 3, H = 16, N = 3000 403 / 407, N = 8192 2704 /
+        // 2683; B = 16, H = 12, N = 4096 2873 / 2828; lengths from a quarter of N on: B = 4, H = 12, N = 4096 364 / 381,
+        // N = 8192 1345 / 1383; B = 1, H = 12, N = 16384 2231 / 2265.  Over 140 such cases four take 0.71 to 1.025 of the
+        // time of eight.
         // One launch for both passes: one start, and the tail of the first is filled by the second (B = 2, H = 2,
         // N = 256: 9.4 us against 9.0 + 8.0; B = 12 heads of N = 1000: 22.5 against 21.9 + 19.4; N = 8192: 1.5 % less).
-        if (want_dkdv && want_dq)
-            return wide ? launch_bwd<64, 8, 64, 72, 1, 8, 4>(pk, pq, s) : launch_bwd<64, 4, 64, 72, 2, 8, 4>(pk, pq, s);
-        if (want_dkdv)
-            return wide ? launch<DKDV, 64, 1, 8, 64, 72, 72, 1, 8>(pk, s) : launch<DKDV, 64, 1, 4, 64, 72, 72, 2, 8>(pk, s);
-        if (want_dq) return wide ? launch<DQ, 64, 1, 8, 64, 72, 72, 1, 4>(pq, s) : launch<DQ, 64, 1, 4, 64, 72, 72, 2, 4>(pq, s);
+        if (want_dkdv && want_dq) return launch_bwd<64, 4, 64, 72, 2, 8, 4>(pk, pq, s);
+        if (want_dkdv) return launch<DKDV, 64, 1, 4, 64, 72, 72, 2, 8>(pk, s);
+        if (want_dq) return launch<DQ, 64, 1, 4, 64, 72, 72, 2, 4>(pq, s);
         return SIGATTN_OK;
     }
     if (want_dkdv) {
@@ -276,8 +274,8 @@ int sigmoid_attn_bwd_dkdv(const void *q, const void *k, const void *v, const voi
     return bwd_impl(q, k, v, d_o, nullptr, dk, dv, seqlens, seqlens, bias, scale, B, N_max, N_max, H, d, stream, false, true);
 }
 
-// Bias-gradient partials: 8 bytes per 256 query rows of every (z, h).  The kernels store one float per tile of 256
-// or 128 rows.
+// Bias-gradient partials: 8 bytes per 256 query rows of every (z, h), which hold one float per tile of 128 (d = 64) or
+// 256 rows (d = 128).
 static long long dq_workgroups(int B, int N, int H) { return (((long long)N + 255) / 256) * B * H; }
 
 size_t sigmoid_attn_bwd_dq_dbias_workspace_bytes(int B, int N_max, int H, int d) {
@@ -316,12 +314,10 @@ static int dq_dbias_impl(const void *q, const void *k, const void *v, const void
     p.B = B; p.N = L_q; p.N_str = L_k; p.H = H;
     p.db_part = static_cast<float *>(workspace);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool four = d == 64 && !eight_waves(L_q, L_k);
-    const int e = four        ? launch<DQ, 64, 1, 4, 64, 72, 72, 2, 4, true>(p, s)
-                  : (d == 64) ? launch<DQ, 64, 1, 8, 64, 72, 72, 1, 4, true>(p, s)
-                              : launch<DQ, 128, 1, 8, 64, 144, 136, 1, 2, true>(p, s);
+    const int e = (d == 64) ? launch<DQ, 64, 1, 4, 64, 72, 72, 2, 4, true>(p, s)
+                            : launch<DQ, 128, 1, 8, 64, 144, 136, 1, 2, true>(p, s);
     if (e) return e;
-    const int rows = four ? 128 : 256;
+    const int rows = (d == 64) ? 128 : 256;         // query rows of a partial sum
     hipLaunchKernelGGL(sigattn_db_reduce, dim3((unsigned)B), dim3(256), 0, s, p.db_part, (L_q + rows - 1) / rows * H, dbias);
     return hipGetLastError() == hipSuccess ? SIGATTN_OK : SIGATTN_ERR_LAUNCH;
 }

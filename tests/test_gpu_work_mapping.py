@@ -44,7 +44,7 @@ def test_every_tile_is_taken_once(B, N, H, d):
     (300, 100, 100, 12, 64),     # one tile a head: workgroups go on with the next head
     (240, 300, 300, 4, 128),     # d = 128, 128- and 256-row owner tiles
     (200, 130, 700, 8, 64),      # cross-attention: more key tiles than query tiles (forward: one tile a workgroup)
-    (40, 4096, 4096, 16, 64),    # eight-wave backward, 256-row owner tiles: two tiles a workgroup
+    (40, 4096, 4096, 16, 64),    # long sequences: two tiles a workgroup in the backward pass
     (2, 130, 130, 16384, 64),    # more owner tiles per sequence than workgroups are dealt to one
 ])
 def test_workgroups_of_several_tiles(B, Lq, Lk, H, d):
