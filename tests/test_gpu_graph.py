@@ -49,3 +49,36 @@ def test_forward_backward_step_in_a_hip_graph():
         for got, ref in zip(outs[:4], eager[:4]):
             assert torch.equal(got.view(torch.int16), ref.view(torch.int16)), f"replay {replay}"
         assert torch.equal(outs[4], eager[4]), f"replay {replay}"
+
+
+@pytest.mark.parametrize("B,N,H,d,lens", [(2, 700, 2, 64, (700, 431)), (300, 100, 12, 64, None), (2, 260, 2, 128, (260, 131))])
+def test_joint_backward_call_in_a_hip_graph(B, N, H, d, lens):
+    # sigmoid_attn_bwd as one call: the joint launch of d = 64 (one tile a workgroup, and several), two launches at d = 128
+    lens = np.random.default_rng(9).integers(0, N + 1, size=B) if lens is None else lens
+    w = W.make(B, N, H, d, lens, seed=42)
+    q, k, v, g = (to_dev(x) for x in (w.q, w.k, w.v, w.d_o))
+    sl, b = torch.from_numpy(w.seqlens).cuda(), torch.from_numpy(w.bias).cuda()
+
+    def call(dq, dk, dv, stream):
+        binding.sigmoid_attn_bwd(q, k, v, g, sl, b, w.scale, dq=dq, dk=dk, dv=dv, stream=stream)
+
+    eager = [torch.empty_like(q) for _ in range(3)]
+    call(*eager, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    outs = [torch.empty_like(q) for _ in range(3)]
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call(*outs, side)
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            call(*outs, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    for replay in range(3):
+        for t in outs:
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for got, ref in zip(outs, eager):
+            assert torch.equal(got.view(torch.int16), ref.view(torch.int16)), f"replay {replay}"
