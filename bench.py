@@ -1,8 +1,9 @@
 #!/usr/bin/env python3
 """Benchmark of the padded sigmoid-attention hot path on one MI355X.
 
-A step is one pass of the whole hot path -- forward, then backward (dK/dV kernel, dQ kernel) -- over one
-batch of the seeded synthetic workload, inputs resident in HBM.  The metric is fwd+bwd TFLOPS over
+A step is one pass of the whole hot path -- forward, then backward, through the two calls a training loop makes -- over
+one batch of the seeded synthetic workload, inputs resident in HBM.  (The backward call is one launch at d = 64, a dK/dV
+and a dQ launch at d = 128; the two halves are timed on their own behind the timed steps.)  The metric is fwd+bwd TFLOPS over
 valid-token FLOPs (paper appendix "FLOP Calculation": forward 4 h d sum_z n_z^2, backward 2.5 x that),
 also given as a fraction of the MI355X dense bf16 MFMA peak.  One JSON line is printed.
 
@@ -119,10 +120,15 @@ def main() -> int:
         if ev: ev[0].record(stream)
         binding.sigmoid_attn_fwd(q, k, v, seqlens, bias, w.scale, out=o, stream=stream)
         if ev: ev[1].record(stream)
-        binding.sigmoid_attn_bwd_dkdv(q, k, v, g, seqlens, bias, w.scale, dk=dk, dv=dv, stream=stream)
+        binding.sigmoid_attn_bwd(q, k, v, g, seqlens, bias, w.scale, dq=dq, dk=dk, dv=dv, stream=stream)
         if ev: ev[2].record(stream)
+
+    def halves(ev):
+        ev[0].record(stream)
+        binding.sigmoid_attn_bwd_dkdv(q, k, v, g, seqlens, bias, w.scale, dk=dk, dv=dv, stream=stream)
+        ev[1].record(stream)
         binding.sigmoid_attn_bwd_dq(q, k, v, g, seqlens, bias, w.scale, dq=dq, stream=stream)
-        if ev: ev[3].record(stream)
+        ev[2].record(stream)
 
     # pre-warm: at least PREWARM_MS of device time on untimed steps, whatever --warmup says, so that clocks
     # and power state have settled under this load before the timed region (the chip is power-limited)
@@ -139,16 +145,23 @@ def main() -> int:
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
-    events = [[torch.cuda.Event(enable_timing=True) for _ in range(4)] for _ in range(args.steps)]
+    new_events = lambda n: [[torch.cuda.Event(enable_timing=True) for _ in range(3)] for _ in range(n)]
+    events = new_events(args.steps)
     t0 = time.perf_counter()
     for i in range(args.steps):
         step(events[i])
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
+    half_events = new_events(min(args.steps, 30))
+    for e in half_events:
+        halves(e)
+    torch.cuda.synchronize()
 
-    ms = np.array([[e[j].elapsed_time(e[j + 1]) for j in range(3)] for e in events])   # fwd, dkdv, dq
-    mean_ms = ms.mean(axis=0)
-    ci = [mean_ci99(ms[:, j]) for j in range(3)]
+    times = lambda evs: np.array([[e[j].elapsed_time(e[j + 1]) for j in range(2)] for e in evs])
+    ms, half_ms = times(events), times(half_events)                     # fwd, bwd | dkdv, dq
+    mean_ms, mean_half = ms.mean(axis=0), half_ms.mean(axis=0)
+    ci = [mean_ci99(ms[:, j]) for j in range(2)]
+    half_ci = [mean_ci99(half_ms[:, j]) for j in range(2)]
     step_ms, step_ci = mean_ci99(ms.sum(axis=1))
     pairs = int(np.sum(w.seqlens.astype(np.int64) ** 2))
     f_fwd = 4 * w.H * w.d * pairs
@@ -156,14 +169,14 @@ def main() -> int:
     ms_per_step = wall * 1e3 / args.steps
     tflops = (f_fwd + f_bwd) / (ms_per_step * 1e-3) / 1e12
 
-    # dominant kernel: the one with the largest share of the step
-    names = ["fwd", "bwd_dkdv", "bwd_dq"]
-    alg_flops = [f_fwd, 6 * w.H * w.d * pairs, 4 * w.H * w.d * pairs]    # contractions the pass must do: 2, 3(+S), 2(+S)
-    # algorithmic FLOPs of a launch = the counted FLOPs of the quantities it produces:
-    #   fwd: S, PV (4 d per pair); dK/dV kernel: dP, dV, dK (6 d per pair); dQ kernel: dQ (2 d) + its share
-    #   of the single counted recomputation of S (2 d), i.e. backward = 10 d per pair in total.
-    dom = int(np.argmax(mean_ms))
-    achieved = alg_flops[dom] / (mean_ms[dom] * 1e-3) / 1e12
+    # dominant kernel of the step: the backward launch at d = 64, the dK/dV launch of the two at d = 128.  Algorithmic
+    # FLOPs of a launch = the counted FLOPs of the quantities it produces (per pair: fwd S, PV 4 d; dK/dV: dP, dV, dK 6 d;
+    # dQ: dQ 2 d and its share of the single counted recomputation of S 2 d; backward 10 d in all).
+    if w.d == 64:
+        dom, dom_ms, dom_flops = "bwd", mean_ms[1], f_bwd
+    else:
+        dom, dom_ms, dom_flops = "bwd_dkdv", mean_half[0], 6 * w.H * w.d * pairs
+    achieved = dom_flops / (dom_ms * 1e-3) / 1e12
 
     out = {
         "metric": "fwd+bwd TFLOPS (valid-token FLOPs) + % of bf16 MFMA peak, d=64 N=8192",
@@ -176,14 +189,16 @@ def main() -> int:
         "pct_of_bf16_peak": round(100 * tflops / PEAK_BF16_TFLOPS, 2),
         "prewarm": {"device_ms": round(prewarm_ms, 1), "steps": prewarm_steps,
                     "note": "untimed steps before --warmup, at least 100 ms of device time"},
-        "kernels_ms": {n: round(float(m), 4) for n, m in zip(names, mean_ms)},
-        "kernels_ms_ci99": {n: round(c[1], 4) for n, c in zip(names, ci)},
+        "kernels_ms": {n: round(float(m), 4) for n, m in zip(("fwd", "bwd"), mean_ms)},
+        "kernels_ms_ci99": {n: round(c[1], 4) for n, c in zip(("fwd", "bwd"), ci)},
+        "halves_ms": {n: round(float(m), 4) for n, m in zip(("bwd_dkdv", "bwd_dq"), mean_half)},
+        "halves_ms_ci99": {n: round(c[1], 4) for n, c in zip(("bwd_dkdv", "bwd_dq"), half_ci)},
         "step_ms_from_events": {"mean": round(step_ms, 4), "ci99": round(step_ci, 4), "n": args.steps},
         "kernels_tflops": {"fwd": round(f_fwd / (mean_ms[0] * 1e-3) / 1e12, 1),
-                           "bwd": round(f_bwd / ((mean_ms[1] + mean_ms[2]) * 1e-3) / 1e12, 1)},
-        "roofline": {"bound": "mfma", "kernel": names[dom], "achieved": round(achieved, 1),
+                           "bwd": round(f_bwd / (mean_ms[1] * 1e-3) / 1e12, 1)},
+        "roofline": {"bound": "mfma", "kernel": dom, "achieved": round(achieved, 1),
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
-                     "traffic": measured_traffic_bytes(w.name, w.seed, names[dom])},
+                     "traffic": measured_traffic_bytes(w.name, w.seed, dom)},
         "context": PAPER_CONTEXT,
     }
     if not args.no_mfma_ceiling:
