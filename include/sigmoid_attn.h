@@ -88,7 +88,7 @@ int sigmoid_attn_bwd(const void *q, const void *k, const void *v, const void *d_
 /*
  * The two halves of the backward pass on their own, as the paper states them: Alg. 2 (dQ only) and
  * Alg. 3 (dK and dV only).  Arguments as for sigmoid_attn_bwd; neither needs a workspace.
- * sigmoid_attn_bwd is equivalent to calling both on one stream.
+ * sigmoid_attn_bwd is equivalent to calling both on one stream (at d = 64 it makes one launch of both).
  */
 int sigmoid_attn_bwd_dq(const void *q, const void *k, const void *v, const void *d_o, void *dq,
                         const int32_t *seqlens, const float *bias, float scale,
@@ -122,8 +122,9 @@ int sigmoid_attn_cross_bwd(const void *q, const void *k, const void *v, const vo
  *   dbias     : out, device float [B]; fully overwritten (0 for an empty sequence)
  *   workspace : device scratch of at least sigmoid_attn_bwd_dq_dbias_workspace_bytes(...) bytes, 16-byte
  *               aligned, owned by the caller; contents irrelevant on entry, undefined on exit
- * The summation order is fixed: results are bitwise reproducible.  nwg = B * H * ceil(N_max / 256)
- * must be below 2^31 (SIGATTN_ERR_TOO_LARGE).
+ * The workspace holds 8 bytes per 256 query rows of every (z, h), that is B * H * ceil(N_max / 256) * 8; the partial
+ * sums in it are one float per 128 query rows at d = 64 and per 256 at d = 128.  The summation order is fixed by the
+ * shapes: results are bitwise reproducible.  B * H * ceil(N_max / 128) must be below 2^31 (SIGATTN_ERR_TOO_LARGE).
  */
 size_t sigmoid_attn_bwd_dq_dbias_workspace_bytes(int B, int N_max, int H, int d);
 int sigmoid_attn_bwd_dq_dbias(const void *q, const void *k, const void *v, const void *d_o, void *dq, float *dbias,
@@ -134,7 +135,7 @@ int sigmoid_attn_bwd_dq_dbias(const void *q, const void *k, const void *v, const
 /*
  * The same with separate query and key lengths (layouts and lengths as for sigmoid_attn_cross_bwd):
  * db_z sums dS_ij over heads, i < n_q and j < n_k.  The workspace is sized by the query side,
- * nwg = B * H * ceil(L_q / 256).
+ * B * H * ceil(L_q / 256) * 8 bytes.
  */
 size_t sigmoid_attn_cross_bwd_dq_dbias_workspace_bytes(int B, int L_q, int L_k, int H, int d);
 int sigmoid_attn_cross_bwd_dq_dbias(const void *q, const void *k, const void *v, const void *d_o, void *dq,
@@ -145,10 +146,10 @@ int sigmoid_attn_cross_bwd_dq_dbias(const void *q, const void *k, const void *v,
 /*
  * sigmoid_attn_bwd_dq_dbias for callers that cannot allocate device memory and have no workspace to pass:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
- * results and errors as sigmoid_attn_bwd_dq_dbias, minus the workspace: the per-workgroup partial sums go
+ * results and errors as sigmoid_attn_bwd_dq_dbias, minus the workspace: the partial sums go
  * to an array of SIGATTN_STATIC_SCRATCH_BYTES bytes that lives in the library's device image (each GPU
  * the library runs on holds its own copy until the process ends).  The call allocates and frees nothing.
- *   limit : B * H * ceil(N_max / 256) * 8 bytes must fit the array (131072 query tiles); beyond that the
+ *   limit : B * H * ceil(N_max / 256) * 8 bytes must fit the array (131072 times 256 query rows); beyond that the
  *           call returns SIGATTN_ERR_TOO_LARGE and enqueues nothing.
  *   races : every call on one GPU uses that GPU's one array, whatever the stream.  Calls whose kernels
  *           may overlap on one GPU (different streams, or graphs replayed concurrently) race on it; calls

@@ -21,7 +21,7 @@ int check_shape(int B, int N, int H, int d) {
     if ((long long)B * H > 2147483647LL) return SIGATTN_ERR_TOO_LARGE;     // grid.x limit
     if ((long long)B * N * H * d >= (1LL << 40)) return SIGATTN_ERR_TOO_LARGE;
     if ((long long)H * d > (1LL << 20)) return SIGATTN_ERR_TOO_LARGE;      // 32-bit lane offsets within one streamed tile
-    if (B > 256 && (long long)N > 262144LL) return SIGATTN_ERR_TOO_LARGE;  // as the header states
+    if (B > 256 && (long long)N > 262144LL) return SIGATTN_ERR_TOO_LARGE;  // a documented limit; the work mapping no longer needs it
     return SIGATTN_OK;
 }
 
@@ -285,7 +285,7 @@ size_t sigmoid_attn_bwd_dq_dbias_workspace_bytes(int B, int N_max, int H, int d)
 
 size_t sigmoid_attn_cross_bwd_dq_dbias_workspace_bytes(int B, int L_q, int L_k, int H, int d) {
     if (check_shape(B, L_k, H, d) != SIGATTN_OK) return 0;
-    return sigmoid_attn_bwd_dq_dbias_workspace_bytes(B, L_q, H, d);     // one partial per 256-row query tile
+    return sigmoid_attn_bwd_dq_dbias_workspace_bytes(B, L_q, H, d);     // sized by the query side
 }
 
 static int dq_dbias_impl(const void *q, const void *k, const void *v, const void *d_o, void *dq, float *dbias,
@@ -358,10 +358,10 @@ int sigmoid_attn_bwd_dq_dbias_static(const void *q, const void *k, const void *v
         (reinterpret_cast<uintptr_t>(dbias) & 3u))
         return SIGATTN_ERR_MISALIGNED;
     const size_t need = sigmoid_attn_bwd_dq_dbias_workspace_bytes(B, N_max, H, d);
-    if (need > (size_t)SIGATTN_STATIC_SCRATCH_BYTES) return SIGATTN_ERR_TOO_LARGE;   // more query tiles than the array holds
+    if (need > (size_t)SIGATTN_STATIC_SCRATCH_BYTES) return SIGATTN_ERR_TOO_LARGE;   // more query rows than the array has room for
     void *ws = static_scratch();
     if (!ws) return SIGATTN_ERR_LAUNCH;
-    // Every workgroup writes its own partial and the second kernel reads exactly those: nothing has to start at zero.
+    // Every owner tile's partial is written and the second kernel reads exactly those: nothing has to start at zero.
     return dq_dbias_impl(q, k, v, d_o, dq, dbias, seqlens, seqlens, bias, scale, B, N_max, N_max, H, d,
                          ws, (size_t)SIGATTN_STATIC_SCRATCH_BYTES, stream);
 }
