@@ -35,6 +35,9 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // at B = 512, N = 512: 2106 / 1850; B = 32, H = 32, N = 512: 225 / 191; B = 16, H = 32, N = 1024: 326 / 309; B = 16, H = 12,
 // N = 4096 (just below the line): 951 / 946; B = 24, H = 12, N = 4096: 2179 / 2182; B = 4, H = 32, N = 4096: 953 / 972;
 // B = 8, H = 12, N = 2048: 125 / 132; forward at B = 24, H = 12, N = 1500: 72 / 78.
+// The host does not know the lengths.  Near the line, a batch of 64-row sequences with a long one at its end (or every
+// tenth) loses by batch order what other spreads gain: forward at B = 40, H = 12, N = 1000 one 30 / 35, every tenth 37 / 42,
+// uniform 90 / 87, lognormal 31 / 24, all valid 153 / 142; backward 80 / 55, 114 / 79, 299 / 274, 88 / 49, 543 / 500.
 int batch_order(const Params &p, long long wgs, int owner_rows) {
     if (p.B > MAP_WAVE_B && ((long long)p.N + owner_rows - 1) / owner_rows > MAP_CLASSES) return 1;
     return p.B * wgs > 16000 + 45LL * p.N_str;
