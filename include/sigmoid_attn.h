@@ -78,6 +78,10 @@ int sigmoid_attn_fwd(const void *q, const void *k, const void *v, void *o,
  *   workspace    : device scratch of at least sigmoid_attn_bwd_workspace_bytes(...) bytes, owned by
  *                  the caller, contents irrelevant on entry and undefined on exit.  That size is 0 for
  *                  every shape (each kernel owns its output tiles), so NULL / 0 is accepted.
+ * With a 16-byte aligned workspace of sigmoid_attn_bwd_onepass_workspace_bytes(...) bytes or more, where that is not 0, the
+ * scores are computed once for all three gradients, which is faster.  dK and dV are the same bits either way; dQ differs
+ * by the rounding of other intermediate values.  Both ways give the same bits in every run.  Calls whose kernels may
+ * overlap need workspaces of their own.
  */
 int sigmoid_attn_bwd(const void *q, const void *k, const void *v, const void *d_o,
                      void *dq, void *dk, void *dv,
@@ -88,7 +92,7 @@ int sigmoid_attn_bwd(const void *q, const void *k, const void *v, const void *d_
 /*
  * The two halves of the backward pass on their own, as the paper states them: Alg. 2 (dQ only) and
  * Alg. 3 (dK and dV only).  Arguments as for sigmoid_attn_bwd; neither needs a workspace.
- * sigmoid_attn_bwd is equivalent to calling both on one stream (at d = 64 it makes one launch of both).
+ * sigmoid_attn_bwd without a workspace is equivalent to calling both on one stream (at d = 64 it makes one launch of both).
  */
 int sigmoid_attn_bwd_dq(const void *q, const void *k, const void *v, const void *d_o, void *dq,
                         const int32_t *seqlens, const float *bias, float scale,
@@ -164,6 +168,10 @@ int sigmoid_attn_bwd_dq_dbias_static(const void *q, const void *k, const void *v
 
 /* Scratch bytes sigmoid_attn_bwd needs for this shape (0 on invalid shapes). */
 size_t sigmoid_attn_bwd_workspace_bytes(int B, int N_max, int H, int d);
+
+/* Scratch bytes with which sigmoid_attn_bwd computes the scores once (0: this shape always takes two passes, and on
+ * invalid shapes).  At most 1 GiB: a larger batch goes through it in slices. */
+size_t sigmoid_attn_bwd_onepass_workspace_bytes(int B, int N_max, int H, int d);
 
 #ifdef __cplusplus
 }

@@ -23,6 +23,7 @@ SIGATTN_ERR_TOO_LARGE = -6
 
 EXPORTS = ("sigmoid_attn_version", "sigmoid_attn_strerror", "sigmoid_attn_fwd", "sigmoid_attn_bwd",
            "sigmoid_attn_bwd_dq", "sigmoid_attn_bwd_dkdv", "sigmoid_attn_bwd_workspace_bytes",
+           "sigmoid_attn_bwd_onepass_workspace_bytes",
            "sigmoid_attn_cross_fwd", "sigmoid_attn_cross_bwd",
            "sigmoid_attn_bwd_dq_dbias", "sigmoid_attn_bwd_dq_dbias_workspace_bytes",
            "sigmoid_attn_cross_bwd_dq_dbias", "sigmoid_attn_cross_bwd_dq_dbias_workspace_bytes",
@@ -87,6 +88,8 @@ def load() -> ctypes.CDLL:
         lib.sigmoid_attn_bwd_dq_dbias_static.restype = ci
         lib.sigmoid_attn_bwd_workspace_bytes.argtypes = [ci, ci, ci, ci]
         lib.sigmoid_attn_bwd_workspace_bytes.restype = sz
+        lib.sigmoid_attn_bwd_onepass_workspace_bytes.argtypes = [ci, ci, ci, ci]
+        lib.sigmoid_attn_bwd_onepass_workspace_bytes.restype = sz
         _lib = lib
     return _lib
 
@@ -101,6 +104,10 @@ def sigmoid_attn_strerror(code: int) -> str:
 
 def sigmoid_attn_bwd_workspace_bytes(B: int, N_max: int, H: int, d: int) -> int:
     return int(load().sigmoid_attn_bwd_workspace_bytes(B, N_max, H, d))
+
+
+def sigmoid_attn_bwd_onepass_workspace_bytes(B: int, N_max: int, H: int, d: int) -> int:
+    return int(load().sigmoid_attn_bwd_onepass_workspace_bytes(B, N_max, H, d))
 
 
 # The marshalling of a call is most of what a small problem costs (two 256-token sequences: 28 us of host work
@@ -133,6 +140,20 @@ def _stream_ptr(stream) -> int:
     return int(stream.cuda_stream)
 
 
+def _scratch(nbytes: int, like, stream):
+    """`nbytes` of device memory for a call on `stream`, or None: it belongs to that stream, so that it is handed out again
+    only to work behind the call.  None where it cannot be had (no memory; a stream that torch does not know)."""
+    try:
+        if stream is None or stream.cuda_stream == _stream_ptr(None):
+            return torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+        if isinstance(stream, torch.cuda.Stream):
+            with torch.cuda.stream(stream):
+                return torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+    except torch.OutOfMemoryError:
+        pass
+    return None
+
+
 def sigmoid_attn_fwd(q, k, v, seqlens, bias, scale: float, out=None, stream=None):
     """O = sigmoid(scale * Q K^T + bias) V over valid tokens; returns `out` (allocated if None)."""
     _check(q, "q")
@@ -151,7 +172,8 @@ def sigmoid_attn_fwd(q, k, v, seqlens, bias, scale: float, out=None, stream=None
 
 def sigmoid_attn_bwd(q, k, v, d_o, seqlens, bias, scale: float, dq=None, dk=None, dv=None, workspace=None,
                      stream=None) -> Tuple:
-    """(dQ, dK, dV) from the forward inputs and dO; outputs and workspace are allocated if None."""
+    """(dQ, dK, dV) from the forward inputs and dO; outputs and workspace are allocated if None (the workspace for the
+    length of the call, where the shape is computed in one pass)."""
     _check(q, "q")
     shape = q.shape
     _check(k, "k", shape)
@@ -161,9 +183,10 @@ def sigmoid_attn_bwd(q, k, v, d_o, seqlens, bias, scale: float, dq=None, dk=None
     _check_vec(seqlens, "seqlens", B, torch.int32)
     _check_vec(bias, "bias", B, torch.float32)
     dq, dk, dv = _output(dq, "dq", q), _output(dk, "dk", q), _output(dv, "dv", q)
-    need = sigmoid_attn_bwd_workspace_bytes(B, N, H, d)
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+    if workspace is None:
+        need = sigmoid_attn_bwd_onepass_workspace_bytes(B, N, H, d)
+        if need > 0:
+            workspace = _scratch(need, q, stream)
     ws_ptr = 0 if workspace is None else workspace.data_ptr()
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     rc = load().sigmoid_attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), d_o.data_ptr(), dq.data_ptr(),

@@ -1,6 +1,7 @@
 // Host side of libsigattn: argument validation, kernel selection and launch behind the C ABI
 // declared in include/sigmoid_attn.h.  Validation happens before any HIP call.
 #include "sigattn_kernels.hpp"
+#include "sigattn_onepass.hpp"
 #include "sigmoid_attn.h"
 
 #include <cmath>
@@ -128,11 +129,60 @@ int launch_bwd(Params kv, Params q, hipStream_t stream) {
                    stream, kv, q, q_first, (int)(q_first ? q_tiles : kv_tiles));
 }
 
+// ---- the backward pass of d = 64 in one launch over the scores (sigattn_onepass.hpp)
+
+constexpr size_t ONEPASS_LIMIT = (size_t)1 << 30;      // scratch of one launch; a larger batch goes through it in slices
+
+size_t onepass_bytes(int B, int N, int H) {            // sums of dQ in fp32, whole tiles, and the counts
+    const size_t heads = (size_t)B * H, tiles = ((size_t)N + onepass::BM - 1) / onepass::BM;
+    return heads * (((size_t)N + onepass::BN - 1) / onepass::BN) * onepass::TILE_BYTES + heads * tiles * onepass::FLAGS * sizeof(int);
+}
+
+// Sequences of one launch; 0: this shape takes two passes.  One pass does five contractions for seven, but in half as many
+// workgroups of twice the keys, one to a CU, each of which follows the one before it in its head: it needs three rounds of
+// them (768) and heads long enough that 256-row tiles round little.  one pass / two, us: B = 8, H = 12, N = 2048 (768 tiles)
+// 299 / 377; B = 16, N = 1024 (768) 161 / 205; B = 4, N = 8192 2293 / 2778; with lengths from a quarter of N on, B = 16,
+// N = 1024 104 / 131; B = 4, N = 4096 348 / 382; B = 2, N = 8192 231 / 214.  Below: B = 2, N = 4096 (384) 340 / 355, uniform 160 / 151;
+// B = 4, N = 2048 (384) 172 / 189, 151 / 155; B = 8, N = 1024 (384) 93 / 105, 63 / 55; B = 40, N = 512 133 / 145, 86 / 83;
+// B = 1, N = 1024 (48) 56 / 24.
+int onepass_sequences(int B, int N, int H, int d) {
+    const long long tiles = ((long long)N + onepass::BM - 1) / onepass::BM;
+    if (d != 64 || N < 1024 || B * (H * tiles) < 768) return 0;
+    const size_t one = onepass_bytes(1, N, H);
+    if (one > ONEPASS_LIMIT) return 0;
+    const long long most = (long long)(ONEPASS_LIMIT / one), slices = (B + most - 1) / most;
+    return (int)((B + slices - 1) / slices);           // slices of equal size
+}
+
+int launch_onepass(onepass::Params p, const int per_slice, unsigned char *workspace, hipStream_t stream) {
+    const int B = p.B, T = (p.L_k + onepass::BM - 1) / onepass::BM, TQ = (p.L_q + onepass::BN - 1) / onepass::BN;
+    const size_t row = (size_t)p.H * onepass::D;
+    // A tile of keys takes about one round of its query tiles after another, 256 at a time, and follows the tile before it
+    // by three of them: 768 / TQ heads in turn keep pace, four times as many leave room (measured at the mapping).
+    const long long turn = (3000 + (long long)p.H * TQ - 1) / ((long long)p.H * TQ);
+    for (int z = 0; z < B; z += per_slice) {
+        onepass::Params s = p;
+        s.B = B - z < per_slice ? B - z : per_slice;
+        const size_t q_off = (size_t)z * p.L_q * row, k_off = (size_t)z * p.L_k * row;
+        s.q += q_off; s.d_o += q_off; s.dq += q_off;
+        s.k += k_off; s.v += k_off; s.dk += k_off; s.dv += k_off;
+        s.seqlens_q += z; s.seqlens_k += z; s.bias += z;
+        s.in_order = s.B > MAP_WAVE_B;
+        s.group = (int)(turn < s.B ? turn : s.B);
+        s.part = workspace;
+        s.flags = reinterpret_cast<int *>(workspace + (size_t)s.B * s.H * TQ * onepass::TILE_BYTES);
+        const int counts = s.B * s.H * T * onepass::FLAGS;
+        if (int e = enqueue(onepass::sigattn_clear_counts, ((long long)counts + 255) / 256, 256, 0, stream, s.flags, counts)) return e;
+        if (int e = enqueue(onepass::sigattn_onepass, (long long)s.B * s.H * T, onepass::THREADS, onepass::LDS_BYTES, stream, s)) return e;
+    }
+    return SIGATTN_OK;
+}
+
 }  // namespace
 
 extern "C" {
 
-int sigmoid_attn_version(void) { return 300; }
+int sigmoid_attn_version(void) { return 400; }
 
 const char *sigmoid_attn_strerror(int code) {
     switch (code) {
@@ -149,7 +199,13 @@ const char *sigmoid_attn_strerror(int code) {
 
 size_t sigmoid_attn_bwd_workspace_bytes(int B, int N_max, int H, int d) {
     if (check_shape(B, N_max, H, d) != SIGATTN_OK) return 0;
-    return 0;   // the backward pass owns each output tile exclusively: no scratch, no atomics
+    return 0;   // in two passes each workgroup owns its output tiles: no scratch, no atomics
+}
+
+size_t sigmoid_attn_bwd_onepass_workspace_bytes(int B, int N_max, int H, int d) {
+    if (check_shape(B, N_max, H, d) != SIGATTN_OK) return 0;
+    const int per_slice = onepass_sequences(B, N_max, H, d);
+    return per_slice == 0 ? 0 : onepass_bytes(per_slice, N_max, H);
 }
 
 // ---- common implementations: separate query-side and key-side lengths (self-attention passes them twice)
@@ -262,6 +318,22 @@ int sigmoid_attn_bwd(const void *q, const void *k, const void *v, const void *d_
     if (e0) return e0;       // argument errors first, as the header orders them
     const size_t need = sigmoid_attn_bwd_workspace_bytes(B, N_max, H, d);
     if (need > 0 && (!workspace || workspace_bytes < need)) return SIGATTN_ERR_WORKSPACE;
+    const size_t one = sigmoid_attn_bwd_onepass_workspace_bytes(B, N_max, H, d);
+    if (one > 0 && workspace && workspace_bytes >= one && aligned16(workspace)) {
+        onepass::Params p{};
+        p.q = static_cast<const bf16_t *>(q);
+        p.k = static_cast<const bf16_t *>(k);
+        p.v = static_cast<const bf16_t *>(v);
+        p.d_o = static_cast<const bf16_t *>(d_o);
+        p.dq = static_cast<bf16_t *>(dq);
+        p.dk = static_cast<bf16_t *>(dk);
+        p.dv = static_cast<bf16_t *>(dv);
+        p.seqlens_q = p.seqlens_k = seqlens;
+        p.bias = bias;
+        p.scale = scale;
+        p.B = B; p.L_q = p.L_k = N_max; p.H = H;
+        return launch_onepass(p, onepass_sequences(B, N_max, H, d), static_cast<unsigned char *>(workspace), static_cast<hipStream_t>(stream));
+    }
     return bwd_impl(q, k, v, d_o, dq, dk, dv, seqlens, seqlens, bias, scale, B, N_max, N_max, H, d, stream, true, true);
 }
 
