@@ -133,21 +133,22 @@ int launch_bwd(Params kv, Params q, hipStream_t stream) {
 
 constexpr size_t ONEPASS_LIMIT = (size_t)1 << 30;      // scratch of one launch; a larger batch goes through it in slices
 
-size_t onepass_bytes(int B, int N, int H) {            // sums of dQ in fp32, whole tiles, and the counts
+size_t onepass_bytes(int B, int N, int H) {            // sums of dQ in fp32, whole tiles; plan and counts of the workgroups
     const size_t heads = (size_t)B * H, tiles = ((size_t)N + onepass::BM - 1) / onepass::BM;
-    return heads * (((size_t)N + onepass::BN - 1) / onepass::BN) * onepass::TILE_BYTES + heads * tiles * onepass::FLAGS * sizeof(int);
+    return heads * (((size_t)N + onepass::BN - 1) / onepass::BN) * onepass::TILE_BYTES +
+           heads * tiles * (sizeof(onepass::TileWork) + onepass::FLAGS * sizeof(int));
 }
 
 // Sequences of one launch; 0: this shape takes two passes.  One pass does five contractions for seven, but in half as many
 // workgroups of twice the keys, one to a CU, each of which follows the one before it in its head: it needs three rounds of
-// them (768) and heads long enough that 256-row tiles round little.  one pass / two, us: B = 8, H = 12, N = 2048 (768 tiles)
-// 299 / 377; B = 16, N = 1024 (768) 161 / 205; B = 4, N = 8192 2293 / 2778; with lengths from a quarter of N on, B = 16,
-// N = 1024 104 / 131; B = 4, N = 4096 348 / 382; B = 2, N = 8192 231 / 214.  Below: B = 2, N = 4096 (384) 340 / 355, uniform 160 / 151;
-// B = 4, N = 2048 (384) 172 / 189, 151 / 155; B = 8, N = 1024 (384) 93 / 105, 63 / 55; B = 40, N = 512 133 / 145, 86 / 83;
-// B = 1, N = 1024 (48) 56 / 24.
+// them (768) and heads long enough that 256-row tiles round little.  One pass / two, us, H = 12, all rows valid, lengths from
+// an eighth of N on, lognormal: N = 700, B = 43 (1548 tiles) 260 / 287, 139 / 149, 120 / 127; N = 1024, B = 66 676 / 821, 361 / 415,
+// 274 / 317; N = 2048, B = 60 2187 / 2783, 894 / 1082, 831 / 1012; B = 8, N = 2048 (768 tiles) 288 / 363.  Below: N = 512, B = 86
+// (2064) 278 / 309, 166 / 160, 143 / 133; B = 4, N = 2048 (384) 172 / 189, from a quarter on 151 / 155; B = 8, N = 1024 (384)
+// 93 / 105, 63 / 55; B = 1, N = 1024 (48) 56 / 24.
 int onepass_sequences(int B, int N, int H, int d) {
     const long long tiles = ((long long)N + onepass::BM - 1) / onepass::BM;
-    if (d != 64 || N < 1024 || B * (H * tiles) < 768) return 0;
+    if (d != 64 || N < 640 || B * (H * tiles) < 768) return 0;
     const size_t one = onepass_bytes(1, N, H);
     if (one > ONEPASS_LIMIT) return 0;
     const long long most = (long long)(ONEPASS_LIMIT / one), slices = (B + most - 1) / most;
@@ -167,13 +168,13 @@ int launch_onepass(onepass::Params p, const int per_slice, unsigned char *worksp
         s.q += q_off; s.d_o += q_off; s.dq += q_off;
         s.k += k_off; s.v += k_off; s.dk += k_off; s.dv += k_off;
         s.seqlens_q += z; s.seqlens_k += z; s.bias += z;
-        s.in_order = s.B > MAP_WAVE_B;
         s.group = (int)(turn < s.B ? turn : s.B);
+        const long long wgs = (long long)s.B * s.H * T;
         s.part = workspace;
-        s.flags = reinterpret_cast<int *>(workspace + (size_t)s.B * s.H * TQ * onepass::TILE_BYTES);
-        const int counts = s.B * s.H * T * onepass::FLAGS;
-        if (int e = enqueue(onepass::sigattn_clear_counts, ((long long)counts + 255) / 256, 256, 0, stream, s.flags, counts)) return e;
-        if (int e = enqueue(onepass::sigattn_onepass, (long long)s.B * s.H * T, onepass::THREADS, onepass::LDS_BYTES, stream, s)) return e;
+        s.plan = reinterpret_cast<onepass::TileWork *>(workspace + (size_t)s.B * s.H * TQ * onepass::TILE_BYTES);
+        s.flags = reinterpret_cast<int *>(s.plan + wgs);
+        if (int e = enqueue(onepass::sigattn_onepass_plan, (wgs + onepass::PLAN_THREADS - 1) / onepass::PLAN_THREADS, onepass::PLAN_THREADS, 0, stream, s)) return e;
+        if (int e = enqueue(onepass::sigattn_onepass, wgs, onepass::THREADS, onepass::LDS_BYTES, stream, s)) return e;
     }
     return SIGATTN_OK;
 }

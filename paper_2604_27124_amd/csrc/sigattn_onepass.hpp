@@ -40,6 +40,9 @@ constexpr size_t LDS_BYTES = STREAM_BYTES + KT_BYTES + 2 * DS_BYTES + 1024;   //
 constexpr int TILE_BYTES = BN * D * 4;       // partial sums of a query tile
 constexpr int FLAGS = NW;                    // progress counters of a workgroup
 
+// One workgroup's work: key tile j of head h of sequence z, which has nq valid queries and nk valid keys.
+struct alignas(32) TileWork { int z, h, j, nq, nk; float bias; };
+
 struct Params {
     const bf16_t *q, *k, *v, *d_o;           // q, d_o [B, L_q, H, D];  k, v [B, L_k, H, D]
     bf16_t *dq, *dk, *dv;
@@ -47,83 +50,80 @@ struct Params {
     const float *bias;
     float scale;
     int B, L_q, L_k, H;
-    int in_order;                            // work mapping: 1 = batch order, 0 = longest sequences first
     int group;                               // sequences whose tiles are dealt in turn
-    int *flags;                              // [B][H][key tiles][FLAGS], zeros at the start
+    TileWork *plan;                          // [B H key tiles]
+    int *flags;                              // [B][H][key tiles][FLAGS]
     unsigned char *part;                     // [B][H][query tiles][TILE_BYTES]
 };
 
-// One workgroup: key tile j of head h of sequence z, which has nq valid queries and nk valid keys.
-struct Work { int z, h, j, nq, nk; };
-
 __device__ __forceinline__ int clamp_len(int v, int n) { return v < 0 ? 0 : (v > n ? n : v); }
 
-__device__ __forceinline__ int wave_inclusive_sum(int v, const int lane) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int up = __shfl_up(v, off, 64);
-        v += (lane >= off) ? up : 0;
-    }
-    return v;
-}
-
-// Work mapping.  A tile of keys has a larger id than the tiles before it in its head (the order of the chain), and long
-// sequences come first.  A tile can only follow the one before it at a distance of about three query tiles, so tiles of one
-// head that start together wait for each other; `group` sequences of neighbouring rank are therefore dealt in turn, tile by
-// tile.  Up to 64 sequences are ranked by their queries (a workgroup's time), in registers, one sequence per lane; more
-// are taken in batch order, in groups as well; padded tiles, which only write zeros, come last or with their sequence.
+// The plan of a launch: the work of every workgroup, and its progress counts set to zero.  Made by a kernel of its own, a
+// thread per tile: in the workgroups themselves it took 5000 to 7000 clocks of each one's 26000 (N = 128) to 170000 (N = 2048).
+//
+// A tile of keys has a larger id than the tiles before it in its head (the order of the chain), and long sequences come
+// first.  A tile can only follow the one before it at a distance of about three query tiles, so tiles of one head that
+// start together wait for each other; `group` sequences of neighbouring rank are therefore dealt in turn, tile by tile.  Up
+// to PLAN_B sequences are ranked, by their queries (a workgroup's time); more are taken in batch order, in groups as well.
+// Padded tiles, which only write zeros, come last or with their sequence.
 // Time with groups of one / few / all sequences, us: 4 x 12 heads, 2958 to 7122 rows 995 / 1004 / 1034; 8 x 12 x 2048
 // 325 / 303 / 299; 16 x 12 of 64 to 4096 rows 593 / 580 / 605; 4 x 12 x 8192 2345 / 2265 / 2240.
-__device__ __forceinline__ Work map_work(const Params &p, const int id) {
-    const int T = (p.L_k + BM - 1) / BM;
-    if (p.in_order) {                                               // groups of sequences, tile by tile
-        const int per = p.group * p.H * T, grp = id / per, z0 = grp * p.group;
-        const int heads = (p.B - z0 < p.group ? p.B - z0 : p.group) * p.H, e = id - grp * per;
-        const int j = e / heads, r = e - j * heads, z = z0 + r / p.H;
-        return {z, r % p.H, j, clamp_len(p.seqlens_q[z], p.L_q), clamp_len(p.seqlens_k[z], p.L_k)};
-    }
-    const int lane = threadIdx.x & 63;
-    const int mq = lane < p.B ? clamp_len(p.seqlens_q[lane], p.L_q) : 0;
-    const int mk = lane < p.B ? clamp_len(p.seqlens_k[lane], p.L_k) : 0;
-    const int my_tiles = (mk + BM - 1) / BM;
-    int rank = 0, all_valid = 0;
-    for (int u = 0; u < p.B; ++u) {
-        rank += (__builtin_amdgcn_readlane(mq, u) >= mq + (lane <= u)) ? 1 : 0;       // more queries, or as many and earlier in the batch
-        all_valid += __builtin_amdgcn_readlane(my_tiles, u);
-    }
-    if (id >= all_valid * p.H) {                                    // padded tiles, in batch order
-        const int cnt = lane < p.B ? T - my_tiles : 0;
-        const int lo = (all_valid + wave_inclusive_sum(cnt, lane) - cnt) * p.H;
-        const int z = __builtin_ctzll(__builtin_amdgcn_ballot_w64(lane < p.B && id >= lo && id < lo + cnt * p.H));
-        const int e = id - __builtin_amdgcn_readlane(lo, z);
-        return {z, e % p.H, __builtin_amdgcn_readlane(my_tiles, z) + e / p.H, __builtin_amdgcn_readlane(mq, z), __builtin_amdgcn_readlane(mk, z)};
-    }
-    // by rank: lane r holds the sequence of rank r (lanes without one keep their own, which has no tiles)
-    const int to = 4 * (lane < p.B ? rank : lane);
-    const int seq = __builtin_amdgcn_ds_permute(to, lane), tiles = __builtin_amdgcn_ds_permute(to, my_tiles);
-    // the group of this id
-    const int start = (wave_inclusive_sum(tiles, lane) - tiles) * p.H;
-    const int lo = 63 - __builtin_clzll(__builtin_amdgcn_ballot_w64(lane < p.B && lane % p.group == 0 && start <= id));
-    const int hi = lo + p.group < p.B ? lo + p.group : p.B;
-    const int e = id - __builtin_amdgcn_readlane(start, lo);
-    for (int base = 0;; base += 64) {                               // lane l counts the group's tiles in front of tile base + l
-        const int j = base + lane;
-        int before = 0, here = 0;
-        for (int u = lo; u < hi; ++u) {
-            const int t = __builtin_amdgcn_readlane(tiles, u);
-            before += t < j ? t : j;
-            here += t > j ? 1 : 0;
+constexpr int PLAN_THREADS = 256, PLAN_B = PLAN_THREADS;
+
+__global__ void __launch_bounds__(PLAN_THREADS) sigattn_onepass_plan(const Params p) {
+    __shared__ int s_q[PLAN_B], s_rank[PLAN_B], s_tiles[PLAN_B];     // queries and rank of a sequence, tiles of a rank
+    __shared__ int s_before[PLAN_B + 1], s_padded[PLAN_B + 1];       // tiles of the ranks before; padded tiles of the sequences before
+    const int T = (p.L_k + BM - 1) / BM, tid = threadIdx.x;
+    const bool ranked = p.B <= PLAN_B;
+    if (ranked) {
+        const int q = tid < p.B ? clamp_len(p.seqlens_q[tid], p.L_q) : -1;
+        const int tiles = tid < p.B ? (clamp_len(p.seqlens_k[tid], p.L_k) + BM - 1) / BM : T;
+        s_q[tid] = q;
+        __syncthreads();
+        int rank = 0;
+        for (int u = 0; u < p.B; ++u) rank += s_q[u] > q || (s_q[u] == q && u < tid) ? 1 : 0;
+        s_rank[tid] = rank;
+        if (tid < p.B) s_tiles[rank] = tiles;
+        __syncthreads();
+        s_before[tid + 1] = tid < p.B ? s_tiles[tid] : 0;
+        s_padded[tid + 1] = T - tiles;
+        if (tid == 0) s_before[0] = s_padded[0] = 0;
+        for (int off = 1; off < PLAN_B; off <<= 1) {                 // inclusive prefix sums
+            __syncthreads();
+            const int x = tid >= off ? s_before[tid + 1 - off] : 0, y = tid >= off ? s_padded[tid + 1 - off] : 0;
+            __syncthreads();
+            s_before[tid + 1] += x;
+            s_padded[tid + 1] += y;
         }
-        const unsigned long long hit = __builtin_amdgcn_ballot_w64(e >= before * p.H && e < (before + here) * p.H);
-        if (hit == 0) continue;
-        const int src = __builtin_ctzll(hit), jj = base + src;
-        const int r = e - __builtin_amdgcn_readlane(before, src) * p.H, place = r / p.H;
-        const bool has = lane >= lo && lane < hi && tiles > jj;
-        const unsigned long long members = __builtin_amdgcn_ballot_w64(has);
-        const int pos = __builtin_amdgcn_mbcnt_hi((unsigned)(members >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)members, 0));
-        const int z = __builtin_amdgcn_readlane(seq, __builtin_ctzll(__builtin_amdgcn_ballot_w64(has && pos == place)));
-        return {z, r - place * p.H, jj, __builtin_amdgcn_readlane(mq, z), __builtin_amdgcn_readlane(mk, z)};
+        __syncthreads();
     }
+    const int i = blockIdx.x * PLAN_THREADS + tid;                   // = ((z H) + h) T + j
+    if (i >= p.B * p.H * T) return;
+    const int j = i % T, h = i / T % p.H, z = i / T / p.H;
+    int id;
+    if (!ranked) {
+        const int z0 = z - z % p.group, members = p.B - z0 < p.group ? p.B - z0 : p.group;
+        id = z0 * p.H * T + (j * members + z - z0) * p.H + h;
+    } else {
+        const int rank = s_rank[z], mine = s_tiles[rank], lo = rank - rank % p.group;
+        int at;                                                      // tiles of one head each in front of this one
+        if (j < mine) {
+            at = s_before[lo];
+            for (int r = lo; r < lo + p.group && r < p.B; ++r) {
+                const int t = s_tiles[r];
+                at += (t < j ? t : j) + (r < rank && t > j ? 1 : 0);
+            }
+        } else {
+            at = s_before[p.B] + s_padded[z] + j - mine;
+        }
+        id = at * p.H + h;
+    }
+    const TileWork w = {z, h, j, clamp_len(p.seqlens_q[z], p.L_q), clamp_len(p.seqlens_k[z], p.L_k), p.bias[z]};
+    p.plan[id] = w;
+    const u32x4 z4 = {0u, 0u, 0u, 0u};
+    u32x4 *const counts = reinterpret_cast<u32x4 *>(p.flags + (size_t)i * FLAGS);
+    counts[0] = z4;
+    counts[1] = z4;
 }
 
 constexpr int SC1 = 16;              // cache policy of a buffer access: agent scope (stores write through, loads miss)
@@ -133,7 +133,7 @@ constexpr int MAX_SPINS = 1 << 24;   // of a wait, each above a microsecond: far
 __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr float LOG2E = 1.4426950408889634f;
-    const Work work = map_work(p, blockIdx.x);
+    const TileWork work = p.plan[blockIdx.x];
     const int z = __builtin_amdgcn_readfirstlane(work.z), h = __builtin_amdgcn_readfirstlane(work.h);
     const int j = __builtin_amdgcn_readfirstlane(work.j);
     const int nq = __builtin_amdgcn_readfirstlane(work.nq), nk = __builtin_amdgcn_readfirstlane(work.nk);
@@ -165,22 +165,7 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
     const int c = lane & 31, g = lane >> 5;
     const float c1 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, -p.scale * LOG2E)));
     const float cb = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int,
-        __builtin_amdgcn_exp2f(__builtin_fminf(__builtin_fmaxf(-p.bias[z] * LOG2E, -126.0f), 126.0f)))));
-
-    // ---- owner rows
-    bf16x8 xa[4], xb[4];
-    {
-        const int rows = nk - m0 < BM ? nk - m0 : BM;
-        const size_t base = base_k + (size_t)m0 * row_stride;
-        const int bytes = __builtin_amdgcn_readfirstlane(rows * (int)row_stride * 2);
-        const auto d1 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(p.k + base), 0, bytes, 0x00027000);
-        const auto d2 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(p.v + base), 0, bytes, 0x00027000);
-        const int off = (int)(((unsigned)(wave * 32 + c) * (unsigned)row_stride + 8u * g) * 2u);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) xa[ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(d1, off + 32 * ks, 0, 0));
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) xb[ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(d2, off + 32 * ks, 0, 0));
-    }
+        __builtin_amdgcn_exp2f(__builtin_fminf(__builtin_fmaxf(-work.bias * LOG2E, -126.0f), 126.0f)))));
 
     // ---- streamed tiles
     const int r0 = tid >> 3, col0 = (tid & 7) * 8;
@@ -223,6 +208,7 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
     const int dsr0 = ds_base + grp * (int)DS_BYTES + kr * 128 + ((64 * nbq + 32 * g16 + 8 * (i16 & 3)) ^ swz(kr));
     const int dsr1 = ds_base + grp * (int)DS_BYTES + (kr + 4) * 128 + ((64 * nbq + 32 * g16 + 8 * (i16 & 3)) ^ swz(kr + 4));
 
+    bf16x8 xa[4], xb[4];                                              // owner rows: lane holds row c of its wave's 32, columns 16 ks + 8 g + 0..7
     f32x16 acc0[2], acc1[2], dqa;
     f32x16 sbuf[2], dbuf[2];
     u32x4 pbuf[2][2], dsbuf[2][2];
@@ -399,21 +385,58 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
             __builtin_amdgcn_sched_barrier(0);
         });
     };
+    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
     using T_ = IntC<1>;
     using F_ = IntC<0>;
-    // ---- prologue
+    // ---- prologue: the first two tiles are requested, and the owner rows, by whole rows.  K and V pass through the place of dS:
+    // from there every wave takes its operands, and K^T is made with the transposing read.  (Operands loaded straight from
+    // memory and K^T written element by element: 2000 clocks more.)
     load_tile();
-    u32x4 f1 = st1, f2 = st2;
-    load_tile();
-    // K^T: row position of head-dim column d, so that a lane's 16 sums of dQ are 16 columns in a row
+    const u32x4 f1 = st1, f2 = st2;
+    {
+        const int rows = nk - m0 < BM ? nk - m0 : BM;
+        const int bytes = __builtin_amdgcn_readfirstlane(rows * (int)row_stride * 2), pass = 64 * (int)row_stride * 2;
+        const auto d1 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(p.k + base_k + (size_t)m0 * row_stride), 0, bytes, 0x00027000);
+        const auto d2 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(p.v + base_k + (size_t)m0 * row_stride), 0, bytes, 0x00027000);
+        u32x4 rk[4], rv[4];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
+        for (int i = 0; i < 4; ++i) rk[i] = __builtin_amdgcn_raw_buffer_load_b128(d1, (int)ld_off0, i * pass, 0);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            // d % 16 = 8 g + e, (d >> 4) & 1 = ks & 1, d / 32 = ks / 2
-            const int pos = 32 * (ks / 2) + 8 * ((e >> 2)) + 4 * (ks & 1) + (e & 3);
-            kts[(pos + 16 * g) * LDT + key] = xa[ks][e];
+        for (int i = 0; i < 4; ++i) rv[i] = __builtin_amdgcn_raw_buffer_load_b128(d2, (int)ld_off0, i * pass, 0);
+        load_tile();
+        __builtin_amdgcn_sched_barrier(0);
+        *reinterpret_cast<u32x4 *>(w1) = f1;
+        *reinterpret_cast<u32x4 *>(w1 + Y2) = f2;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            unsigned char *const home = smem + ds_base + (r0 + 64 * i) * 128 + ((2 * col0) ^ swz(r0));
+            *reinterpret_cast<u32x4 *>(home) = rk[i];
+            *reinterpret_cast<u32x4 *>(home + DS_BYTES) = rv[i];
         }
+    }
+    barrier();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        const unsigned char *const a = smem + ds_base + key * 128 + ((32 * ks + 16 * g) ^ swz(key));
+        xa[ks] = *reinterpret_cast<const bf16x8 *>(a);
+        xb[ks] = *reinterpret_cast<const bf16x8 *>(a + DS_BYTES);
+    }
+    // K^T of the wave's keys.  Row position of head-dim column d: 8 (d % 16 / 4) + 4 (d / 16 % 2) + d % 4 of its 32, so that a
+    // lane's 16 sums of dQ are 16 columns in a row.
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh)                                   // 16 keys
+#pragma unroll
+        for (int db = 0; db < 4; ++db) {                             // 16 columns
+            const int from = wave * 32 + 16 * kh + 4 * (lane >> 4) + (i16 >> 2);
+            const s16x4 t = __builtin_amdgcn_ds_read_tr16_b64_v4i16(SIGATTN_LDS_PTR(s16x4, smem + ds_base + from * 128 + ((32 * db + 8 * (i16 & 3)) ^ swz(from))));
+            const int pos = 32 * (db / 2) + 8 * (i16 >> 2) + 4 * (db & 1) + (i16 & 3);
+            *reinterpret_cast<s16x4 *>(kts + pos * LDT + wave * 32 + 16 * kh + 4 * (lane >> 4)) = t;
+        }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) xa[ks] = scale_bf16x8(xa[ks], c1);
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb) { acc0[mb] = zero; acc1[mb] = zero; }
+    barrier();
     if (m0 + BM > nk) {                                              // rows of dS of the keys behind the end: zeros
         if (!key_ok) {
             const u32x4 z4 = {0u, 0u, 0u, 0u};
@@ -425,19 +448,11 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
         }
     }
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) xa[ks] = scale_bf16x8(xa[ks], c1);
-    *reinterpret_cast<u32x4 *>(w1) = f1;
-    *reinterpret_cast<u32x4 *>(w1 + Y2) = f2;
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb) { acc0[mb] = zero; acc1[mb] = zero; }
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-#pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
         sbuf[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_read_rows(rd + 16 * ks), xa[ks], ks == 0 ? zero : sbuf[0], 0, 0, 0);
         dbuf[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_read_rows(rd + Y2 + 16 * ks), xb[ks], ks == 0 ? zero : dbuf[0], 0, 0, 0);
     }
 
-    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
     const int L = ntiles - 1;
     const int tail = nq - L * BN;
     auto mask_block = [&](auto nb_c) {
@@ -454,11 +469,23 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto dq_bulk = [&](auto k0, auto k1) {
-        static_for<decltype(k0)::value, decltype(k1)::value>([&](auto k_) {
-            dq_fetch_a(k_);
-            dq_fetch_b(k_);
-            dqa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, qb, dqa, 0, 0, 0);
+    auto dq_bulk = [&](auto k0, auto k1) {                           // without anything else between: four operand pairs ahead
+        constexpr int A = decltype(k0)::value, N = decltype(k1)::value - A;
+        bf16x8 a[4], b[4];
+        auto get = [&](auto k_) {
+            constexpr int K = decltype(k_)::value;
+            dq_fetch_a(IntC<A + K>{});
+            dq_fetch_b(IntC<A + K>{});
+            a[K % 4] = qa;
+            b[K % 4] = qb;
+        };
+        static_for<0, 4>([&](auto k_) { get(k_); });
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<0, N>([&](auto k_) {
+            constexpr int K = decltype(k_)::value;
+            dqa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[K % 4], b[K % 4], dqa, 0, 0, 0);
+            if constexpr (K + 4 < N) get(IntC<K + 4>{});
+            __builtin_amdgcn_sched_barrier(0);
         });
     };
     // ON: this wave works on dQ of tile t - 1 (in the second step here and the first step of the next tile)
@@ -555,11 +582,6 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
             }
     }
     zero_dq_share();
-}
-
-__global__ void __launch_bounds__(256) sigattn_clear_counts(int *flags, const int n) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) flags[i] = 0;
 }
 
 }  // namespace onepass

@@ -31,7 +31,8 @@ def lengths(B, N, seed):
 
 @pytest.mark.parametrize("B,N,H", [
     (20, 1030, 8),       # ranked; one query row in the last of 17 tiles, 6 keys in the last of five
-    (70, 1024, 3),       # batch order, groups of sequences, the last one smaller
+    (70, 1024, 3),       # more sequences than lanes, ranked
+    (260, 650, 2),       # batch order, groups of sequences, the last one smaller
     (5, 4100, 10),       # a few sequences a group, long chains
     (1, 16500, 12),      # more tiles of a head than lanes
 ])

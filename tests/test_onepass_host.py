@@ -1,5 +1,5 @@
 """The one-pass backward on the host: which shapes take it, what the compiled kernel has to hold to, and that its work
-mapping gives every tile once and in the order the chain of a head needs."""
+plan gives every tile once and in the order the chain of a head needs."""
 import os
 import random
 import re
@@ -15,9 +15,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 def test_workspace_size():
     f = A.sigmoid_attn_bwd_onepass_workspace_bytes
-    assert f(4, 8192, 12, 64) == 48 * (128 * 64 * 64 * 4 + 32 * 8 * 4)
+    assert f(4, 8192, 12, 64) == 48 * (128 * 64 * 64 * 4 + 32 * (8 * 4 + 32))
     assert f(8, 2048, 12, 64) > 0 and f(7, 2048, 12, 64) == 0          # 768 tiles of 256 keys
-    assert f(16, 1024, 12, 64) > 0 and f(64, 1023, 12, 64) == 0
+    assert f(16, 1024, 12, 64) > 0 and f(64, 639, 12, 64) == 0
     assert f(4, 8192, 12, 128) == 0 and f(0, 8192, 12, 64) == 0
     assert 0 < f(1000, 4096, 16, 64) <= 1 << 30                        # in slices
     assert f(1, 1100, 16384, 64) == 0                                  # one sequence that no slice can hold
@@ -31,7 +31,7 @@ def test_compiled_kernel(tmp_path):
     subprocess.run([B.hipcc(), *flags, "-I", os.path.join(ROOT, "include"), "-S", "--cuda-device-only", "-o", str(out),
                     os.path.join(B.CSRC, "sigattn_api.hip")], check=True, capture_output=True)
     text = out.read_text()
-    text = text[re.search(r"^_ZN7sigattn7onepass15sigattn_onepass\w+:", text, re.M).start():]
+    text = text[re.search(r"^_ZN7sigattn7onepass15sigattn_onepassE\w+:", text, re.M).start():]
     end = text.index(".Lfunc_end")
     meta = dict(re.findall(r"^; (NumVgprs|ScratchSize|Occupancy): (\d+)", text[end:end + 6000], re.M)[:3])
     assert meta["ScratchSize"] == "0" and meta["Occupancy"] == "2"
@@ -39,7 +39,7 @@ def test_compiled_kernel(tmp_path):
     body = [l for l in body if l and not l.startswith(".")]
     assert not any(re.match(r"v_pk_(add|mul|fma)_f32", l) for l in body)
     waits = [re.search(r"s_waitcnt .*lgkmcnt\((\d+)\)", body[i - 1]) for i, l in enumerate(body) if l == "s_barrier"]
-    assert len(waits) == 10 and all(m and m.group(1) == "0" for m in waits)
+    assert len(waits) == 11 and all(m and m.group(1) == "0" for m in waits)
     counts = [i for i, l in enumerate(body) if l.startswith("global_store_dword ")]
     assert counts
     for i in counts:
@@ -48,41 +48,32 @@ def test_compiled_kernel(tmp_path):
         assert "s_waitcnt vmcnt(0)" in body[sums:i], body[sums:i]
 
 
-def map_work(wg, nq, nk, H, T, group):
-    """The device's mapping of a ranked launch, step by step (lists stand for the lanes of a wave)."""
-    n = len(nq)
-    tiles_of = [(k + 255) // 256 for k in nk]
-    if wg >= sum(tiles_of) * H:                                        # padded tiles
-        lo = sum(tiles_of)
-        for z in range(n):
-            if lo * H <= wg < (lo + T - tiles_of[z]) * H:
-                e = wg - lo * H
-                return z, e % H, tiles_of[z] + e // H
-            lo += T - tiles_of[z]
-    rank = [sum(nq[u] >= nq[l] + (l <= u) for u in range(n)) for l in range(n)]
-    seq = sorted(range(n), key=lambda l: rank[l])
-    tiles = [tiles_of[z] for z in seq]
-    start = [sum(tiles[:l]) * H for l in range(n)]
-    lo = max(l for l in range(0, n, group) if start[l] <= wg)
-    hi, e = min(n, lo + group), wg - start[lo]
-    for j in range(T):
-        before, here = sum(min(t, j) for t in tiles[lo:hi]), sum(t > j for t in tiles[lo:hi])
-        if before * H <= e < (before + here) * H:
-            r = e - before * H
-            return seq[[l for l in range(lo, hi) if tiles[l] > j][r // H]], r % H, j
+def place(z, h, j, nq, nk, H, T, group):
+    """The id that the device's plan gives to a tile, step by step."""
+    n, tiles = len(nq), [(k + 255) // 256 for k in nk]
+    if n > 256:                                                        # batch order
+        z0 = z - z % group
+        return z0 * H * T + (j * min(group, n - z0) + z - z0) * H + h
+    rank = [sum(nq[u] > nq[v] or (nq[u] == nq[v] and u < v) for u in range(n)) for v in range(n)]
+    ranked = [tiles[v] for v in sorted(range(n), key=lambda v: rank[v])]
+    r, lo = rank[z], rank[z] - rank[z] % group
+    if j < tiles[z]:
+        at = sum(ranked[:lo]) + sum(min(t, j) + (k < r and t > j) for k, t in list(enumerate(ranked))[lo:lo + group])
+    else:
+        at = sum(ranked) + sum(T - t for t in tiles[:z]) + j - tiles[z]
+    return at * H + h
 
 
-@pytest.mark.parametrize("seed", range(20))
-def test_mapping_is_complete_and_ordered(seed):
+@pytest.mark.parametrize("seed", range(12))
+def test_plan_is_complete_and_ordered(seed):
     rng = random.Random(seed)
-    n, H, L = rng.choice((1, 2, 5, 16, 64)), rng.choice((1, 2, 12)), rng.choice((200, 256, 300, 4096))
+    n, H, L = rng.choice((1, 2, 5, 16, 64, 260)), rng.choice((1, 2, 3)), rng.choice((200, 256, 300, 1500))
     nk = [rng.randint(0, L) for _ in range(n)]
     nq = nk if seed % 2 else [rng.randint(0, 700) for _ in range(n)]
-    T, seen, last = (L + 255) // 256, set(), {}
-    for wg in range(n * H * T):
-        z, h, j = map_work(wg, nq, nk, H, T, min(n, 1 + seed % 5))
-        seen.add((z, h, j))
-        if j * 256 < nk[z]:
-            assert last.get((z, h), -1) == j - 1                       # a tile's predecessor has a smaller id
-            last[z, h] = j
-    assert len(seen) == n * H * T
+    T, group, seen = (L + 255) // 256, min(n, 1 + seed % 5), set()
+    for z in range(n):
+        for h in range(H):
+            ids = [place(z, h, j, nq, nk, H, T, group) for j in range(T)]
+            assert ids == sorted(ids)                                  # a tile's predecessor has a smaller id
+            seen.update(ids)
+    assert seen == set(range(n * H * T))
