@@ -2,6 +2,7 @@
 // declared in include/sigmoid_attn.h.  Validation happens before any HIP call.
 #include "sigattn_kernels.hpp"
 #include "sigattn_onepass.hpp"
+#include "sigattn_pair.hpp"
 #include "sigmoid_attn.h"
 
 #include <cmath>
@@ -129,6 +130,30 @@ int launch_bwd(Params kv, Params q, hipStream_t stream) {
                    stream, kv, q, q_first, (int)(q_first ? q_tiles : kv_tiles));
 }
 
+// ---- launches that leave most of the GPU idle, d = 64 (sigattn_pair.hpp)
+
+// One workgroup of 64 rows to a CU, or other kernels: a second one on a CU takes the time that the pairs save.  Other kernels /
+// pairs, us: forward at B = 2, H = 2, N = 256 (16 workgroups) 6.7 / 5.7; B = 1, H = 12, N = 1000 (192) 15.2 / 11.3; B = 1, H = 2, N = 4096
+// (128) 47.8 / 33.1; B = 1, H = 12, N = 2048 (384) 26.3 / 28.1; B = 4, H = 16, N = 1024 (1024) 21.7 / 30.5.  Backward at B = 2, H = 2,
+// N = 256 (32) 9.2 / 7.0, N = 700 (88) 16.5 / 11.9; B = 1, H = 2, N = 4096 (256) 70.4 / 47.9; B = 2, H = 4, 200 queries, 4000 keys (536)
+// 50.5 / 35.1, but B = 1, H = 12, N = 1000 (384) 22.1 / 27.6 and B = 8, H = 4, up to 500 rows (512) 13.1 / 13.2.
+constexpr long long PAIR_WGS = 256;
+bool pair_reach(const Params &p) { return (long long)p.N_str * p.H * pair::D * 2 < (1LL << 31); }
+long long pair_tiles(const Params &p) { return ((long long)p.N + pair::BM - 1) / pair::BM * p.B * p.H; }
+
+template <int MODE>
+int launch_pair(Params p, hipStream_t stream) {
+    p.in_order = 0;
+    return enqueue(pair::sigattn_pair<MODE>, pair_tiles(p), pair::THREADS, pair::lds_bytes(MODE), stream, p);
+}
+
+int launch_pair_bwd(Params kv, Params q, hipStream_t stream) {
+    kv.in_order = q.in_order = 0;
+    const int q_first = kv.N_str < q.N_str;             // the pass whose workgroups stream more rows starts
+    return enqueue(pair::sigattn_pair_bwd, pair_tiles(kv) + pair_tiles(q), pair::THREADS, pair::lds_bytes(DKDV), stream, kv, q, q_first,
+                   (int)(q_first ? pair_tiles(q) : pair_tiles(kv)));
+}
+
 // ---- the backward pass of d = 64 in one launch over the scores (sigattn_onepass.hpp)
 
 constexpr size_t ONEPASS_LIMIT = (size_t)1 << 30;      // scratch of one launch; a larger batch goes through it in slices
@@ -233,10 +258,11 @@ static int fwd_impl(const void *q, const void *k, const void *v, void *o,
     p.B = B; p.N = L_q; p.N_str = L_k; p.H = H;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (d == 64) {
-        // Four waves of two owner blocks (256 query rows, two workgroups to a CU) feed two MFMAs from every LDS
+        // More workgroups than CUs: four waves of two owner blocks (256 query rows, two workgroups to a CU) feed two MFMAs from every LDS
         // operand read.  A grid of at most one such workgroup per CU is split finer, into 128-row tiles (B = 4,
         // H = 16, N = 1024, 256 workgroups: 19.3 against 23.0 us; B = 8, H = 12, 384 workgroups: 32.4 against
         // 30.2 us), and sequences that fit one 128-row tile take it (B = 200, H = 8, N = 100: 19.2 against 25.1 us).
+        if (pair_tiles(p) <= PAIR_WGS && pair_reach(p)) return launch_pair<FWD>(p, s);
         if (L_q <= 128 || (long long)B * H * ((L_q + 255) / 256) <= 256) return launch<FWD, 64, 1, 4, 64, 72, 72, 2, 4>(p, s);
         return launch<FWD, 64, 2, 4, 64, 72, 72, 2, 4>(p, s);
     }
@@ -287,6 +313,12 @@ static int bwd_impl(const void *q, const void *k, const void *v, const void *d_o
         // time of eight.
         // One launch for both passes: one start, and the tail of the first is filled by the second (B = 2, H = 2,
         // N = 256: 9.4 us against 9.0 + 8.0; B = 12 heads of N = 1000: 22.5 against 21.9 + 19.4; N = 8192: 1.5 % less).
+        if ((want_dkdv ? pair_tiles(pk) : 0) + (want_dq ? pair_tiles(pq) : 0) <= PAIR_WGS && pair_reach(pk) && pair_reach(pq)) {
+            if (want_dkdv && want_dq) return launch_pair_bwd(pk, pq, s);
+            if (want_dkdv) return launch_pair<DKDV>(pk, s);
+            if (want_dq) return launch_pair<DQ>(pq, s);
+            return SIGATTN_OK;
+        }
         if (want_dkdv && want_dq) return launch_bwd<64, 4, 64, 72, 2, 8, 4>(pk, pq, s);
         if (want_dkdv) return launch<DKDV, 64, 1, 4, 64, 72, 72, 2, 8>(pk, s);
         if (want_dq) return launch<DQ, 64, 1, 4, 64, 72, 72, 2, 4>(pq, s);
