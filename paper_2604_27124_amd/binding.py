@@ -30,6 +30,7 @@ EXPORTS = ("sigmoid_attn_version", "sigmoid_attn_strerror", "sigmoid_attn_fwd", 
            "sigmoid_attn_bwd_dq_dbias_static")
 
 _lib = None
+_fast = None            # the module _fastcall, or _NoFastCalls where it is not built; bound to the loaded library
 
 
 class _Torch:
@@ -45,6 +46,27 @@ class _Torch:
 torch = _Torch()
 
 
+class _NoFastCalls:
+    fwd = bwd = staticmethod(lambda *args: None)
+
+
+def _fastcalls():
+    """The plain calls in native code (csrc/fastcall.cpp): they give None for whatever is not plain."""
+    global _fast
+    lib = load()
+    if _fast is None:
+        torch.Tensor                                             # the extension needs torch's libraries
+        try:
+            from . import _fastcall as fast
+        except ImportError:
+            _fast = _NoFastCalls
+        else:
+            fast.use(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+                lib.sigmoid_attn_fwd, lib.sigmoid_attn_bwd, lib.sigmoid_attn_bwd_onepass_workspace_bytes)))
+            _fast = fast
+    return _fast
+
+
 class SigAttnError(RuntimeError):
     def __init__(self, code: int):
         self.code = code
@@ -53,8 +75,9 @@ class SigAttnError(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """The loaded C library (raises if it has not been built)."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
+        _fast = None
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2604_27124_amd.build` "
                                "(there is no fallback path)")
@@ -110,9 +133,9 @@ def sigmoid_attn_bwd_onepass_workspace_bytes(B: int, N_max: int, H: int, d: int)
     return int(load().sigmoid_attn_bwd_onepass_workspace_bytes(B, N_max, H, d))
 
 
-# The marshalling of a call is most of what a small problem costs (two 256-token sequences: 28 us of host work
-# around 15 us of kernels for forward + backward, 19 us of both now), so shapes are compared as they come, the stream's
-# handle is taken without a Stream object (0.3 against 3.0 us) and outputs allocated here are not checked again.
+# The marshalling of a call is most of what a small problem costs, so the plain forms of the two calls of a training step
+# are made in native code, shapes are compared as they come, the stream's handle is taken without a Stream object (0.3
+# against 3.0 us) and outputs allocated here are not checked again.
 def _check(t, name: str, shape=None):
     if not (t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous() and t.dim() == 4):
         raise ValueError(f"{name} must be a contiguous CUDA bf16 tensor of shape [B, N_max, H, d]")
@@ -156,6 +179,10 @@ def _scratch(nbytes: int, like, stream):
 
 def sigmoid_attn_fwd(q, k, v, seqlens, bias, scale: float, out=None, stream=None):
     """O = sigmoid(scale * Q K^T + bias) V over valid tokens; returns `out` (allocated if None)."""
+    if out is None and stream is None:
+        res = (_fast or _fastcalls()).fwd(q, k, v, seqlens, bias, scale)
+        if res is not None:
+            return res
     _check(q, "q")
     _check(k, "k", q.shape)
     _check(v, "v", q.shape)
@@ -174,6 +201,10 @@ def sigmoid_attn_bwd(q, k, v, d_o, seqlens, bias, scale: float, dq=None, dk=None
                      stream=None) -> Tuple:
     """(dQ, dK, dV) from the forward inputs and dO; outputs and workspace are allocated if None (the workspace for the
     length of the call, where the shape is computed in one pass)."""
+    if dq is None and dk is None and dv is None and workspace is None and stream is None:
+        res = (_fast or _fastcalls()).bwd(q, k, v, d_o, seqlens, bias, scale)
+        if res is not None:
+            return res
     _check(q, "q")
     shape = q.shape
     _check(k, "k", shape)

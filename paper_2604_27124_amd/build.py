@@ -13,6 +13,8 @@ SOURCES = ["sigattn_api.hip"]
 PROBE_LIB = os.path.join(HERE, "libmachine_probes.so")  # measurement aids for the benchmark, a library of their own
 PROBE_SOURCES = ["machine_probes.hip"]
 
+FASTCALL = os.path.join(HERE, "_fastcall.so")            # the binding's plain calls in native code (host only)
+
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # packed-fp32 VALU forms are switched off for every device function of this library
@@ -40,8 +42,30 @@ def _compile(lib: str, sources, verbose: bool) -> str:
     return lib
 
 
+def _compile_fastcall(verbose: bool) -> None:
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(hipcc()))), "include"),
+           "-o", FASTCALL, os.path.join(CSRC, "fastcall.cpp"),
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if verbose or res.returncode != 0:
+        print(" ".join(cmd))
+        print(res.stdout)
+        print(res.stderr)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed building _fastcall.so")
+
+
 def build_library(verbose: bool = False) -> str:
-    """libsigattn.so (the method) and libmachine_probes.so (the benchmark's measurement aids)."""
+    """libsigattn.so (the method), _fastcall.so (its plain calls from torch) and libmachine_probes.so (the benchmark's
+    measurement aids)."""
+    _compile_fastcall(verbose)
     _compile(PROBE_LIB, PROBE_SOURCES, verbose)
     return _compile(LIB, SOURCES, verbose)
 

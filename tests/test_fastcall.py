@@ -1,0 +1,43 @@
+"""The binding's plain calls in native code: what is not plain goes the Python way, and both ways give the same."""
+import pytest
+import torch
+
+from paper_2604_27124_amd import binding as A
+
+
+def test_what_is_not_plain_is_left_to_python():
+    fast = A._fastcalls()
+    assert fast.__name__.endswith("_fastcall")                        # built, and bound to the loaded library
+    x, n, b = torch.zeros(1, 8, 1, 64, dtype=torch.bfloat16), torch.zeros(1, dtype=torch.int32), torch.zeros(1)
+    for args in ((x, x, x, n, b, 0.125), (x, x, x, n, b), (1, 2, 3, 4, 5, 6.0), (None,) * 6):
+        assert fast.fwd(*args) is None and fast.bwd(args[0], *args) is None
+    with pytest.raises(ValueError):
+        A.sigmoid_attn_fwd(x, x, x, n, b, 0.125)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,N,H,d", [(2, 256, 2, 64), (16, 1030, 12, 64), (3, 200, 2, 128)])      # pairs; one pass; d = 128
+def test_same_results_as_the_python_way(B, N, H, d):
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v, g = (torch.empty(B, N, H, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in range(4))
+    n, b = torch.tensor([N - 3 * i for i in range(B)], dtype=torch.int32, device="cuda"), torch.full((B,), -5.0, device="cuda")
+    stream = torch.cuda.current_stream()
+    assert A._fastcalls().fwd(q, k, v, n, b, 0.125) is not None
+    plain = (A.sigmoid_attn_fwd(q, k, v, n, b, 0.125), *A.sigmoid_attn_bwd(q, k, v, g, n, b, 0.125))
+    other = (A.sigmoid_attn_fwd(q, k, v, n, b, 0.125, stream=stream), *A.sigmoid_attn_bwd(q, k, v, g, n, b, 0.125, stream=stream))
+    for x, y in zip(plain, other):
+        assert x.is_contiguous() and not x.requires_grad and torch.equal(x.view(torch.int16), y.view(torch.int16))
+    # refused as before: shape, layout, type, a lengths tensor of another kind, an argument the library refuses
+    for bad in ((q, k[:, :-1], v, n, b, 0.125), (q, k, v.transpose(1, 2).contiguous().transpose(1, 2), n, b, 0.125),
+                (q.float(), k, v, n, b, 0.125), (q, k, v, n.long(), b, 0.125), (q, k, v, n, b[:-1], 0.125)):
+        with pytest.raises(ValueError):
+            A.sigmoid_attn_fwd(*bad)
+    with pytest.raises(A.SigAttnError):
+        A.sigmoid_attn_fwd(q, k, v, n, b, float("nan"))
+    with pytest.raises(RuntimeError):                                  # a wrapped tensor has no memory to give
+        torch.vmap(lambda t: A.sigmoid_attn_fwd(t, k, v, n, b, 0.125))(q[None])
+    with torch.cuda.stream(torch.cuda.Stream()) as _:                  # the current stream, whichever it is
+        torch.cuda.current_stream().wait_stream(stream)
+        side = A.sigmoid_attn_fwd(q, k, v, n, b, 0.125)
+    torch.cuda.synchronize()
+    assert torch.equal(side.view(torch.int16), plain[0].view(torch.int16))
