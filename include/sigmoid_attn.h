@@ -170,7 +170,7 @@ int sigmoid_attn_bwd_dq_dbias_static(const void *q, const void *k, const void *v
 size_t sigmoid_attn_bwd_workspace_bytes(int B, int N_max, int H, int d);
 
 /* Scratch bytes with which sigmoid_attn_bwd computes the scores once (0: this shape always takes two passes, and on
- * invalid shapes).  At most 1 GiB: a larger batch goes through it in slices. */
+ * invalid shapes).  At most 512 MiB: a larger batch goes through it in slices. */
 size_t sigmoid_attn_bwd_onepass_workspace_bytes(int B, int N_max, int H, int d);
 
 #ifdef __cplusplus

@@ -135,11 +135,22 @@ int launch_bwd(Params kv, Params q, hipStream_t stream) {
 // One workgroup of 64 rows to a CU, or other kernels: a second one on a CU takes the time that the pairs save.  Other kernels /
 // pairs, us: forward at B = 2, H = 2, N = 256 (16 workgroups) 6.7 / 5.7; B = 1, H = 12, N = 1000 (192) 15.2 / 11.3; B = 1, H = 2, N = 4096
 // (128) 47.8 / 33.1; B = 1, H = 12, N = 2048 (384) 26.3 / 28.1; B = 4, H = 16, N = 1024 (1024) 21.7 / 30.5.  Backward at B = 2, H = 2,
-// N = 256 (32) 9.2 / 7.0, N = 700 (88) 16.5 / 11.9; B = 1, H = 2, N = 4096 (256) 70.4 / 47.9; B = 2, H = 4, 200 queries, 4000 keys (536)
-// 50.5 / 35.1, but B = 1, H = 12, N = 1000 (384) 22.1 / 27.6 and B = 8, H = 4, up to 500 rows (512) 13.1 / 13.2.
+// N = 256 (32) 9.2 / 7.0, N = 700 (88) 16.5 / 11.9; B = 1, H = 2, N = 4096 (256) 70.4 / 47.9; B = 2, H = 4, 200 queries, 4000 keys (32 of 63
+// steps, 504 of four) 50.5 / 35.1, but B = 1, H = 12, N = 1000 (384) 22.1 / 27.6 and B = 8, H = 4, up to 500 rows (512) 13.1 / 13.2.
 constexpr long long PAIR_WGS = 256;
-bool pair_reach(const Params &p) { return (long long)p.N_str * p.H * pair::D * 2 < (1LL << 31); }
+// What the kernels can take: a head's streamed rows under one descriptor, a ranking that has a class for every tile count.
+bool pair_reach(const Params &p) {
+    return (long long)p.N_str * p.H * pair::D * 2 < (1LL << 31) && (p.B <= MAP_WAVE_B || (p.N + pair::BM - 1) / pair::BM <= MAP_CLASSES);
+}
 long long pair_tiles(const Params &p) { return ((long long)p.N + pair::BM - 1) / pair::BM * p.B * p.H; }
+long long pair_steps(const Params &p) { return ((long long)p.N_str + pair::BN - 1) / pair::BN; }                 // of one workgroup
+
+// The workgroups that the longest ones leave room for: all of a pass, or of both, in units of the longest.
+long long pair_load(const Params &p) { return pair_tiles(p); }
+long long pair_load(const Params &a, const Params &b) {
+    const long long sa = pair_steps(a), sb = pair_steps(b), most = sa > sb ? sa : sb;
+    return (pair_tiles(a) * sa + pair_tiles(b) * sb + most - 1) / most;
+}
 
 template <int MODE>
 int launch_pair(Params p, hipStream_t stream) {
@@ -156,7 +167,7 @@ int launch_pair_bwd(Params kv, Params q, hipStream_t stream) {
 
 // ---- the backward pass of d = 64 in one launch over the scores (sigattn_onepass.hpp)
 
-constexpr size_t ONEPASS_LIMIT = (size_t)1 << 30;      // scratch of one launch; a larger batch goes through it in slices
+constexpr size_t ONEPASS_LIMIT = (size_t)1 << 29;      // scratch of one launch; a larger batch goes through it in slices
 
 size_t onepass_bytes(int B, int N, int H) {            // sums of dQ in fp32, whole tiles; plan and counts of the workgroups
     const size_t heads = (size_t)B * H, tiles = ((size_t)N + onepass::BM - 1) / onepass::BM;
@@ -167,13 +178,14 @@ size_t onepass_bytes(int B, int N, int H) {            // sums of dQ in fp32, wh
 // Sequences of one launch; 0: this shape takes two passes.  One pass does five contractions for seven, but in half as many
 // workgroups of twice the keys, one to a CU, each of which follows the one before it in its head: it needs three rounds of
 // them (768) and heads long enough that 256-row tiles round little.  One pass / two, us, H = 12, all rows valid, lengths from
-// an eighth of N on, lognormal: N = 700, B = 43 (1548 tiles) 260 / 287, 139 / 149, 120 / 127; N = 1024, B = 66 676 / 821, 361 / 415,
-// 274 / 317; N = 2048, B = 60 2187 / 2783, 894 / 1082, 831 / 1012; B = 8, N = 2048 (768 tiles) 288 / 363.  Below: N = 512, B = 86
-// (2064) 278 / 309, 166 / 160, 143 / 133; B = 4, N = 2048 (384) 172 / 189, from a quarter on 151 / 155; B = 8, N = 1024 (384)
-// 93 / 105, 63 / 55; B = 1, N = 1024 (48) 56 / 24.
+// an eighth of N on, lognormal: N = 512, B = 40 (960 tiles) 124 / 141, 63 / 70, 57 / 66; B = 86 268 / 315, 149 / 150, 127 / 136; N = 700,
+// B = 43 247 / 293, 126 / 142, 103 / 126; N = 1024, B = 66 671 / 833, 351 / 423, 265 / 319; N = 2048, B = 9 (864) 368 / 423, 148 / 153,
+// 162 / 174; B = 60 2246 / 2838, 892 / 1115, 842 / 1038.  Not below: N = 384, B = 86 (2064) 185 / 189, 106 / 96, 89 / 80; N = 300,
+// B = 256, H = 16 567 / 589, 302 / 296, 288 / 259; B = 4, N = 2048 (384 tiles) 172 / 189, from a quarter on 151 / 155; B = 8,
+// N = 1024 (384) 93 / 105, 63 / 55; B = 1, N = 1024 (48) 56 / 24.
 int onepass_sequences(int B, int N, int H, int d) {
     const long long tiles = ((long long)N + onepass::BM - 1) / onepass::BM;
-    if (d != 64 || N < 640 || B * (H * tiles) < 768) return 0;
+    if (d != 64 || N <= 448 || B * (H * tiles) < 768) return 0;
     const size_t one = onepass_bytes(1, N, H);
     if (one > ONEPASS_LIMIT) return 0;
     const long long most = (long long)(ONEPASS_LIMIT / one), slices = (B + most - 1) / most;
@@ -262,7 +274,7 @@ static int fwd_impl(const void *q, const void *k, const void *v, void *o,
         // operand read.  A grid of at most one such workgroup per CU is split finer, into 128-row tiles (B = 4,
         // H = 16, N = 1024, 256 workgroups: 19.3 against 23.0 us; B = 8, H = 12, 384 workgroups: 32.4 against
         // 30.2 us), and sequences that fit one 128-row tile take it (B = 200, H = 8, N = 100: 19.2 against 25.1 us).
-        if (pair_tiles(p) <= PAIR_WGS && pair_reach(p)) return launch_pair<FWD>(p, s);
+        if (pair_load(p) <= PAIR_WGS && pair_reach(p)) return launch_pair<FWD>(p, s);
         if (L_q <= 128 || (long long)B * H * ((L_q + 255) / 256) <= 256) return launch<FWD, 64, 1, 4, 64, 72, 72, 2, 4>(p, s);
         return launch<FWD, 64, 2, 4, 64, 72, 72, 2, 4>(p, s);
     }
@@ -313,11 +325,10 @@ static int bwd_impl(const void *q, const void *k, const void *v, const void *d_o
         // time of eight.
         // One launch for both passes: one start, and the tail of the first is filled by the second (B = 2, H = 2,
         // N = 256: 9.4 us against 9.0 + 8.0; B = 12 heads of N = 1000: 22.5 against 21.9 + 19.4; N = 8192: 1.5 % less).
-        if ((want_dkdv ? pair_tiles(pk) : 0) + (want_dq ? pair_tiles(pq) : 0) <= PAIR_WGS && pair_reach(pk) && pair_reach(pq)) {
-            if (want_dkdv && want_dq) return launch_pair_bwd(pk, pq, s);
-            if (want_dkdv) return launch_pair<DKDV>(pk, s);
-            if (want_dq) return launch_pair<DQ>(pq, s);
-            return SIGATTN_OK;
+        if (pair_reach(pk) && pair_reach(pq)) {
+            if (want_dkdv && want_dq && pair_load(pk, pq) <= PAIR_WGS) return launch_pair_bwd(pk, pq, s);
+            if (want_dkdv && !want_dq && pair_load(pk) <= PAIR_WGS) return launch_pair<DKDV>(pk, s);
+            if (want_dq && !want_dkdv && pair_load(pq) <= PAIR_WGS) return launch_pair<DQ>(pq, s);
         }
         if (want_dkdv && want_dq) return launch_bwd<64, 4, 64, 72, 2, 8, 4>(pk, pq, s);
         if (want_dkdv) return launch<DKDV, 64, 1, 4, 64, 72, 72, 2, 8>(pk, s);

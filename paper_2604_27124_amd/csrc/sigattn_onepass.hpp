@@ -509,41 +509,76 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
         }
     };
     const bool on = ((L - 1) & 1) == grp;                            // at the last tile
-    int slot_rt = 0;
-    if (L > 0) {
-        step(F_{}, T_{}, F_{}, IntC<0>{}, IntC<0>{}, IntC<0>{}, T_{}, 1);
-        barrier();
-        load_tile();
-        step(T_{}, T_{}, F_{}, IntC<1>{}, IntC<0>{}, IntC<0>{}, F_{}, 0);
-        int t = 1, state = grp ? 3 : 0;
-        while (t < L) {
-            if (state == 0) { tile_body(IntC<1>{}, T_{}, t); state = 1; ++t; }
-            if (t < L && state == 1) { tile_body(IntC<2>{}, F_{}, t); state = 2; ++t; }
-            if (t < L && state == 2) { tile_body(IntC<0>{}, T_{}, t); state = 3; ++t; }
-            if (t < L && state == 3) { tile_body(IntC<1>{}, F_{}, t); state = 4; ++t; }
-            if (t < L && state == 4) { tile_body(IntC<2>{}, T_{}, t); state = 5; ++t; }
-            if (t < L && state == 5) { tile_body(IntC<0>{}, F_{}, t); state = 0; ++t; }
+    // A wave whose keys are all behind the end moves its share of the tiles and makes its blocks of dQ, and nothing else: the
+    // SIMD's other wave has the time (32 x 32 heads of 384 rows 201 -> 185 us; 43 x 12 of up to 700, lognormal 120 -> 103; 86 x 12 of up to
+    // 1024 300 -> 288).
+    if (m0 + wave * 32 >= nk) {
+        for (int t = 0; t < L; ++t) {
+            const bool mine = t > 0 && ((t - 1) & 1) == grp;         // dQ of tile t - 1, else (from tile 2 on) of t - 2
+            if (mine) dq_begin(t - 1);
+            else if (t >= 2) dq_bulk(IntC<8>{}, IntC<16>{});
+            store_tile((t + 1) % RING_TILES);
+            barrier();
+            load_tile();
+            if (mine) {
+                dq_bulk(IntC<0>{}, IntC<8>{});
+            } else if (t > 0) {
+                dq_look();
+                if (t >= 2) {
+                    dq_end(t - 2);
+                    dq_flag(t - 2);
+                }
+            }
         }
-        slot_rt = L % RING_TILES;
-        if (on) {
-            dq_begin(L - 1);
-        }
-        step(T_{}, T_{}, F_{}, IntC<0>{}, DynInt{slot_rt}, IntC<0>{}, F_{}, 0);
+        if (L > 0 && on) dq_begin(L - 1);
         if (!on && L >= 2) dq_bulk(IntC<8>{}, IntC<16>{});
+        barrier();
+        if (!on && L >= 2) {
+            dq_end(L - 2);
+            dq_flag(L - 2);
+        }
+        if (on && L > 0) {
+            dq_bulk(IntC<0>{}, IntC<16>{});
+            dq_end(L - 1);
+        }
+        if (!on) dq_begin(L);
     } else {
-        step(F_{}, T_{}, F_{}, IntC<0>{}, DynInt{0}, IntC<0>{}, F_{}, 0);
+        int slot_rt = 0;
+        if (L > 0) {
+            step(F_{}, T_{}, F_{}, IntC<0>{}, IntC<0>{}, IntC<0>{}, T_{}, 1);
+            barrier();
+            load_tile();
+            step(T_{}, T_{}, F_{}, IntC<1>{}, IntC<0>{}, IntC<0>{}, F_{}, 0);
+            int t = 1, state = grp ? 3 : 0;
+            while (t < L) {
+                if (state == 0) { tile_body(IntC<1>{}, T_{}, t); state = 1; ++t; }
+                if (t < L && state == 1) { tile_body(IntC<2>{}, F_{}, t); state = 2; ++t; }
+                if (t < L && state == 2) { tile_body(IntC<0>{}, T_{}, t); state = 3; ++t; }
+                if (t < L && state == 3) { tile_body(IntC<1>{}, F_{}, t); state = 4; ++t; }
+                if (t < L && state == 4) { tile_body(IntC<2>{}, T_{}, t); state = 5; ++t; }
+                if (t < L && state == 5) { tile_body(IntC<0>{}, F_{}, t); state = 0; ++t; }
+            }
+            slot_rt = L % RING_TILES;
+            if (on) {
+                dq_begin(L - 1);
+            }
+            step(T_{}, T_{}, F_{}, IntC<0>{}, DynInt{slot_rt}, IntC<0>{}, F_{}, 0);
+            if (!on && L >= 2) dq_bulk(IntC<8>{}, IntC<16>{});
+        } else {
+            step(F_{}, T_{}, F_{}, IntC<0>{}, DynInt{0}, IntC<0>{}, F_{}, 0);
+        }
+        if (tail < BN) mask_block(IntC<0>{});
+        barrier();
+        if (L > 0) dsw += fl;
+        if (!on && L >= 2) dq_end(L - 2);
+        step(T_{}, F_{}, F_{}, IntC<1>{}, DynInt{slot_rt}, IntC<0>{}, F_{}, 0);
+        if (tail < BN) mask_block(IntC<1>{});
+        if (!on && L >= 2) dq_flag(L - 2);
+        if (on && L > 0) dq_bulk(IntC<0>{}, IntC<16>{});
+        step(T_{}, F_{}, T_{}, IntC<0>{}, DynInt{(slot_rt + 1) % RING_TILES}, IntC<0>{}, F_{}, 0);
+        if (on && L > 0) dq_end(L - 1);
+        if (!on) dq_begin(L);
     }
-    if (tail < BN) mask_block(IntC<0>{});
-    barrier();
-    if (L > 0) dsw += fl;
-    if (!on && L >= 2) dq_end(L - 2);
-    step(T_{}, F_{}, F_{}, IntC<1>{}, DynInt{slot_rt}, IntC<0>{}, F_{}, 0);
-    if (tail < BN) mask_block(IntC<1>{});
-    if (!on && L >= 2) dq_flag(L - 2);
-    if (on && L > 0) dq_bulk(IntC<0>{}, IntC<16>{});
-    step(T_{}, F_{}, T_{}, IntC<0>{}, DynInt{(slot_rt + 1) % RING_TILES}, IntC<0>{}, F_{}, 0);
-    if (on && L > 0) dq_end(L - 1);
-    if (!on) dq_begin(L);
     barrier();
     if (on) {
         if (L > 0) dq_flag(L - 1);

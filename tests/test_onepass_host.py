@@ -17,9 +17,9 @@ def test_workspace_size():
     f = A.sigmoid_attn_bwd_onepass_workspace_bytes
     assert f(4, 8192, 12, 64) == 48 * (128 * 64 * 64 * 4 + 32 * (8 * 4 + 32))
     assert f(8, 2048, 12, 64) > 0 and f(7, 2048, 12, 64) == 0          # 768 tiles of 256 keys
-    assert f(16, 1024, 12, 64) > 0 and f(64, 639, 12, 64) == 0
+    assert f(32, 449, 12, 64) > 0 and f(500, 448, 12, 64) == 0
     assert f(4, 8192, 12, 128) == 0 and f(0, 8192, 12, 64) == 0
-    assert 0 < f(1000, 4096, 16, 64) <= 1 << 30                        # in slices
+    assert 0 < f(1000, 4096, 16, 64) <= 1 << 29                        # in slices
     assert f(1, 1100, 16384, 64) == 0                                  # one sequence that no slice can hold
 
 
@@ -51,12 +51,10 @@ def test_compiled_kernels(assembly, kernel):
         assert re.match(r"s_waitcnt .*lgkmcnt\(0\)", body[j]), body[j:i + 1]
     if "onepass" not in kernel:
         return
-    counts = [i for i, l in enumerate(body) if l.startswith("global_store_dword ")]
-    assert counts
-    for i in counts:
-        assert body[i].endswith("sc1")
-        sums = max(j for j in range(i) if body[j].startswith("buffer_store"))
-        assert "s_waitcnt vmcnt(0)" in body[sums:i], body[sums:i]
+    counts = [l for l in body if l.startswith("global_store_dword ")]
+    waits = re.findall(r"ASMSTART\n\ts_waitcnt vmcnt\(0\)\n", text[:end])   # of dq_flag, one per place it stands at
+    assert counts and all(l.endswith("sc1") for l in counts) and len(waits) >= len(counts)
+    assert sum(l.startswith("buffer_store_dwordx4") and l.endswith("sc1") for l in body) >= 4 * len(counts)
 
 
 def place(z, h, j, nq, nk, H, T, group):
