@@ -165,6 +165,34 @@ int launch_pair_bwd(Params kv, Params q, hipStream_t stream) {
                    (int)(q_first ? pair_tiles(q) : pair_tiles(kv)));
 }
 
+// ---- the same for d = 128: half the rows to a workgroup
+
+// A workgroup to a CU (two rounds of them for both backward passes, whose other form is two launches).  Eight waves and 256
+// rows / four and 128, us: forward at B = 2, H = 16, N = 1000 (256 workgroups of 128 rows) 28.2 / 23.5; N = 2048 (512) 63.2 / 80.3; B = 1,
+// H = 16, N = 4096 (512) 117 / 148.  Backward at B = 1, H = 16, N = 1024 (256 of both passes) 72.5 / 36.3; B = 2, H = 16, N = 1000 (512) 76.9 /
+// 66.1, with two launches 69.3; B = 4, H = 16, N = 512 (512) 48.2 / 41.9, 44.3; B = 8, H = 16, N = 512 (1024) 78.5 / 85.5.
+constexpr long long HALF_WGS = 256, HALF_BWD_WGS = 512;
+
+long long half_tiles(const Params &p) { return ((long long)p.N + 32 * half128::NW - 1) / (32 * half128::NW) * p.B * p.H; }
+bool half_ranks(const Params &p) { return p.B <= MAP_WAVE_B || (p.N + 32 * half128::NW - 1) / (32 * half128::NW) <= MAP_CLASSES; }
+bool half_fits(const Params &p) { return half_tiles(p) <= HALF_WGS && half_ranks(p); }
+
+template <int MODE, int LD1, int LD2, int OCC>
+int launch_half(Params p, hipStream_t stream) {
+    using C = Cfg<MODE, 128, 1, half128::NW, 64, LD1, LD2, 4>;
+    static_assert(C::BM == 32 * half128::NW, "tile height");
+    p.in_order = 0;
+    return enqueue(half128::sigattn_half<MODE, LD1, LD2, OCC>, half_tiles(p), C::THREADS, C::LDS_BYTES, stream, p);
+}
+
+int launch_half_bwd(Params kv, Params q, hipStream_t stream) {
+    constexpr size_t lds_kv = Cfg<DKDV, 128, 1, half128::NW, 64, 144, 144, 4>::LDS_BYTES, lds_q = Cfg<DQ, 128, 1, half128::NW, 64, 144, 136, 4>::LDS_BYTES;
+    kv.in_order = q.in_order = 0;
+    const int q_first = kv.N_str < q.N_str;             // the pass whose workgroups stream more rows starts
+    return enqueue(half128::sigattn_half_bwd, half_tiles(kv) + half_tiles(q), half128::NW * 64, lds_kv > lds_q ? lds_kv : lds_q, stream, kv, q,
+                   q_first, (int)(q_first ? half_tiles(q) : half_tiles(kv)));
+}
+
 // ---- the backward pass of d = 64 in one launch over the scores (sigattn_onepass.hpp)
 
 constexpr size_t ONEPASS_LIMIT = (size_t)1 << 29;      // scratch of one launch; a larger batch goes through it in slices
@@ -280,6 +308,7 @@ static int fwd_impl(const void *q, const void *k, const void *v, void *o,
     }
     // d = 128: K is only read row-wise (272-byte rows), V only through the transposing reads, which at that
     // stride ran at a quarter of their rate; 288-byte rows with the split column layout are conflict-free.
+    if (half_fits(p)) return launch_half<FWD, 136, 144, half128::OCC_FWD>(p, s);
     return launch<FWD, 128, 1, 8, 64, 136, 144, 1, 4>(p, s);
 }
 
@@ -335,6 +364,8 @@ static int bwd_impl(const void *q, const void *k, const void *v, const void *d_o
         if (want_dq) return launch<DQ, 64, 1, 4, 64, 72, 72, 2, 4>(pq, s);
         return SIGATTN_OK;
     }
+    if (want_dkdv && want_dq && half_tiles(pk) + half_tiles(pq) <= HALF_BWD_WGS && half_ranks(pk) && half_ranks(pq))
+        return launch_half_bwd(pk, pq, s);
     if (want_dkdv) {
         // d = 128: the fp32 accumulators of dK and dV (128 registers) fit only with the whole register file of a
         // SIMD for one wave, so four waves of 32 keys, one per SIMD (both streamed tensors are read row-wise and
@@ -342,6 +373,7 @@ static int bwd_impl(const void *q, const void *k, const void *v, const void *d_o
         const int e = launch<DKDV, 128, 1, 4, 64, 144, 144, 1, 4>(pk, s);
         if (e) return e;
     }
+    if (want_dq && half_fits(pq)) return launch_half<DQ, 144, 136, half128::OCC_BWD>(pq, s);
     if (want_dq) return launch<DQ, 128, 1, 8, 64, 144, 136, 1, 4>(pq, s);
     return SIGATTN_OK;
 }

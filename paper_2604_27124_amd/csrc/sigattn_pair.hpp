@@ -323,4 +323,34 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_pair_bwd(const Params kv, 
 }
 
 }  // namespace pair
+
+// d = 128, launches of at most a workgroup to a CU: forward and dQ passes of sigattn_kernel with four waves and 128 owner rows
+// instead of eight and 256, so that each wave has a SIMD of its own, and the backward pass as one launch (dK/dV has 128
+// owner rows there too), so that its halves run beside each other and not one after the other.  The bits are the same.
+// us: forward of 8 heads of 1000 rows 26.8 -> 22.0, of 2 x 2 of 256 11.8 -> 9.4; backward 71.4 -> 33.8 and 29.4 -> 13.8 (with dQ in smaller
+// workgroups but a launch of its own 61.7 and 25.2).
+namespace half128 {
+
+constexpr int NW = 4, OCC_FWD = 2, OCC_BWD = 1;      // with 256 registers the dQ pass spills 121
+
+template <int MODE, int LD1, int LD2, int OCC>
+__global__ void __launch_bounds__(NW * 64, OCC) sigattn_half(const Params p) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ MapScratch scratch;
+    using C = Cfg<MODE, 128, 1, NW, 64, LD1, LD2, 4>;
+    sigattn::run_pass<MODE, 128, 1, NW, 64, LD1, LD2, 4, false>(p, map_work<C::BM, C::THREADS>(p, blockIdx.x, scratch), smem, nullptr);
+}
+
+__global__ void __launch_bounds__(NW * 64, OCC_BWD) sigattn_half_bwd(const Params kv, const Params q, const int q_first, const int first_tiles) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ MapScratch scratch;
+    const int id = blockIdx.x;
+    const bool is_kv = (id < first_tiles) != (q_first != 0);
+    const int rest = id < first_tiles ? id : id - first_tiles;
+    constexpr int BM = NW * 32, THREADS = NW * 64;
+    if (is_kv) sigattn::run_pass<DKDV, 128, 1, NW, 64, 144, 144, 4, false>(kv, map_work<BM, THREADS>(kv, rest, scratch), smem, nullptr);
+    else sigattn::run_pass<DQ, 128, 1, NW, 64, 144, 136, 4, false>(q, map_work<BM, THREADS>(q, rest, scratch), smem, nullptr);
+}
+
+}  // namespace half128
 }  // namespace sigattn

@@ -1,4 +1,4 @@
-"""Small launches of d = 64, in which two waves share 32 owner rows, against the kernels of larger launches: the same
+"""Small launches (d = 64: two waves share 32 owner rows; d = 128: four waves a workgroup, one backward launch) against the kernels of larger launches: the same
 sequences with others beside them in the batch.  Every sum has the same order, so the bits are the same."""
 import numpy as np
 import pytest
@@ -17,10 +17,11 @@ pytestmark = pytest.mark.gpu
     ((300, 0), (257, 300), 300, 320),      # five and a row; a sequence without queries
     ((100, 37), (0, 1000), 100, 1000),     # without keys; sixteen tiles against two
 ])
-def test_same_bits_as_larger_launches(nq, nk, Lq, Lk):
-    H, copies = 2, 256                     # at least 512 tiles of 64 rows with the copies, at most 64 without
+@pytest.mark.parametrize("d", [64, 128])
+def test_same_bits_as_larger_launches(nq, nk, Lq, Lk, d):
+    H, copies = 2, 512                     # more than 1024 tiles with the copies, at most 64 without
     gen = torch.Generator(device="cuda").manual_seed(Lq * Lk)
-    normal = lambda n: torch.empty(2, n, H, 64, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    normal = lambda n: torch.empty(2, n, H, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
     q, k, v, g = normal(Lq), normal(Lk), normal(Lk), normal(Lq)
     sq, sk = (torch.tensor(n, dtype=torch.int32, device="cuda") for n in (nq, nk))
     q[1, 0, 1, 3] = float("inf")           # saturates one row's scores; may not reach others

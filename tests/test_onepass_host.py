@@ -33,17 +33,22 @@ def assembly(tmp_path_factory):
 
 
 @pytest.mark.parametrize("kernel", ["7onepass15sigattn_onepassE", "4pair12sigattn_pairILi0E", "4pair12sigattn_pairILi1E",
-                                    "4pair12sigattn_pairILi2E", "4pair16sigattn_pair_bwdE"])
+                                    "4pair12sigattn_pairILi2E", "4pair16sigattn_pair_bwdE", "7half12812sigattn_halfILi0E",
+                                    "7half12812sigattn_halfILi1E", "7half12816sigattn_half_bwdE"])
 def test_compiled_kernels(assembly, kernel):
-    """No spills and two waves a SIMD; every barrier waits for all LDS work.  One pass: the sums between workgroups are
+    """No spills, and two waves a SIMD where one is not all there is; in the kernels with loops of their own every barrier
+    waits for all LDS work (those of d = 128 run the loop that the other tests look at).  One pass: the sums between workgroups are
     stored and read at agent scope, and each count follows a full wait for them."""
     text = assembly[re.search(rf"^_ZN7sigattn{kernel}\w+:", assembly, re.M).start():]
     end = text.index(".Lfunc_end")
     meta = dict(re.findall(r"^; (NumVgprs|ScratchSize|Occupancy): (\d+)", text[end:end + 6000], re.M)[:3])
-    assert meta["ScratchSize"] == "0" and meta["Occupancy"] == "2"
+    alone = kernel.endswith(("halfILi1E", "half_bwdE"))                # one wave a SIMD with all its registers
+    assert meta["ScratchSize"] == "0" and meta["Occupancy"] == ("1" if alone else "2")
     body = [l.split(";")[0].strip() for l in text[:end].split("\n")]
     body = [l for l in body if l and not l.startswith(".")]
     assert not any(re.match(r"v_pk_(add|mul|fma)_f32", l) for l in body)
+    if "half" in kernel:
+        return
     barriers = [i for i, l in enumerate(body) if l == "s_barrier"]
     assert len(barriers) >= 10
     for i in barriers:                                                 # the wait may stand a few plain instructions before
