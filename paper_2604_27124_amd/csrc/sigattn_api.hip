@@ -312,10 +312,11 @@ static int fwd_impl(const void *q, const void *k, const void *v, void *o,
     return launch<FWD, 128, 1, 8, 64, 136, 144, 1, 4>(p, s);
 }
 
-static int bwd_impl(const void *q, const void *k, const void *v, const void *d_o,
-                    void *dq, void *dk, void *dv,
-                    const int32_t *seqlens_q, const int32_t *seqlens_k, const float *bias, float scale,
-                    int B, int L_q, int L_k, int H, int d, void *stream, bool want_dq, bool want_dkdv) {
+// Everything a backward call can be refused for; every way of making the call asks here first.
+static int check_bwd(const void *q, const void *k, const void *v, const void *d_o,
+                     const void *dq, const void *dk, const void *dv,
+                     const int32_t *seqlens_q, const int32_t *seqlens_k, const float *bias, float scale,
+                     int B, int L_q, int L_k, int H, int d, bool want_dq, bool want_dkdv) {
     if (!q || !k || !v || !d_o || !seqlens_q || !seqlens_k || !bias || !std::isfinite(scale)) return SIGATTN_ERR_INVALID_ARG;
     if ((want_dq && !dq) || (want_dkdv && (!dk || !dv))) return SIGATTN_ERR_INVALID_ARG;
     if (int e = check_shape(B, L_q, H, d)) return e;
@@ -323,6 +324,14 @@ static int bwd_impl(const void *q, const void *k, const void *v, const void *d_o
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(d_o)) return SIGATTN_ERR_MISALIGNED;
     if ((want_dq && !aligned16(dq)) || (want_dkdv && (!aligned16(dk) || !aligned16(dv))))
         return SIGATTN_ERR_MISALIGNED;
+    return SIGATTN_OK;
+}
+
+static int bwd_impl(const void *q, const void *k, const void *v, const void *d_o,
+                    void *dq, void *dk, void *dv,
+                    const int32_t *seqlens_q, const int32_t *seqlens_k, const float *bias, float scale,
+                    int B, int L_q, int L_k, int H, int d, void *stream, bool want_dq, bool want_dkdv) {
+    if (int e = check_bwd(q, k, v, d_o, dq, dk, dv, seqlens_q, seqlens_k, bias, scale, B, L_q, L_k, H, d, want_dq, want_dkdv)) return e;
 
     Params p{};
     p.q = static_cast<const bf16_t *>(q);
@@ -389,9 +398,8 @@ int sigmoid_attn_bwd(const void *q, const void *k, const void *v, const void *d_
                      const int32_t *seqlens, const float *bias, float scale,
                      int B, int N_max, int H, int d,
                      void *workspace, size_t workspace_bytes, void *stream) {
-    if (!dq || !dk || !dv) return SIGATTN_ERR_INVALID_ARG;
-    const int e0 = bwd_impl(q, k, v, d_o, dq, dk, dv, seqlens, seqlens, bias, scale, B, N_max, N_max, H, d, nullptr, false, false);
-    if (e0) return e0;       // argument errors first, as the header orders them
+    // argument errors first, as the header orders them
+    if (int e = check_bwd(q, k, v, d_o, dq, dk, dv, seqlens, seqlens, bias, scale, B, N_max, N_max, H, d, true, true)) return e;
     const size_t need = sigmoid_attn_bwd_workspace_bytes(B, N_max, H, d);
     if (need > 0 && (!workspace || workspace_bytes < need)) return SIGATTN_ERR_WORKSPACE;
     const size_t one = sigmoid_attn_bwd_onepass_workspace_bytes(B, N_max, H, d);

@@ -108,6 +108,20 @@ def test_bwd_argument_validation(lib):
     assert B.sigmoid_attn_bwd_workspace_bytes(2, 256, 2, 96) == 0
 
 
+@pytest.mark.parametrize("B_,N,H,d", [(20, 1030, 8, 64), (2, 256, 2, 64), (3, 300, 4, 128)])      # one pass, small launches
+def test_bwd_refuses_misaligned_tensors_with_a_workspace(lib, B_, N, H, d):
+    """Whichever kernels a workspace leads to, the same calls are refused, before anything is launched."""
+    p, need = 4096, max(B.sigmoid_attn_bwd_onepass_workspace_bytes(B_, N, H, d), 4096)
+    names = ("q", "k", "v", "d_o", "dq", "dk", "dv")
+    for ws in (p, p + 16, None):
+        for bad in names:
+            ptrs = [p + 2 if n == bad else p for n in names]
+            assert lib.sigmoid_attn_bwd(*ptrs, p, p, 0.125, B_, N, H, d, ws, need if ws else 0, None) == B.SIGATTN_ERR_MISALIGNED, (bad, ws)
+            ptrs = [None if n == bad else p for n in names]
+            assert lib.sigmoid_attn_bwd(*ptrs, p, p, 0.125, B_, N, H, d, ws, need if ws else 0, None) == B.SIGATTN_ERR_INVALID_ARG, (bad, ws)
+        assert lib.sigmoid_attn_bwd(*[p] * 7, p, p, float("nan"), B_, N, H, d, ws, need if ws else 0, None) == B.SIGATTN_ERR_INVALID_ARG
+
+
 def test_cross_argument_validation(lib):
     p = 4096
 
