@@ -5,11 +5,18 @@
 // also forms dQ from the dS it has: five contractions and one sigmoid.  dQ of a query tile is then a sum over the
 // workgroups of a head; it is passed on from one to the next in fp32, in the order of the keys, through a scratch buffer:
 //
-//   workgroup j waits until workgroup j - 1 has published tile t, starts its contraction from those sums and publishes
+//   key tile j waits until key tile j - 1 has published tile t, starts its contraction from those sums and publishes
 //   the new ones; the last one writes dQ.
 //
-// So the order of the sums is fixed, nothing is added atomically, and results are the same bits in every run.  A workgroup
-// waits only for one with a smaller id, which the hardware has started earlier: every wait ends.
+// So the order of the sums is fixed, nothing is added atomically, and results are the same bits in every run.
+//
+// Every wait ends, in whatever order the hardware starts workgroups and whatever else runs on the GPU: the plan gives a
+// workgroup a head, and which of its key tiles is the next that none has taken when it starts.  So the tile it waits for has been
+// taken by a workgroup that has started, which keeps its CU until it ends, and the first tile waits for none.  (With the tile from
+// the workgroup's id too it would not: the XCDs start workgroups each for itself, and two launches on two streams could each
+// fill an XCD with workgroups that wait for one queued behind the other's.)  The tile is asked for while the first queries are on
+// their way, which costs 0 to 1 % (step of 4 x 12 heads of up to 8192 rows 1360 -> 1366 us, 512 x 12 of up to 512 1034 -> 1044).  A counter for the
+// whole plan, whose answer everything waits for: 512 x 12 x 512 3 % slower, 32 x 32 x 384 4 % and 16 x 12 of up to 4096 2 % faster.
 //
 // dS changes hands through LDS: the accumulators of a wave hold 32 keys by 32 queries with the queries along the registers,
 // and dQ contracts over the keys of all eight waves.  A query tile has four 32 x 32 blocks of dQ; four waves take the
@@ -40,7 +47,8 @@ constexpr size_t LDS_BYTES = STREAM_BYTES + KT_BYTES + 2 * DS_BYTES + 1024;   //
 constexpr int TILE_BYTES = BN * D * 4;       // partial sums of a query tile
 constexpr int FLAGS = NW;                    // progress counters of a workgroup
 
-// One workgroup's work: key tile j of head h of sequence z, which has nq valid queries and nk valid keys.
+// One workgroup's work: a key tile of head h of sequence z, which has nq valid queries and nk valid keys.  j counts the tiles of
+// the head; of those with valid keys each workgroup takes the next one when it starts.
 struct alignas(32) TileWork { int z, h, j, nq, nk; float bias; };
 
 struct Params {
@@ -52,7 +60,8 @@ struct Params {
     int B, L_q, L_k, H;
     int group;                               // sequences whose tiles are dealt in turn
     TileWork *plan;                          // [B H key tiles]
-    int *flags;                              // [B][H][key tiles][FLAGS]
+    int *flags;                              // [B][H][key tiles][FLAGS]; those of a head's last tile, which no tile follows,
+                                             // hold the number of its tiles that have been taken
     unsigned char *part;                     // [B][H][query tiles][TILE_BYTES]
 };
 
@@ -135,13 +144,13 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
     constexpr float LOG2E = 1.4426950408889634f;
     const TileWork work = p.plan[blockIdx.x];
     const int z = __builtin_amdgcn_readfirstlane(work.z), h = __builtin_amdgcn_readfirstlane(work.h);
-    const int j = __builtin_amdgcn_readfirstlane(work.j);
+    int j = __builtin_amdgcn_readfirstlane(work.j);
     const int nq = __builtin_amdgcn_readfirstlane(work.nq), nk = __builtin_amdgcn_readfirstlane(work.nk);
     const int T = (p.L_k + BM - 1) / BM, TQ = (p.L_q + BN - 1) / BN;
     const size_t row_stride = (size_t)p.H * D;
     const size_t base_q = (size_t)z * p.L_q * row_stride + (size_t)h * D;
     const size_t base_k = (size_t)z * p.L_k * row_stride + (size_t)h * D;
-    const int m0 = j * BM;
+    int m0 = j * BM;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ntiles = nk > 0 ? (nq + BN - 1) / BN : 0;      // streamed tiles
     const int key_tiles = (nk + BM - 1) / BM;
@@ -197,11 +206,8 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
     // dS: element (key, q') at key * 128 + (2 q' ^ X(key)), X = 16 b2 + 32 b3 + 64 b1 of the key's bits; q' counts the 64 rows
     // of a tile so that the rows of a lane's four packed pairs are neighbours: q' = 32 nb + 16 A + 8 g + 4 (a & 1) + i for row 32 nb + 8 a + 4 g + i, A = a / 2
     const int key = wave * 32 + c;
-    const bool key_ok = m0 + key < nk;
     auto swz = [](int k) { return 16 * ((k >> 2) & 1) + 32 * ((k >> 3) & 1) + 64 * ((k >> 1) & 1); };
     const int ds_base = (int)(STREAM_BYTES + KT_BYTES);
-    int dsw = key_ok ? ds_base + key * 128 + ((16 * g) ^ swz(key)) : ds_base + 2 * (int)DS_BYTES + 128 * (wave & 7) + 16 * g;
-    const int flip = key_ok ? (int)DS_BYTES : 0;
     const int job = wave & 3, grp = wave >> 2, nbq = job & 1, dh = job >> 1;      // dQ block of this wave, and which tiles' (every second)
     const bf16_t *const kt = kts + (32 * dh + c) * LDT + 8 * g;
     const int kr = 8 * g + (i16 >> 2);                                             // + 4 for the second read
@@ -215,6 +221,22 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
     bf16x8 ring[RING], qa, qb;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
+    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    // ---- the first queries are requested, and the tile of keys is taken
+    load_tile();
+    const u32x4 f1 = st1, f2 = st2;
+    __builtin_amdgcn_sched_barrier(0);
+    if (key_tiles > 1) {
+        __shared__ int taken;
+        if (tid == 0) taken = __hip_atomic_fetch_add(p.flags + (((size_t)z * p.H + h) * T + T - 1) * FLAGS, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        barrier();
+        j = __builtin_amdgcn_readfirstlane(taken);
+        m0 = j * BM;
+    }
+    const bool key_ok = m0 + key < nk;
+    int dsw = key_ok ? ds_base + key * 128 + ((16 * g) ^ swz(key)) : ds_base + 2 * (int)DS_BYTES + 128 * (wave & 7) + 16 * g;
+    const int flip = key_ok ? (int)DS_BYTES : 0;
     // ---- the chain of partial dQ sums
     const bool chained = j > 0, last_of_chain = j == key_tiles - 1;
     unsigned char *part = p.part + ((size_t)z * p.H + h) * TQ * (size_t)TILE_BYTES + (size_t)grp * TILE_BYTES;   // this wave's next tile
@@ -385,14 +407,11 @@ __global__ void __launch_bounds__(THREADS, 2) sigattn_onepass(const Params p) {
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
     using T_ = IntC<1>;
     using F_ = IntC<0>;
-    // ---- prologue: the first two tiles are requested, and the owner rows, by whole rows.  K and V pass through the place of dS:
+    // ---- prologue: the owner rows are requested, by whole rows, and the second tile.  K and V pass through the place of dS:
     // from there every wave takes its operands, and K^T is made with the transposing read.  (Operands loaded straight from
     // memory and K^T written element by element: 2000 clocks more.)
-    load_tile();
-    const u32x4 f1 = st1, f2 = st2;
     {
         const int rows = nk - m0 < BM ? nk - m0 : BM;
         const int bytes = __builtin_amdgcn_readfirstlane(rows * (int)row_stride * 2), pass = 64 * (int)row_stride * 2;

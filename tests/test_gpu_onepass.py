@@ -118,6 +118,23 @@ def test_workspaces_and_streams():
             assert torch.equal(bits(x), bits(y))
 
 
+def test_overlapping_launches_with_heads_across_xcds():
+    """Two streams, heads whose key tiles lie on several XCDs (12 heads, 33 links of a chain): a tile waits only for one that has
+    been started, so both end with the bits of a launch on its own."""
+    args = inputs(3, 8448, 12, (8448, 8200, 7000), seed=11)
+    ref = A.sigmoid_attn_bwd(*args, 0.125)
+    outs = [[torch.empty_like(args[0]) for _ in range(3)] for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for _ in range(2):
+        for side, out in zip(streams, outs):
+            A.sigmoid_attn_bwd(*args, 0.125, *out, stream=side)
+    torch.cuda.synchronize()
+    for got in outs:
+        for x, y in zip(ref, got):
+            assert torch.equal(bits(x), bits(y))
+
+
 def test_in_a_hip_graph():
     args = inputs(20, 1030, 8, lengths(20, 1030, 2), seed=3)
     eager = A.sigmoid_attn_bwd(*args, 0.125)

@@ -62,6 +62,18 @@ def test_compiled_kernels(assembly, kernel):
     assert sum(l.startswith("buffer_store_dwordx4") and l.endswith("sc1") for l in body) >= 4 * len(counts)
 
 
+def test_key_tiles_are_taken_from_a_counter(assembly):
+    """Which key tile of its head a workgroup works on is how many of the head have been taken before: one atomic addition that
+    returns, by one lane, handed to the others by a barrier before anything of the tile is read."""
+    text = assembly[re.search(r"^_ZN7sigattn7onepass15sigattn_onepassE\w+:", assembly, re.M).start():]
+    body = [l.split(";")[0].strip() for l in text[:text.index(".Lfunc_end")].split("\n")]
+    atomics = [i for i, l in enumerate(body) if "_atomic_" in l]
+    assert len(atomics) == 1 and re.match(r"global_atomic_add v\d+, .* sc0$", body[atomics[0]])
+    handed = next(i for i in range(atomics[0], len(body)) if body[i] == "s_barrier")
+    loads = [i for i, l in enumerate(body) if l.startswith("buffer_load")]
+    assert [i for i in loads if i < handed] == loads[:2]              # those of queries and dO, which do not depend on the tile
+
+
 def place(z, h, j, nq, nk, H, T, group):
     """The id that the device's plan gives to a tile, step by step."""
     n, tiles = len(nq), [(k + 255) // 256 for k in nk]
@@ -91,3 +103,41 @@ def test_plan_is_complete_and_ordered(seed):
             assert ids == sorted(ids)                                  # a tile's predecessor has a smaller id
             seen.update(ids)
     assert seen == set(range(n * H * T))
+
+
+def finishes(launches, by_start, first, cus=4):
+    """Two launches of one-pass workgroups on a GPU of eight XCDs of `cus` CUs, a workgroup to a CU.  Ids go to the XCDs in turn,
+    and each XCD starts its ids of a launch in order, those of launch first[xcd] before the other's.  A launch is the plan: the
+    (head, key tile) of each id.  A workgroup takes that tile, or (by_start) the next one of that head, and ends when the
+    tile before its own has.  True if both launches end."""
+    queues = [[[i for i in range(len(t)) if i % 8 == x] for t in launches] for x in range(8)]
+    taken, running, done = [{}, {}], [[] for _ in range(8)], [set(), set()]
+    moved = True
+    while moved:
+        moved = False
+        for x in range(8):
+            for l in (first[x], 1 - first[x]):
+                while queues[x][l] and len(running[x]) < cus:
+                    head, j = launches[l][queues[x][l].pop(0)]
+                    taken[l][head] = taken[l].get(head, 0) + 1
+                    running[x].append((l, head, taken[l][head] - 1 if by_start else j))
+                    moved = True
+        for x in range(8):
+            for l, head, j in list(running[x]):
+                if j == 0 or (head, j - 1) in done[l]:
+                    running[x].remove((l, head, j))
+                    done[l].add((head, j))
+                    moved = True
+    return all(len(d) == len(t) for d, t in zip(done, launches))
+
+
+@pytest.mark.parametrize("H,sequences,T", [(12, 5, 6), (3, 20, 5), (8, 4, 6)])
+def test_overlapping_launches_end(H, sequences, T):
+    """With tiles taken by start both launches end, whichever each XCD starts first; with tiles by id they can wait for each other
+    for ever (not where the number of heads keeps a head on one XCD)."""
+    n = [256 * T] * sequences
+    ids = {place(z, h, j, n, n, H, T, sequences): (z * H + h, j) for z in range(sequences) for h in range(H) for j in range(T)}
+    launch = [ids[i] for i in range(len(ids))]
+    orders = [[m >> x & 1 for x in range(8)] for m in range(256)]
+    assert all(finishes([launch, launch], True, first) for first in orders)
+    assert all(finishes([launch, launch], False, first) for first in orders) == (H % 8 == 0)
