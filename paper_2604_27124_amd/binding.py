@@ -165,11 +165,14 @@ def _stream_ptr(stream) -> int:
 
 def _scratch(nbytes: int, like, stream):
     """`nbytes` of device memory for a call on `stream`, or None: it belongs to that stream, so that it is handed out again
-    only to work behind the call.  None where it cannot be had (no memory; a stream that torch does not know)."""
+    only to work behind the call.  None where it cannot be had (no memory; a stream that torch does not know; tensors of another
+    device than the stream's, whose memory is handed out by the order of that device's streams)."""
     try:
         if stream is None or stream.cuda_stream == _stream_ptr(None):
+            if like.device.index != torch.cuda.current_device():
+                return None
             return torch.empty(nbytes, dtype=torch.uint8, device=like.device)
-        if isinstance(stream, torch.cuda.Stream):
+        if isinstance(stream, torch.cuda.Stream) and stream.device == like.device:
             with torch.cuda.stream(stream):
                 return torch.empty(nbytes, dtype=torch.uint8, device=like.device)
     except torch.OutOfMemoryError:

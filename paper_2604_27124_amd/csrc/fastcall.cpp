@@ -7,6 +7,7 @@
 
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -103,6 +104,8 @@ PyObject *bwd(PyObject *, PyObject *const *args, Py_ssize_t n) {
     try {
         Call c;
         if (!bwd_fn || !bytes_fn || !read(args, n, true, c)) return none();
+        const size_t need = bytes_fn(c.B, c.N, c.H, c.d);
+        if (need && c.q.get_device() != c10::hip::current_device()) return none();   // scratch belongs to a stream of its own device
         at::Tensor dq, dk, dv, ws;
         int rc;
         {
@@ -110,7 +113,6 @@ PyObject *bwd(PyObject *, PyObject *const *args, Py_ssize_t n) {
             dq = at::empty_like(c.q);
             dk = at::empty_like(c.q);
             dv = at::empty_like(c.q);
-            const size_t need = bytes_fn(c.B, c.N, c.H, c.d);
             if (need) ws = at::empty({(int64_t)need}, c.q.options().dtype(at::kByte).requires_grad(false));
             rc = bwd_fn(data<void>(c.q), data<void>(c.k), data<void>(c.v), data<void>(c.g), data<void>(dq), data<void>(dk), data<void>(dv),
                         data<int32_t>(c.seqlens), data<float>(c.bias), c.scale, c.B, c.N, c.H, c.d, need ? data<void>(ws) : nullptr,

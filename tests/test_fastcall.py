@@ -15,6 +15,20 @@ def test_what_is_not_plain_is_left_to_python():
         A.sigmoid_attn_fwd(x, x, x, n, b, 0.125)
 
 
+def test_scratch_belongs_to_the_stream_it_is_used_on(monkeypatch):
+    """Memory for a call is taken only where torch hands it out by the order of the stream the kernels run on."""
+    from types import SimpleNamespace as NS
+    made = []
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0, raising=False)
+    monkeypatch.setattr(torch, "empty", lambda n, dtype, device: made.append((n, device)) or "memory")
+    here, there = (NS(device=torch.device("cuda", i)) for i in (0, 1))
+    for stream in (None, NS(cuda_stream=0)):                           # default streams of all devices have the same handle
+        assert A._scratch(64, here, stream) == "memory" and A._scratch(64, there, stream) is None
+    assert A._scratch(64, here, NS(cuda_stream=5)) is None             # torch does not know it
+    assert made == [(64, here.device)] * 2
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,N,H,d", [(2, 256, 2, 64), (16, 1030, 12, 64), (3, 200, 2, 128)])      # pairs; one pass; d = 128
 def test_same_results_as_the_python_way(B, N, H, d):
