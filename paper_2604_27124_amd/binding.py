@@ -180,6 +180,14 @@ def _scratch(nbytes: int, like, stream):
     return None
 
 
+def _workspace_args(workspace, like):
+    """Address and bytes of a caller's workspace; 0, 0 for what the kernels may not write to as a whole: memory of the host or
+    of another device, a view with gaps or whose elements share memory."""
+    if not (getattr(workspace, "is_cuda", False) and workspace.device == like.device and workspace.is_contiguous()):
+        return 0, 0
+    return workspace.data_ptr(), workspace.numel() * workspace.element_size()
+
+
 def sigmoid_attn_fwd(q, k, v, seqlens, bias, scale: float, out=None, stream=None):
     """O = sigmoid(scale * Q K^T + bias) V over valid tokens; returns `out` (allocated if None)."""
     if out is None and stream is None:
@@ -203,7 +211,8 @@ def sigmoid_attn_fwd(q, k, v, seqlens, bias, scale: float, out=None, stream=None
 def sigmoid_attn_bwd(q, k, v, d_o, seqlens, bias, scale: float, dq=None, dk=None, dv=None, workspace=None,
                      stream=None) -> Tuple:
     """(dQ, dK, dV) from the forward inputs and dO; outputs and workspace are allocated if None (the workspace for the
-    length of the call, where the shape is computed in one pass)."""
+    length of the call, where the shape is computed in one pass).  A workspace is contiguous memory of the tensors' device; any
+    other is left alone, and the call made without one."""
     if dq is None and dk is None and dv is None and workspace is None and stream is None:
         res = (_fast or _fastcalls()).bwd(q, k, v, d_o, seqlens, bias, scale)
         if res is not None:
@@ -221,8 +230,7 @@ def sigmoid_attn_bwd(q, k, v, d_o, seqlens, bias, scale: float, dq=None, dk=None
         need = sigmoid_attn_bwd_onepass_workspace_bytes(B, N, H, d)
         if need > 0:
             workspace = _scratch(need, q, stream)
-    ws_ptr = 0 if workspace is None else workspace.data_ptr()
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_ptr, ws_bytes = _workspace_args(workspace, q)
     rc = load().sigmoid_attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), d_o.data_ptr(), dq.data_ptr(),
                                  dk.data_ptr(), dv.data_ptr(), seqlens.data_ptr(), bias.data_ptr(), float(scale),
                                  B, N, H, d, ws_ptr, ws_bytes, _stream_ptr(stream))

@@ -29,6 +29,34 @@ def test_scratch_belongs_to_the_stream_it_is_used_on(monkeypatch):
     assert made == [(64, here.device)] * 2
 
 
+def test_workspaces_the_kernels_may_write_to():
+    from types import SimpleNamespace as NS
+    def tensor(**kw):
+        t = dict(is_cuda=True, device=torch.device("cuda", 0), is_contiguous=lambda: True, data_ptr=lambda: 4096, numel=lambda: 10, element_size=lambda: 2)
+        return NS(**{**t, **kw})
+    q = tensor()
+    assert A._workspace_args(tensor(), q) == (4096, 20)
+    for bad in (None, torch.empty(1 << 20), torch.empty(1).expand(1 << 20), tensor(is_contiguous=lambda: False), tensor(device=torch.device("cuda", 1))):
+        assert A._workspace_args(bad, q) == (0, 0)
+
+
+@pytest.mark.gpu
+def test_a_workspace_of_another_kind_is_left_alone():
+    B, N, H = 16, 1030, 12
+    need = A.sigmoid_attn_bwd_onepass_workspace_bytes(B, N, H, 64)
+    q, k, v, g = (torch.randn(B, N, H, 64, device="cuda").bfloat16() for _ in range(4))
+    n, b = torch.full((B,), N, dtype=torch.int32, device="cuda"), torch.full((B,), -5.0, device="cuda")
+    want = (A.sigmoid_attn_bwd_dq(q, k, v, g, n, b, 0.125), *A.sigmoid_attn_bwd_dkdv(q, k, v, g, n, b, 0.125))
+    host, small = torch.full((need,), 3, dtype=torch.uint8), torch.full((256,), 3, dtype=torch.uint8, device="cuda")
+    strided = torch.full((need, 2), 3, dtype=torch.uint8, device="cuda")
+    for ws in (host, small[:1].expand(need), strided[:, 0]):
+        got = A.sigmoid_attn_bwd(q, k, v, g, n, b, 0.125, workspace=ws)
+        torch.cuda.synchronize()
+        for x, y in zip(got, want):                                    # two passes, as without a workspace
+            assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+    assert bool((host == 3).all()) and bool((small == 3).all()) and bool((strided == 3).all())
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,N,H,d", [(2, 256, 2, 64), (16, 1030, 12, 64), (3, 200, 2, 128)])      # pairs; one pass; d = 128
 def test_same_results_as_the_python_way(B, N, H, d):
