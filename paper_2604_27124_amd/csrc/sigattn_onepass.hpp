@@ -49,7 +49,8 @@ constexpr int FLAGS = NW;                    // progress counters of a workgroup
 
 // One workgroup's work: a key tile of head h of sequence z, which has nq valid queries and nk valid keys.  j counts the tiles of
 // the head; of those with valid keys each workgroup takes the next one when it starts.
-struct alignas(32) TileWork { int z, h, j, nq, nk; float bias; };
+struct alignas(16) TileWork { int z, h, j, nq, nk; float bias; };    // as far as a workspace has to be aligned
+static_assert(sizeof(TileWork) == 32, "two 16-byte accesses");
 
 struct Params {
     const bf16_t *q, *k, *v, *d_o;           // q, d_o [B, L_q, H, D];  k, v [B, L_k, H, D]

@@ -103,6 +103,12 @@ def test_workspaces_and_streams():
     ws = torch.full((need,), 0x7f, dtype=torch.uint8, device="cuda")   # contents irrelevant on entry
     for x, y in zip(ref, A.sigmoid_attn_bwd(*args, 0.125, workspace=ws)):
         assert torch.equal(bits(x), bits(y))
+    ws = torch.full((need + 64,), 0x7f, dtype=torch.uint8, device="cuda")
+    for start in (16, 48):                                             # aligned to 16 bytes and no further
+        for x, y in zip(ref, A.sigmoid_attn_bwd(*args, 0.125, workspace=ws[start:start + need])):
+            assert torch.equal(bits(x), bits(y))
+        assert bool((ws[:start] == 0x7f).all()) and bool((ws[start + need:] == 0x7f).all())
+    ws = ws[:need]
     dq = A.sigmoid_attn_bwd(*args, 0.125, workspace=ws[:need - 1])[0]  # too small for one pass: two
     assert torch.equal(bits(dq), bits(A.sigmoid_attn_bwd_dq(*args, 0.125)))
     torch.cuda.synchronize()

@@ -23,6 +23,15 @@ def test_workspace_size():
     assert f(1, 1100, 16384, 64) == 0                                  # one sequence that no slice can hold
 
 
+def test_plan_needs_no_more_alignment_than_a_workspace_has(tmp_path):
+    src = tmp_path / "align.hip"
+    src.write_text('#include "sigattn_onepass.hpp"\n'
+                   "static_assert(alignof(sigattn::onepass::TileWork) <= 16 && alignof(sigattn::u32x4) <= 16, \"aligned to 16 bytes\");\n")
+    flags = [f for f in B.HIPCC_FLAGS if f not in ("-shared", "-fPIC", "-O3")]
+    r = subprocess.run([B.hipcc(), *flags, "-I", B.CSRC, "-fsyntax-only", "--cuda-device-only", str(src)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+
 @pytest.fixture(scope="module")
 def assembly(tmp_path_factory):
     out = tmp_path_factory.mktemp("isa") / "api.s"
