@@ -22,6 +22,7 @@ int check_shape(int B, int N, int H, int d) {
     if (d != 64 && d != 128) return SIGATTN_ERR_UNSUPPORTED_D;
     if ((long long)B * H > 2147483647LL) return SIGATTN_ERR_TOO_LARGE;     // grid.x limit
     if ((long long)B * N * H * d >= (1LL << 40)) return SIGATTN_ERR_TOO_LARGE;
+    static_assert(pair::MAX_ROW_BYTES == (1LL << 20) * (long long)sizeof(bf16_t), "longest row");
     if ((long long)H * d > (1LL << 20)) return SIGATTN_ERR_TOO_LARGE;      // 32-bit lane offsets within one streamed tile
     if (B > 256 && (long long)N > 262144LL) return SIGATTN_ERR_TOO_LARGE;  // a documented limit; the work mapping no longer needs it
     return SIGATTN_OK;

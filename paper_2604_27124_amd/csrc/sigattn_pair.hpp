@@ -23,6 +23,7 @@ constexpr int D = 64, NW = 4, THREADS = NW * 64, BM = 64, BN = 64, LD = 72;
 // LDS slots of the two streamed tensors: a tile that is only read row-wise, for scores, is read in the step behind its
 // store (two slots); one that is contracted over its rows two steps later (four).  So two workgroups of FWD or DQ fit a CU.
 constexpr int NBUF = 4;
+constexpr long long MAX_ROW_BYTES = 2ll << 20;                         // of a row of all heads (the host takes H d up to 2^20)
 constexpr int slots1(int mode) { return mode == FWD ? 2 : NBUF; }      // K (FWD, DQ), Q (DKDV)
 constexpr int slots2(int mode) { return mode == DQ ? 2 : NBUF; }       // V, dO (DKDV)
 constexpr size_t stream_bytes(int mode) { return (size_t)(slots1(mode) + slots2(mode)) * BN * LD * sizeof(bf16_t); }
@@ -85,20 +86,24 @@ __device__ __forceinline__ void run_pass(const Params &p, const Work work, unsig
     bf16_t *const y1s = reinterpret_cast<bf16_t *>(smem);
     const int ntiles = (ns + BN - 1) / BN;
     const int r0 = tid >> 3, col0 = (tid & 7) * 8;
-    const int ld_off = (int)(((unsigned)r0 * (unsigned)row_stride + (unsigned)col0) * 2u), pass = 32 * (int)row_stride * 2;
+    const int ld_off = (int)(((unsigned)r0 * (unsigned)row_stride + (unsigned)col0) * 2u);
+    const unsigned pass = 32u * (unsigned)row_stride * 2u;
     // one descriptor per tensor, ending with the last valid row: what lies behind it reads as zeros (the host keeps a head's
     // rows below 2^31 bytes)
     const int str_bytes = __builtin_amdgcn_readfirstlane(ns * (int)row_stride * 2);
     const auto ds1 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(y1 + base_s), 0, str_bytes, 0x00027000);
     const auto ds2 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(y2 + base_s), 0, str_bytes, 0x00027000);
-    int at = 0;                                                        // bytes to the tile that is requested next
+    // Bytes to the tile that is requested next.  Tiles are requested up to STAGES + 2 behind the last one (they read as zeros), so
+    // this may pass 2^31; with its lane's offset it stays below 2^32.
+    unsigned at = 0;
+    static_assert((1ll << 31) + (STAGES + 4) * BN * MAX_ROW_BYTES < 1ll << 32, "offsets of requested tiles in 32 bits");
     u32x4 st[STAGES][4];
     auto load_tile = [&](auto stage_c) {
         constexpr int S = decltype(stage_c)::value % STAGES;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            st[S][i] = __builtin_amdgcn_raw_buffer_load_b128(ds1, ld_off, at + i * pass, 0);
-            st[S][2 + i] = __builtin_amdgcn_raw_buffer_load_b128(ds2, ld_off, at + i * pass, 0);
+            st[S][i] = __builtin_amdgcn_raw_buffer_load_b128(ds1, ld_off, (int)(at + i * pass), 0);
+            st[S][2 + i] = __builtin_amdgcn_raw_buffer_load_b128(ds2, ld_off, (int)(at + i * pass), 0);
         }
         at += 2 * pass;
     };
