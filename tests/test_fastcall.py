@@ -1,8 +1,12 @@
 """The binding's plain calls in native code: what is not plain goes the Python way, and both ways give the same."""
+import subprocess
+import sys
+
 import pytest
 import torch
 
 from paper_2604_27124_amd import binding as A
+from paper_2604_27124_amd import build
 
 
 def test_what_is_not_plain_is_left_to_python():
@@ -13,6 +17,21 @@ def test_what_is_not_plain_is_left_to_python():
         assert fast.fwd(*args) is None and fast.bwd(args[0], *args) is None
     with pytest.raises(ValueError):
         A.sigmoid_attn_fwd(x, x, x, n, b, 0.125)
+
+
+@pytest.mark.parametrize("lacks", ["torch", "g++"])
+def test_the_library_builds_without_what_only_the_extension_needs(monkeypatch, tmp_path, capsys, lacks):
+    made = []
+    monkeypatch.setattr(build, "_compile", lambda lib, sources, verbose: made.append(lib) or lib)
+    monkeypatch.setattr(build, "FASTCALL", str(tmp_path / "_fastcall.so"))
+    (tmp_path / "_fastcall.so").write_text("of an earlier build")
+    if lacks == "torch":
+        monkeypatch.setitem(sys.modules, "torch", None)
+    else:
+        monkeypatch.setattr(subprocess, "run", lambda cmd, **kw: (_ for _ in ()).throw(FileNotFoundError(cmd[0])))
+    assert build.build_library() == build.LIB
+    assert made == [build.PROBE_LIB, build.LIB] and not list(tmp_path.iterdir())
+    assert "_fastcall.so was not built" in capsys.readouterr().err
 
 
 def test_scratch_belongs_to_the_stream_it_is_used_on(monkeypatch):
