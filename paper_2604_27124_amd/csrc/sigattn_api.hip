@@ -206,15 +206,23 @@ size_t onepass_bytes(int B, int N, int H) {            // sums of dQ in fp32, wh
 
 // Sequences of one launch; 0: this shape takes two passes.  One pass does five contractions for seven, but in half as many
 // workgroups of twice the keys, one to a CU, each of which follows the one before it in its head: it needs three rounds of
-// them (768) and heads long enough that 256-row tiles round little.  One pass / two, us, H = 12, all rows valid, lengths from
-// an eighth of N on, lognormal: N = 512, B = 40 (960 tiles) 124 / 141, 63 / 70, 57 / 66; B = 86 268 / 315, 149 / 150, 127 / 136; N = 700,
-// B = 43 247 / 293, 126 / 142, 103 / 126; N = 1024, B = 66 671 / 833, 351 / 423, 265 / 319; N = 2048, B = 9 (864) 368 / 423, 148 / 153,
-// 162 / 174; B = 60 2246 / 2838, 892 / 1115, 842 / 1038.  Not below: N = 384, B = 86 (2064) 185 / 189, 106 / 96, 89 / 80; N = 300,
-// B = 256, H = 16 567 / 589, 302 / 296, 288 / 259; B = 4, N = 2048 (384 tiles) 172 / 189, from a quarter on 151 / 155; B = 8,
-// N = 1024 (384) 93 / 105, 63 / 55; B = 1, N = 1024 (48) 56 / 24.
+// them (768) and heads long enough that 256-row tiles round little; heads of two tiles, of which rounding takes most, need twelve.
+// Time of two passes / one, H = 12, lengths: all valid, three quarters of N, from an eighth of N on, lognormal:
+//   tiles of 256 keys       about 384               about 650               about 768               about 1536              about 3072
+//   N = 384       0.97 0.95 0.81 0.72     0.92 0.88 0.90 0.96     1.01 0.95 0.94 0.96     0.90 0.89 0.88 0.96     0.98 0.92 0.94 0.89
+//   N = 449       1.06 0.98 0.96 0.80     1.06 0.91 1.03 0.96     1.17 0.98 1.08 0.97     1.13 0.95 0.93 0.97     1.20 0.99 1.02 1.00
+//   N = 512       1.04 0.99 1.04 0.78     1.00 0.93 1.07 1.01     1.15 1.01 0.96 1.00     1.12 0.94 0.98 1.00     1.17 1.00 1.07 1.00
+//   N = 576       0.97 0.88 0.86 0.65     1.12 1.15 1.10 0.99     1.13 1.19 1.07 1.08     1.03 0.98 1.09 1.14     1.11 1.15 1.07 1.03
+//   N = 700       1.16 0.96 0.85 0.75     1.24 1.14 1.07 0.99     1.23 1.09 1.05 0.96     1.14 1.07 1.09 1.10     1.22 1.13 1.17 1.15
+//   N = 1024      1.03 0.96 0.88 0.69     1.14 1.22 1.04 0.93     1.31 1.15 1.17 0.95     1.26 1.18 1.16 1.18     1.25 1.24 1.21 1.20
+//   N = 2048      1.04 0.96 0.88 0.90     1.25 1.22 1.06 0.97     1.28 1.17 1.11 0.99     1.26 1.21 1.21 1.19     1.28 1.27 1.24 1.25
+//   N = 4096      1.04 0.96 0.81 1.03     1.15 1.16 1.01 1.12     1.26 1.17 1.11 1.13     1.26 1.22 1.19 1.16     1.27 1.26 1.24 1.23
+// So below 768 ragged batches lose what full ones gain, and at N <= 512 they still do at 2000.  The host does not know the lengths:
+// a batch of one long sequence among others of a sixteenth of it leaves most CUs without a tile, and one pass takes longer
+// (us, two / one: B = 16, N = 1024 38 / 60; B = 8, N = 2048 67 / 114; B = 8, N = 4096 214 / 252; not from N = 8192 on, 759 / 722 at B = 4).
 int onepass_sequences(int B, int N, int H, int d) {
-    const long long tiles = ((long long)N + onepass::BM - 1) / onepass::BM;
-    if (d != 64 || N <= 448 || B * (H * tiles) < 768) return 0;
+    const long long tiles = ((long long)N + onepass::BM - 1) / onepass::BM * H * B;
+    if (d != 64 || N <= 448 || tiles < (N <= 512 ? 3072 : 768)) return 0;
     const size_t one = onepass_bytes(1, N, H);
     if (one > ONEPASS_LIMIT) return 0;
     const long long most = (long long)(ONEPASS_LIMIT / one), slices = (B + most - 1) / most;

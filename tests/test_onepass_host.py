@@ -17,7 +17,9 @@ def test_workspace_size():
     f = A.sigmoid_attn_bwd_onepass_workspace_bytes
     assert f(4, 8192, 12, 64) == 48 * (128 * 64 * 64 * 4 + 32 * (8 * 4 + 32))
     assert f(8, 2048, 12, 64) > 0 and f(7, 2048, 12, 64) == 0          # 768 tiles of 256 keys
-    assert f(32, 449, 12, 64) > 0 and f(500, 448, 12, 64) == 0
+    assert f(128, 449, 12, 64) > 0 and f(128, 512, 12, 64) > 0 and f(500, 448, 12, 64) == 0
+    assert f(127, 449, 12, 64) == 0 and f(127, 512, 12, 64) == 0 and f(32, 513, 12, 64) > 0    # two tiles a head: 3072
+    assert f(32, 512, 32, 64) == 0
     assert f(4, 8192, 12, 128) == 0 and f(0, 8192, 12, 64) == 0
     assert 0 < f(1000, 4096, 16, 64) <= 1 << 29                        # in slices
     assert f(1, 1100, 16384, 64) == 0                                  # one sequence that no slice can hold

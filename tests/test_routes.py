@@ -1,0 +1,40 @@
+"""Which kernels a call takes, by the rules on sizes of the library's host side (compiled for the host alone; nothing is launched)."""
+import pytest
+
+from host_routes import P, Routes
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    return Routes(tmp_path_factory.mktemp("routes"))
+
+
+ONE = ["onepass.sigattn_onepass_plan", "onepass.sigattn_onepass"]
+
+
+@pytest.mark.parametrize("B,N,H,one", [
+    (32, 512, 32, False), (128, 512, 12, True), (127, 512, 12, False),      # heads of two key tiles: 3072 tiles
+    (128, 449, 12, True), (128, 448, 12, False),
+    (22, 513, 12, True), (21, 513, 12, False),                             # longer ones: 768
+    (8, 2048, 12, True), (7, 2048, 12, False), (2, 8192, 12, True),
+])
+def test_one_pass_where_it_gains(routes, B, N, H, one):
+    assert ([l.name for l in routes.bwd(B, N, H, 64)] == ONE) == one
+    assert [l.name for l in routes.bwd(B, N, H, 64, workspace=False)] == ["sigattn_bwd_kernel<64>"]
+
+
+@pytest.mark.parametrize("B,N,H", [(150, 2048, 16), (101, 4096, 16), (9, 16384, 32), (512, 512, 12)])
+def test_slices_cover_the_batch_inside_the_workspace(routes, B, N, H):
+    need = routes.lib.sigmoid_attn_bwd_onepass_workspace_bytes(B, N, H, 64)
+    out, done = routes.bwd(B, N, H, 64), 0
+    for plan, work in zip(out[::2], out[1::2]):
+        assert [plan.name, work.name] == ONE
+        for l in (plan, work):
+            assert l.q == P + done * N * H * 64 * 2 and l.B == plan.B and 1 <= l.in_order <= l.B    # in_order: the group
+            assert (l.part, l.plan, l.flags) == (plan.part, plan.plan, plan.flags)
+        tiles = plan.B * H * -(-N // 256)
+        assert work.grid == tiles and plan.grid == -(-tiles // 256)
+        assert work.part == 2 * P and work.plan - work.part == plan.B * H * -(-N // 64) * 16384
+        assert work.flags - work.plan == tiles * 32 and work.flags + tiles * 32 <= 2 * P + need
+        done += plan.B
+    assert done == B
