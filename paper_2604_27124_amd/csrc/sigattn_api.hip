@@ -153,14 +153,23 @@ long long pair_load(const Params &a, const Params &b) {
     return (pair_tiles(a) * sa + pair_tiles(b) * sb + most - 1) / most;
 }
 
+// Work mapping of a small launch: more sequences than a wave ranks for itself take a histogram, 1.7 us of 5 to 7, for an order that
+// matters only where workgroups follow each other on a CU and differ in length.  Sorted / batch order, us, d = 64: forward at
+// B = 65, H = 1, N = 64 6.0 / 4.3, B = 256 6.5 / 4.7; backward at B = 100 6.9 / 5.5; d = 128: backward at B = 256, H = 1, N = 128 (one tile a
+// head) 28.8 / 24.4; at B = 128, H = 1, N = 200 (512 workgroups, two a CU) all valid 35.0 / 32.6, from an eighth on 26.1 / 26.0, one long
+// sequence at the end 18.4 / 26.6.
+int small_order(const Params &p, long long wgs, int owner_rows) {
+    return p.B > MAP_WAVE_B && (wgs <= 256 || (p.N <= owner_rows && p.N_str <= owner_rows));
+}
+
 template <int MODE>
 int launch_pair(Params p, hipStream_t stream) {
-    p.in_order = 0;
+    p.in_order = small_order(p, pair_tiles(p), pair::BM);
     return enqueue(pair::sigattn_pair<MODE>, pair_tiles(p), pair::THREADS, pair::lds_bytes(MODE), stream, p);
 }
 
 int launch_pair_bwd(Params kv, Params q, hipStream_t stream) {
-    kv.in_order = q.in_order = 0;
+    kv.in_order = q.in_order = small_order(kv, pair_tiles(kv) + pair_tiles(q), pair::BM);
     const int q_first = kv.N_str < q.N_str;             // the pass whose workgroups stream more rows starts
     return enqueue(pair::sigattn_pair_bwd, pair_tiles(kv) + pair_tiles(q), pair::THREADS, pair::lds_bytes(DKDV), stream, kv, q, q_first,
                    (int)(q_first ? pair_tiles(q) : pair_tiles(kv)));
@@ -182,13 +191,13 @@ template <int MODE, int LD1, int LD2, int OCC>
 int launch_half(Params p, hipStream_t stream) {
     using C = Cfg<MODE, 128, 1, half128::NW, 64, LD1, LD2, 4>;
     static_assert(C::BM == 32 * half128::NW, "tile height");
-    p.in_order = 0;
+    p.in_order = small_order(p, half_tiles(p), C::BM);
     return enqueue(half128::sigattn_half<MODE, LD1, LD2, OCC>, half_tiles(p), C::THREADS, C::LDS_BYTES, stream, p);
 }
 
 int launch_half_bwd(Params kv, Params q, hipStream_t stream) {
     constexpr size_t lds_kv = Cfg<DKDV, 128, 1, half128::NW, 64, 144, 144, 4>::LDS_BYTES, lds_q = Cfg<DQ, 128, 1, half128::NW, 64, 144, 136, 4>::LDS_BYTES;
-    kv.in_order = q.in_order = 0;
+    kv.in_order = q.in_order = small_order(kv, half_tiles(kv) + half_tiles(q), 32 * half128::NW);
     const int q_first = kv.N_str < q.N_str;             // the pass whose workgroups stream more rows starts
     return enqueue(half128::sigattn_half_bwd, half_tiles(kv) + half_tiles(q), half128::NW * 64, lds_kv > lds_q ? lds_kv : lds_q, stream, kv, q,
                    q_first, (int)(q_first ? half_tiles(q) : half_tiles(kv)));

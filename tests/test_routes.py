@@ -38,3 +38,23 @@ def test_slices_cover_the_batch_inside_the_workspace(routes, B, N, H):
         assert work.flags - work.plan == tiles * 32 and work.flags + tiles * 32 <= 2 * P + need
         done += plan.B
     assert done == B
+
+
+@pytest.mark.parametrize("B,N,H,d,fwd,bwd", [
+    # (kernel, batch order)                                 one tile a head or all workgroups at once: batch order
+    (64, 64, 1, 64, ("pair.sigattn_pair<0>", 0), ("pair.sigattn_pair_bwd", 0)),          # ranked in registers
+    (65, 64, 1, 64, ("pair.sigattn_pair<0>", 1), ("pair.sigattn_pair_bwd", 1)),
+    (128, 64, 1, 64, ("pair.sigattn_pair<0>", 1), ("pair.sigattn_pair_bwd", 1)),
+    (128, 128, 1, 64, ("pair.sigattn_pair<0>", 1), ("sigattn_bwd_kernel<64>", 1)),
+    (64, 128, 1, 128, ("half128.sigattn_half<0>", 0), ("half128.sigattn_half_bwd", 0)),
+    (128, 128, 1, 128, ("half128.sigattn_half<0>", 1), ("half128.sigattn_half_bwd", 1)),
+    (256, 128, 1, 128, ("half128.sigattn_half<0>", 1), ("half128.sigattn_half_bwd", 1)),
+    (128, 129, 1, 128, ("half128.sigattn_half<0>", 1), ("half128.sigattn_half_bwd", 0)),  # 512 of two tiles a head: longest first
+])
+def test_small_launches_of_many_sequences(routes, B, N, H, d, fwd, bwd):
+    assert [(l.name, l.in_order) for l in routes.fwd(B, N, N, H, d)] == [fwd]
+    assert [(l.name, l.in_order) for l in routes.bwd(B, N, H, d)] == [bwd]
+    for which, mode in (("dq", 1), ("dkdv", 2)):
+        (l,) = routes.half(which, B, N, H, d)
+        if "pair" in l.name or "half128" in l.name:
+            assert l.name.endswith(f"<{mode}>") and l.in_order == (B > 64)
