@@ -146,10 +146,15 @@ bool pair_reach(const Params &p) {
 long long pair_tiles(const Params &p) { return ((long long)p.N + pair::BM - 1) / pair::BM * p.B * p.H; }
 long long pair_steps(const Params &p) { return ((long long)p.N_str + pair::BN - 1) / pair::BN; }                 // of one workgroup
 
-// The workgroups that the longest ones leave room for: all of a pass, or of both, in units of the longest.
+// The workgroups of a pass, or those of both in units of the longest: the time of one is its steps and a start and end of about
+// PAIR_START of them, which is most of a short one's.  Other kernels / pairs, us, backward at B = 16, H = 2, 100 queries, 1000 keys (250 units;
+// all valid, from an eighth on, one long sequence) 22.1 / 19.1, 19.2 / 14.3, 20.2 / 15.2; B = 64, H = 1, 64 queries, 300 keys (268) 13.2 / 16.3, 12.8 /
+// 16.0, 12.6 / 13.4; B = 16, H = 2, 200 and 3000 (412) 52.0 / 60.8, 48.4 / 39.8, 48.3 / 34.3; B = 64, H = 2, 64 and 300 (535) 13.6 / 26.6, 12.3 / 24.4,
+// 10.5 / 21.8.  (By steps alone those are 128, 128, 256 and 256 units.)
+constexpr long long PAIR_START = 6;
 long long pair_load(const Params &p) { return pair_tiles(p); }
 long long pair_load(const Params &a, const Params &b) {
-    const long long sa = pair_steps(a), sb = pair_steps(b), most = sa > sb ? sa : sb;
+    const long long sa = pair_steps(a) + PAIR_START, sb = pair_steps(b) + PAIR_START, most = sa > sb ? sa : sb;
     return (pair_tiles(a) * sa + pair_tiles(b) * sb + most - 1) / most;
 }
 

@@ -58,3 +58,13 @@ def test_small_launches_of_many_sequences(routes, B, N, H, d, fwd, bwd):
         (l,) = routes.half(which, B, N, H, d)
         if "pair" in l.name or "half128" in l.name:
             assert l.name.endswith(f"<{mode}>") and l.in_order == (B > 64)
+
+
+@pytest.mark.parametrize("B,Lq,Lk,H,pairs", [
+    (16, 100, 1000, 2, True), (40, 64, 300, 1, True), (16, 200, 3000, 1, True), (2, 200, 4000, 4, True),
+    (64, 64, 300, 1, False), (64, 64, 300, 2, False), (64, 100, 1000, 1, False), (16, 200, 3000, 2, False),
+    (64, 128, 128, 1, True), (65, 100, 100, 1, False),                      # workgroups of one length: their number
+])
+def test_short_workgroups_count_with_their_start(routes, B, Lq, Lk, H, pairs):
+    for a, b in ((Lq, Lk), (Lk, Lq)):
+        assert [l.name for l in routes.cross_bwd(B, a, b, H, 64)] == ["pair.sigattn_pair_bwd" if pairs else "sigattn_bwd_kernel<64>"]
