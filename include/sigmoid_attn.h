@@ -79,9 +79,12 @@ int sigmoid_attn_fwd(const void *q, const void *k, const void *v, void *o,
  *                  the caller, contents irrelevant on entry and undefined on exit.  That size is 0 for
  *                  every shape (each kernel owns its output tiles), so NULL / 0 is accepted.
  * With a 16-byte aligned workspace of sigmoid_attn_bwd_onepass_workspace_bytes(...) bytes or more, where that is not 0, the
- * scores are computed once for all three gradients, which is faster.  dK and dV are the same bits either way; dQ differs
- * by the rounding of other intermediate values.  Both ways give the same bits in every run.  Calls whose kernels may
- * overlap need workspaces of their own.
+ * scores are computed once for all three gradients, which is faster for most batches.  (Not where one sequence is many times
+ * as long as the others, so that its 256-row tiles over all heads leave CUs idle: up to 2.6 times slower.)  dK and dV are the
+ * same bits either way; dQ differs by the rounding of other intermediate values, with the same error against exact arithmetic.
+ * Which way a call takes follows from B, N_max, H, d and from whether there is such a workspace, and from nothing else; within
+ * either way the bits of a sequence's results depend on that sequence alone, and are the same in every run.  Calls whose kernels
+ * may overlap need workspaces of their own.
  */
 int sigmoid_attn_bwd(const void *q, const void *k, const void *v, const void *d_o,
                      void *dq, void *dk, void *dv,

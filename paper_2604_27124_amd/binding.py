@@ -211,8 +211,14 @@ def sigmoid_attn_fwd(q, k, v, seqlens, bias, scale: float, out=None, stream=None
 def sigmoid_attn_bwd(q, k, v, d_o, seqlens, bias, scale: float, dq=None, dk=None, dv=None, workspace=None,
                      stream=None) -> Tuple:
     """(dQ, dK, dV) from the forward inputs and dO; outputs and workspace are allocated if None (the workspace for the
-    length of the call, where the shape is computed in one pass).  A workspace is contiguous memory of the tensors' device; any
-    other is left alone, and the call made without one."""
+    length of the call, at most 512 MiB, where the shape is computed in one pass).  A workspace is contiguous memory of the
+    tensors' device; any other is left alone, and the call made without one.
+
+    dQ's last bits depend on whether the call is computed in one pass or two, which follows from the shape and the workspace.
+    Without a workspace argument that is one pass wherever the shape takes it, except where the workspace cannot be had: no
+    memory left, a stream object that is not torch's, tensors of another device than the current one.  A caller who needs the
+    same bits in those cases too passes a workspace (one pass), or an empty tensor (two passes, as do batches of one long
+    sequence among short ones, which are faster so)."""
     if dq is None and dk is None and dv is None and workspace is None and stream is None:
         res = (_fast or _fastcalls()).bwd(q, k, v, d_o, seqlens, bias, scale)
         if res is not None:

@@ -124,6 +124,35 @@ def test_workspaces_and_streams():
             assert torch.equal(bits(x), bits(y))
 
 
+@pytest.mark.parametrize("B,N", [(40, 1030), (300, 1030), (40, 2100), (150, 1500)])     # ranked, batch order, other padding, slices
+def test_a_sequence_has_the_same_bits_in_every_batch(B, N):
+    """One pass: what surrounds a sequence (other sequences, padding, slices of the batch) reaches none of its bits."""
+    base = inputs(20, 1030, 16, lengths(20, 1030, 9), seed=12)
+    ref = A.sigmoid_attn_bwd(*base, 0.125)
+    args = inputs(B, N, 16, lengths(B, N, 10), seed=13)
+    at = [(7 * z + 3) % B for z in range(20)]
+    for z, to in enumerate(at):
+        for whole, part in zip(args[:4], base[:4]):
+            whole[to, :1030] = part[z]
+        args[4][to] = base[4][z]
+    assert A.sigmoid_attn_bwd_onepass_workspace_bytes(B, N, 16, 64) > 0
+    for one, many in zip(ref, A.sigmoid_attn_bwd(*args, 0.125)):
+        for z, to in enumerate(at):
+            assert torch.equal(bits(one[z]), bits(many[to, :1030])), z
+
+
+def test_where_no_workspace_can_be_had(monkeypatch):
+    """Without memory for it the call is the two-pass one, bit for bit, and so is one with an empty workspace."""
+    args = inputs(20, 1030, 8, lengths(20, 1030, 4), seed=14)
+    two = (A.sigmoid_attn_bwd_dq(*args, 0.125), *A.sigmoid_attn_bwd_dkdv(*args, 0.125))
+    empty = A.sigmoid_attn_bwd(*args, 0.125, workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    monkeypatch.setattr(A, "_fast", A._NoFastCalls)
+    monkeypatch.setattr(A, "_scratch", lambda *a: None)
+    for got in (empty, A.sigmoid_attn_bwd(*args, 0.125)):
+        for x, y in zip(got, two):
+            assert torch.equal(bits(x), bits(y))
+
+
 def test_overlapping_launches_with_heads_across_xcds():
     """Two streams, heads whose key tiles lie on several XCDs (12 heads, 33 links of a chain): a tile waits only for one that has
     been started, so both end with the bits of a launch on its own."""
