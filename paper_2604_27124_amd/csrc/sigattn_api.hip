@@ -146,16 +146,19 @@ bool pair_reach(const Params &p) {
 long long pair_tiles(const Params &p) { return ((long long)p.N + pair::BM - 1) / pair::BM * p.B * p.H; }
 long long pair_steps(const Params &p) { return ((long long)p.N_str + pair::BN - 1) / pair::BN; }                 // of one workgroup
 
-// The workgroups of a pass, or those of both in units of the longest: the time of one is its steps and a start and end of about
-// PAIR_START of them, which is most of a short one's.  Other kernels / pairs, us, backward at B = 16, H = 2, 100 queries, 1000 keys (250 units;
-// all valid, from an eighth on, one long sequence) 22.1 / 19.1, 19.2 / 14.3, 20.2 / 15.2; B = 64, H = 1, 64 queries, 300 keys (268) 13.2 / 16.3, 12.8 /
-// 16.0, 12.6 / 13.4; B = 16, H = 2, 200 and 3000 (412) 52.0 / 60.8, 48.4 / 39.8, 48.3 / 34.3; B = 64, H = 2, 64 and 300 (535) 13.6 / 26.6, 12.3 / 24.4,
-// 10.5 / 21.8.  (By steps alone those are 128, 128, 256 and 256 units.)
+// Both passes of a backward call: a workgroup to a CU, or where those of one pass live at most half as long as those of the other, as
+// many short ones besides as fit behind each other.  (With one more than 256 of about the same length, two share a CU for all their
+// life.)  A workgroup's life is its steps and a start and end of about PAIR_START of them.  Other kernels / pairs, us, all
+// valid and lengths from an eighth on: 40 queries, 148 keys, 64 heads (256 workgroups) 7.6 / 6.6, 7.5 / 6.4, 72 heads (288) 8.0 / 9.3, 7.8 /
+// 6.6; 64 and 128, 80 heads (240) 7.1 / 6.2, 6.9 / 6.0, 88 (264) 7.5 / 9.8, 7.4 / 7.5; 200 and 400, 24 heads (264) 11.9 / 13.4, 10.6 / 8.3.
+// Short ones besides: 64 and 512, 48 heads (432, room for 240) 12.4 / 10.0, 10.4 / 8.5, 56 (504, 280) 13.4 / 13.7, 12.5 / 10.0; 100 and 1000,
+// 32 heads (576, 251) 21.4 / 16.3, 15.1 / 11.5; 200 and 3000, 16 heads (816, 206) 48.4 / 32.5, 44.8 / 30.7, 32 (1632, 412) 52.0 / 60.8, 48.4 / 39.8;
+// 64 and 300, 128 heads (768, 535) 13.6 / 26.6, 12.3 / 24.4.
 constexpr long long PAIR_START = 6;
-long long pair_load(const Params &p) { return pair_tiles(p); }
-long long pair_load(const Params &a, const Params &b) {
-    const long long sa = pair_steps(a) + PAIR_START, sb = pair_steps(b) + PAIR_START, most = sa > sb ? sa : sb;
-    return (pair_tiles(a) * sa + pair_tiles(b) * sb + most - 1) / most;
+bool pair_fits(const Params &a, const Params &b) {
+    const long long ta = pair_tiles(a), tb = pair_tiles(b), la = pair_steps(a) + PAIR_START, lb = pair_steps(b) + PAIR_START;
+    const long long most = la > lb ? la : lb, least = la > lb ? lb : la;
+    return ta + tb <= PAIR_WGS || (most >= 2 * least && ta * la + tb * lb <= PAIR_WGS * most);
 }
 
 // Work mapping of a small launch: more sequences than a wave ranks for itself take a histogram, 1.7 us of 5 to 7, for an order that
@@ -233,7 +236,9 @@ size_t onepass_bytes(int B, int N, int H) {            // sums of dQ in fp32, wh
 //   N = 4096      1.04 0.96 0.81 1.03     1.15 1.16 1.01 1.12     1.26 1.17 1.11 1.13     1.26 1.22 1.19 1.16     1.27 1.26 1.24 1.23
 // So below 768 ragged batches lose what full ones gain, and at N <= 512 they still do at 2000.  The host does not know the lengths:
 // a batch of one long sequence among others of a sixteenth of it leaves most CUs without a tile, and one pass takes longer
-// (us, two / one: B = 16, N = 1024 38 / 60; B = 8, N = 2048 67 / 114; B = 8, N = 4096 214 / 252; not from N = 8192 on, 759 / 722 at B = 4).
+// (us, two / one: B = 16, N = 1024 38 / 60; B = 8, N = 2048 67 / 114; B = 8, N = 4096 214 / 252; not from N = 8192 on, 759 / 722 at B = 4;
+// H = 2, where the long one has fewest tiles: B = 85, N = 1406 33 / 87; with lognormal lengths B = 19, N = 5892 382 / 444, over 21
+// such batches of two heads 0.86 to 1.28 times as fast, 1.04 on average).
 int onepass_sequences(int B, int N, int H, int d) {
     const long long tiles = ((long long)N + onepass::BM - 1) / onepass::BM * H * B;
     if (d != 64 || N <= 448 || tiles < (N <= 512 ? 3072 : 768)) return 0;
@@ -325,7 +330,7 @@ static int fwd_impl(const void *q, const void *k, const void *v, void *o,
         // operand read.  A grid of at most one such workgroup per CU is split finer, into 128-row tiles (B = 4,
         // H = 16, N = 1024, 256 workgroups: 19.3 against 23.0 us; B = 8, H = 12, 384 workgroups: 32.4 against
         // 30.2 us), and sequences that fit one 128-row tile take it (B = 200, H = 8, N = 100: 19.2 against 25.1 us).
-        if (pair_load(p) <= PAIR_WGS && pair_reach(p)) return launch_pair<FWD>(p, s);
+        if (pair_tiles(p) <= PAIR_WGS && pair_reach(p)) return launch_pair<FWD>(p, s);
         if (L_q <= 128 || (long long)B * H * ((L_q + 255) / 256) <= 256) return launch<FWD, 64, 1, 4, 64, 72, 72, 2, 4>(p, s);
         return launch<FWD, 64, 2, 4, 64, 72, 72, 2, 4>(p, s);
     }
@@ -387,9 +392,9 @@ static int bwd_impl(const void *q, const void *k, const void *v, const void *d_o
         // One launch for both passes: one start, and the tail of the first is filled by the second (B = 2, H = 2,
         // N = 256: 9.4 us against 9.0 + 8.0; B = 12 heads of N = 1000: 22.5 against 21.9 + 19.4; N = 8192: 1.5 % less).
         if (pair_reach(pk) && pair_reach(pq)) {
-            if (want_dkdv && want_dq && pair_load(pk, pq) <= PAIR_WGS) return launch_pair_bwd(pk, pq, s);
-            if (want_dkdv && !want_dq && pair_load(pk) <= PAIR_WGS) return launch_pair<DKDV>(pk, s);
-            if (want_dq && !want_dkdv && pair_load(pq) <= PAIR_WGS) return launch_pair<DQ>(pq, s);
+            if (want_dkdv && want_dq && pair_fits(pk, pq)) return launch_pair_bwd(pk, pq, s);
+            if (want_dkdv && !want_dq && pair_tiles(pk) <= PAIR_WGS) return launch_pair<DKDV>(pk, s);
+            if (want_dq && !want_dkdv && pair_tiles(pq) <= PAIR_WGS) return launch_pair<DQ>(pq, s);
         }
         if (want_dkdv && want_dq) return launch_bwd<64, 4, 64, 72, 2, 8, 4>(pk, pq, s);
         if (want_dkdv) return launch<DKDV, 64, 1, 4, 64, 72, 72, 2, 8>(pk, s);

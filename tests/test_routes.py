@@ -61,10 +61,11 @@ def test_small_launches_of_many_sequences(routes, B, N, H, d, fwd, bwd):
 
 
 @pytest.mark.parametrize("B,Lq,Lk,H,pairs", [
-    (16, 100, 1000, 2, True), (40, 64, 300, 1, True), (16, 200, 3000, 1, True), (2, 200, 4000, 4, True),
-    (64, 64, 300, 1, False), (64, 64, 300, 2, False), (64, 100, 1000, 1, False), (16, 200, 3000, 2, False),
-    (64, 128, 128, 1, True), (65, 100, 100, 1, False),                      # workgroups of one length: their number
+    (8, 40, 148, 8, True), (9, 40, 148, 8, False), (5, 64, 128, 16, True), (11, 64, 128, 8, False),     # 256 of about one length
+    (64, 128, 128, 1, True), (65, 100, 100, 1, False), (64, 64, 300, 2, False), (16, 200, 400, 1, True), (3, 200, 400, 8, False),
+    (3, 64, 512, 16, True), (7, 64, 512, 8, False), (16, 100, 1000, 2, True), (64, 100, 1000, 1, False),   # short ones besides
+    (16, 200, 3000, 1, True), (16, 200, 3000, 2, False), (2, 200, 4000, 4, True),
 ])
-def test_short_workgroups_count_with_their_start(routes, B, Lq, Lk, H, pairs):
+def test_pairs_of_both_passes(routes, B, Lq, Lk, H, pairs):
     for a, b in ((Lq, Lk), (Lk, Lq)):
         assert [l.name for l in routes.cross_bwd(B, a, b, H, 64)] == ["pair.sigattn_pair_bwd" if pairs else "sigattn_bwd_kernel<64>"]
