@@ -251,9 +251,6 @@ int onepass_sequences(int B, int N, int H, int d) {
 int launch_onepass(onepass::Params p, const int per_slice, unsigned char *workspace, hipStream_t stream) {
     const int B = p.B, T = (p.L_k + onepass::BM - 1) / onepass::BM, TQ = (p.L_q + onepass::BN - 1) / onepass::BN;
     const size_t row = (size_t)p.H * onepass::D;
-    // A tile of keys takes about one round of its query tiles after another, 256 at a time, and follows the tile before it
-    // by three of them: 768 / TQ heads in turn keep pace, four times as many leave room (measured at the mapping).
-    const long long turn = (3000 + (long long)p.H * TQ - 1) / ((long long)p.H * TQ);
     for (int z = 0; z < B; z += per_slice) {
         onepass::Params s = p;
         s.B = B - z < per_slice ? B - z : per_slice;
@@ -261,7 +258,7 @@ int launch_onepass(onepass::Params p, const int per_slice, unsigned char *worksp
         s.q += q_off; s.d_o += q_off; s.dq += q_off;
         s.k += k_off; s.v += k_off; s.dk += k_off; s.dv += k_off;
         s.seqlens_q += z; s.seqlens_k += z; s.bias += z;
-        s.group = (int)(turn < s.B ? turn : s.B);
+        s.group = onepass::plan_group(s.B, p.H, TQ);
         const long long wgs = (long long)s.B * s.H * T;
         s.part = workspace;
         s.plan = reinterpret_cast<onepass::TileWork *>(workspace + (size_t)s.B * s.H * TQ * onepass::TILE_BYTES);

@@ -27,14 +27,14 @@
 // 8 x 12 x 2048 368 -> 294 us (both passes in one launch before).
 #pragma once
 #include "sigattn_kernels.hpp"
+#include "sigattn_onepass_plan.hpp"
 
 namespace sigattn {
 namespace onepass {
 
 constexpr int D = 64;
 constexpr int NW = 8, THREADS = NW * 64;     // waves of 32 keys each
-constexpr int BM = NW * 32;                  // key rows of a workgroup
-constexpr int BN = 64;                       // query rows of a streamed tile
+static_assert(BM == NW * 32, "key rows of a workgroup");
 constexpr int RING_TILES = 3;                // LDS ring: tile t lives in slot t % 3
 constexpr int LD = 72;                       // elements of a streamed row in LDS
 constexpr int LDT = BM + 8;                  // elements of a row of the transposed key tile
@@ -46,11 +46,6 @@ constexpr size_t DS_BYTES = (size_t)BM * BN * sizeof(bf16_t);      // one of two
 constexpr size_t LDS_BYTES = STREAM_BYTES + KT_BYTES + 2 * DS_BYTES + 1024;   // the last for dS of keys behind the end
 constexpr int TILE_BYTES = BN * D * 4;       // partial sums of a query tile
 constexpr int FLAGS = NW;                    // progress counters of a workgroup
-
-// One workgroup's work: a key tile of head h of sequence z, which has nq valid queries and nk valid keys.  j counts the tiles of
-// the head; of those with valid keys each workgroup takes the next one when it starts.
-struct alignas(16) TileWork { int z, h, j, nq, nk; float bias; };    // as far as a workspace has to be aligned
-static_assert(sizeof(TileWork) == 32, "two 16-byte accesses");
 
 struct Params {
     const bf16_t *q, *k, *v, *d_o;           // q, d_o [B, L_q, H, D];  k, v [B, L_k, H, D]
@@ -66,70 +61,30 @@ struct Params {
     unsigned char *part;                     // [B][H][query tiles][TILE_BYTES]
 };
 
-__device__ __forceinline__ int clamp_len(int v, int n) { return v < 0 ? 0 : (v > n ? n : v); }
-
-// The plan of a launch: the work of every workgroup, and its progress counts set to zero.  Made by a kernel of its own, a
-// thread per tile: in the workgroups themselves it took 5000 to 7000 clocks of each one's 26000 (N = 128) to 170000 (N = 2048).
-//
-// A tile of keys has a larger id than the tiles before it in its head (the order of the chain), and long sequences come
-// first.  A tile can only follow the one before it at a distance of about three query tiles, so tiles of one head that
-// start together wait for each other; `group` sequences of neighbouring rank are therefore dealt in turn, tile by tile.  Up
-// to PLAN_B sequences are ranked, by their queries (a workgroup's time); more are taken in batch order, in groups as well.
-// Padded tiles, which only write zeros, come last or with their sequence.
-// Time with groups of one / few / all sequences, us: 4 x 12 heads, 2958 to 7122 rows 995 / 1004 / 1034; 8 x 12 x 2048
-// 325 / 303 / 299; 16 x 12 of 64 to 4096 rows 593 / 580 / 605; 4 x 12 x 8192 2345 / 2265 / 2240.
-constexpr int PLAN_THREADS = 256, PLAN_B = PLAN_THREADS;
-
+// The plan of a launch (sigattn_onepass_plan.hpp): the work of every workgroup, and its progress counts set to zero.  Made by a
+// kernel of its own, a thread per tile: in the workgroups themselves it took 5000 to 7000 clocks of each one's 26000 (N = 128) to
+// 170000 (N = 2048).
 __global__ void __launch_bounds__(PLAN_THREADS) sigattn_onepass_plan(const Params p) {
-    __shared__ int s_q[PLAN_B], s_rank[PLAN_B], s_tiles[PLAN_B];     // queries and rank of a sequence, tiles of a rank
-    __shared__ int s_before[PLAN_B + 1], s_padded[PLAN_B + 1];       // tiles of the ranks before; padded tiles of the sequences before
+    __shared__ PlanScratch s;
     const int T = (p.L_k + BM - 1) / BM, tid = threadIdx.x;
-    const bool ranked = p.B <= PLAN_B;
-    if (ranked) {
-        const int q = tid < p.B ? clamp_len(p.seqlens_q[tid], p.L_q) : -1;
-        const int tiles = tid < p.B ? (clamp_len(p.seqlens_k[tid], p.L_k) + BM - 1) / BM : T;
-        s_q[tid] = q;
+    if (p.B <= PLAN_B) {
+        const int q = tid < p.B ? p.seqlens_q[tid] : 0, k = tid < p.B ? p.seqlens_k[tid] : 0;
+        plan_take(s, tid, p.B, q, p.L_q);
         __syncthreads();
-        int rank = 0;
-        for (int u = 0; u < p.B; ++u) rank += s_q[u] > q || (s_q[u] == q && u < tid) ? 1 : 0;
-        s_rank[tid] = rank;
-        if (tid < p.B) s_tiles[rank] = tiles;
+        plan_rank(s, tid, p.B, k, p.L_k);
         __syncthreads();
-        s_before[tid + 1] = tid < p.B ? s_tiles[tid] : 0;
-        s_padded[tid + 1] = T - tiles;
-        if (tid == 0) s_before[0] = s_padded[0] = 0;
-        for (int off = 1; off < PLAN_B; off <<= 1) {                 // inclusive prefix sums
+        plan_fill(s, tid, p.B, k, p.L_k);
+        for (int step = 0; step < PLAN_SCANS; ++step) {
             __syncthreads();
-            const int x = tid >= off ? s_before[tid + 1 - off] : 0, y = tid >= off ? s_padded[tid + 1 - off] : 0;
-            __syncthreads();
-            s_before[tid + 1] += x;
-            s_padded[tid + 1] += y;
+            plan_scan(s, tid, step);
         }
         __syncthreads();
     }
     const int i = blockIdx.x * PLAN_THREADS + tid;                   // = ((z H) + h) T + j
     if (i >= p.B * p.H * T) return;
     const int j = i % T, h = i / T % p.H, z = i / T / p.H;
-    int id;
-    if (!ranked) {
-        const int z0 = z - z % p.group, members = p.B - z0 < p.group ? p.B - z0 : p.group;
-        id = z0 * p.H * T + (j * members + z - z0) * p.H + h;
-    } else {
-        const int rank = s_rank[z], mine = s_tiles[rank], lo = rank - rank % p.group;
-        int at;                                                      // tiles of one head each in front of this one
-        if (j < mine) {
-            at = s_before[lo];
-            for (int r = lo; r < lo + p.group && r < p.B; ++r) {
-                const int t = s_tiles[r];
-                at += (t < j ? t : j) + (r < rank && t > j ? 1 : 0);
-            }
-        } else {
-            at = s_before[p.B] + s_padded[z] + j - mine;
-        }
-        id = at * p.H + h;
-    }
     const TileWork w = {z, h, j, clamp_len(p.seqlens_q[z], p.L_q), clamp_len(p.seqlens_k[z], p.L_k), p.bias[z]};
-    p.plan[id] = w;
+    p.plan[plan_id(s, z, h, j, p.B, p.H, T, p.group)] = w;
     const u32x4 z4 = {0u, 0u, 0u, 0u};
     u32x4 *const counts = reinterpret_cast<u32x4 *>(p.flags + (size_t)i * FLAGS);
     counts[0] = z4;

@@ -1,10 +1,13 @@
 """The one-pass backward on the host: which shapes take it, what the compiled kernel (and those of the pairs) has to hold
-to, and that its plan gives every tile once and in the order the chain of a head needs."""
+to, that its plan (its own functions, run on the CPU) gives every tile once and in the order the chain of a head needs, and that
+two launches at once end."""
+import ctypes
 import os
 import random
 import re
 import subprocess
 
+import numpy as np
 import pytest
 
 from paper_2604_27124_amd import binding as A
@@ -48,8 +51,9 @@ def assembly(tmp_path_factory):
                                     "7half12812sigattn_halfILi1E", "7half12816sigattn_half_bwdE"])
 def test_compiled_kernels(assembly, kernel):
     """No spills, and two waves a SIMD where one is not all there is; in the kernels with loops of their own every barrier
-    waits for all LDS work (those of d = 128 run the loop that the other tests look at).  One pass: the sums between workgroups are
-    stored and read at agent scope, and each count follows a full wait for them."""
+    waits for all LDS work (the partial waits of the d = 128 ones are looked at with those of the large kernels, whose loop
+    they run).  One pass: the sums between workgroups are stored and read at agent scope, and between the last of them and each
+    count stands a full wait."""
     text = assembly[re.search(rf"^_ZN7sigattn{kernel}\w+:", assembly, re.M).start():]
     end = text.index(".Lfunc_end")
     meta = dict(re.findall(r"^; (NumVgprs|ScratchSize|Occupancy): (\d+)", text[end:end + 6000], re.M)[:3])
@@ -67,10 +71,13 @@ def test_compiled_kernels(assembly, kernel):
         assert re.match(r"s_waitcnt .*lgkmcnt\(0\)", body[j]), body[j:i + 1]
     if "onepass" not in kernel:
         return
-    counts = [l for l in body if l.startswith("global_store_dword ")]
-    waits = re.findall(r"ASMSTART\n\ts_waitcnt vmcnt\(0\)\n", text[:end])   # of dq_flag, one per place it stands at
-    assert counts and all(l.endswith("sc1") for l in counts) and len(waits) >= len(counts)
-    assert sum(l.startswith("buffer_store_dwordx4") and l.endswith("sc1") for l in body) >= 4 * len(counts)
+    counts = [i for i, l in enumerate(body) if l.startswith("global_store_dword ")]
+    assert counts and all(body[i].endswith("sc1") for i in counts)
+    for i in counts:
+        wait = next(j for j in range(i - 1, -1, -1) if body[j].startswith(("s_waitcnt vmcnt(0)", "buffer_", "global_", "ds_", "v_mfma")))
+        assert body[wait].startswith("s_waitcnt vmcnt(0)"), body[wait:i + 1]     # before any other memory or matrix work
+    sums = [l for l in body if l.startswith("buffer_store_dwordx4") and l.endswith("sc1")]
+    assert len(sums) >= 4 * len(counts) and len(sums) % 4 == 0
 
 
 def test_key_tiles_are_taken_from_a_counter(assembly):
@@ -85,8 +92,29 @@ def test_key_tiles_are_taken_from_a_counter(assembly):
     assert [i for i in loads if i < handed] == loads[:2]              # those of queries and dO, which do not depend on the tile
 
 
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    """The ids [B, H, key tiles] that the plan kernel's own functions give, compiled for the host."""
+    out = tmp_path_factory.mktemp("plan") / "plan.so"
+    flags = [f for f in B.HIPCC_FLAGS if f != "-O3"]
+    subprocess.run([B.hipcc(), *flags, "--offload-host-only", "-I", B.CSRC, "-o", str(out),
+                    os.path.join(os.path.dirname(__file__), "onepass_plan.hip")], check=True, capture_output=True)
+    lib = ctypes.CDLL(str(out))
+
+    def ids(nq, nk, H, L_q, L_k, group=None):
+        n, T = len(nq), (L_k + 255) // 256
+        group = lib.group_of(n, H, (L_q + 63) // 64) if group is None else group
+        assert 1 <= group <= n
+        q, k, got = np.array(nq, dtype=np.int32), np.array(nk, dtype=np.int32), np.full((n, H, T), -1, dtype=np.int32)
+        at = lambda a: a.ctypes.data_as(ctypes.c_void_p)
+        assert lib.plan_ids(at(q), at(k), n, H, L_q, L_k, group, at(got)) == T
+        return got, group
+
+    return ids
+
+
 def place(z, h, j, nq, nk, H, T, group):
-    """The id that the device's plan gives to a tile, step by step."""
+    """The id of a tile, step by step from what the plan is to be."""
     n, tiles = len(nq), [(k + 255) // 256 for k in nk]
     if n > 256:                                                        # batch order
         z0 = z - z % group
@@ -101,19 +129,35 @@ def place(z, h, j, nq, nk, H, T, group):
     return at * H + h
 
 
-@pytest.mark.parametrize("seed", range(12))
-def test_plan_is_complete_and_ordered(seed):
-    rng = random.Random(seed)
-    n, H, L = rng.choice((1, 2, 5, 16, 64, 260)), rng.choice((1, 2, 3)), rng.choice((200, 256, 300, 1500))
-    nk = [rng.randint(0, L) for _ in range(n)]
-    nq = nk if seed % 2 else [rng.randint(0, 700) for _ in range(n)]
-    T, group, seen = (L + 255) // 256, min(n, 1 + seed % 5), set()
-    for z in range(n):
-        for h in range(H):
-            ids = [place(z, h, j, nq, nk, H, T, group) for j in range(T)]
-            assert ids == sorted(ids)                                  # a tile's predecessor has a smaller id
-            seen.update(ids)
-    assert seen == set(range(n * H * T))
+@pytest.mark.parametrize("n,H,L,group", [
+    (1, 1, 200, None), (1, 12, 16500, None), (2, 3, 256, 1), (5, 10, 4100, None), (16, 2, 300, 3), (64, 3, 1500, 7), (70, 3, 1024, None),
+    (255, 1, 600, 255), (256, 1, 600, None), (256, 2, 449, 100), (257, 1, 600, None), (260, 2, 650, 9), (600, 3, 513, None),
+])
+@pytest.mark.parametrize("seed", range(4))
+def test_plan_is_complete_and_ordered(plan, n, H, L, group, seed):
+    """Every tile has an id and every id a tile; a head's tiles have rising ids; tiles with valid keys come before those
+    without (more than 256 sequences: in batch order).  Lengths out of range are clamped, and empty sides have no tiles."""
+    rng = random.Random(f"{n} {H} {L} {seed}")
+    nk = [rng.choice((rng.randint(0, L), rng.randint(0, L), 0, L, L + 5, -3)) for _ in range(n)]
+    nq = nk if seed % 2 else [rng.choice((rng.randint(0, 700), 0, 64)) for _ in range(n)]      # queries of their own: also none where there are keys
+    L_q = L if seed % 2 else 700
+    ids, group = plan(nq, nk, H, L_q, L, group)
+    clamp = lambda v, top: max(0, min(v, top))
+    cq, ck = [clamp(v, L_q) for v in nq], [clamp(v, L) for v in nk]
+    assert sorted(ids.ravel()) == list(range(ids.size))
+    assert (np.diff(ids, axis=2) > 0).all()
+    T = ids.shape[2]
+    for z in rng.sample(range(n), min(n, 12)):
+        for h in {0, H - 1}:
+            for j in {0, T // 2, T - 1}:
+                assert ids[z, h, j] == place(z, h, j, cq, ck, H, T, group), (z, h, j)
+    if n <= 256:
+        valid = np.arange(T)[None, None, :] < np.array([(k + 255) // 256 for k in ck])[:, None, None]
+        valid = np.broadcast_to(valid, ids.shape)
+        assert not valid.any() or valid.all() or ids[valid].max() < ids[~valid].min()
+        order = [z for z in sorted(range(n), key=lambda z: (-cq[z], z)) if ck[z] > 0]          # groups of ranks: longest first
+        first = [ids[z, 0, 0] for z in order]
+        assert group > 1 or first == sorted(first)
 
 
 def finishes(launches, by_start, first, cus=4):
@@ -143,12 +187,12 @@ def finishes(launches, by_start, first, cus=4):
 
 
 @pytest.mark.parametrize("H,sequences,T", [(12, 5, 6), (3, 20, 5), (8, 4, 6)])
-def test_overlapping_launches_end(H, sequences, T):
+def test_overlapping_launches_end(plan, H, sequences, T):
     """With tiles taken by start both launches end, whichever each XCD starts first; with tiles by id they can wait for each other
     for ever (not where the number of heads keeps a head on one XCD)."""
     n = [256 * T] * sequences
-    ids = {place(z, h, j, n, n, H, T, sequences): (z * H + h, j) for z in range(sequences) for h in range(H) for j in range(T)}
-    launch = [ids[i] for i in range(len(ids))]
+    ids, _ = plan(n, n, H, 256 * T, 256 * T, sequences)
+    launch = [(i // T, i % T) for i in np.argsort(ids.ravel())]
     orders = [[m >> x & 1 for x in range(8)] for m in range(256)]
     assert all(finishes([launch, launch], True, first) for first in orders)
     assert all(finishes([launch, launch], False, first) for first in orders) == (H % 8 == 0)
