@@ -36,7 +36,7 @@ def kernels():
     for line in text.split("\n"):
         m = re.match(r"^(_Z\w+):", line)                  # any function: what follows belongs to it, not to the one before
         if m:
-            name = m.group(1) if re.match(r"_ZN7sigattn\d+sigattn_(bwd_)?kernel", m.group(1)) else None
+            name = m.group(1) if re.match(r"_ZN7sigattn(7half128)?\d+sigattn_((bwd_)?kernel|half)", m.group(1)) else None
             in_body = name is not None
             if in_body:
                 result[name] = {"body": [], "meta": {}}
@@ -57,6 +57,9 @@ def kernels():
 
 def passes_and_d(name):
     """The passes a kernel holds, and its head dimension."""
+    if "half128" in name:                                 # the same loops in four-wave workgroups, d = 128
+        m = re.search(r"sigattn_halfILi(\d)E", name)
+        return ((int(m.group(1)),) if m else (DKDV, DQ)), 128
     m = re.search(r"sigattn_bwd_kernelILi(\d+)E", name)
     if m:
         return (DKDV, DQ), int(m.group(1))
@@ -67,7 +70,8 @@ def passes_and_d(name):
 def test_every_kernel_is_looked_at(kernels):
     shapes = sorted((d, p) for p, d in map(passes_and_d, kernels))
     assert shapes == sorted([(64, (FWD,))] * 2 + [(64, (DKDV,)), (64, (DQ,)), (64, (DQ,)), (64, (DKDV, DQ)),
-                            (128, (FWD,)), (128, (DKDV,)), (128, (DQ,)), (128, (DQ,))])
+                            (128, (FWD,)), (128, (DKDV,)), (128, (DQ,)), (128, (DQ,)),
+                            (128, (FWD,)), (128, (DQ,)), (128, (DKDV, DQ))])             # the last three: half128
     for name, k in kernels.items():
         assert set(k["meta"]) == {"NumVgprs", "ScratchSize", "Occupancy"}, name
         assert any(ins.startswith("s_endpgm") for ins in k["body"]), name
@@ -116,7 +120,8 @@ def test_no_packed_fp32_and_next_to_no_spills(kernels):
             assert not re.match(r"v_pk_(add|mul|fma)_f32", ins), f"{name}: packed fp32 instruction {ins!r}"
         # two registers a lane: what the four-wave joint backward and the d = 128 dQ + dbias kernel park today
         assert k["meta"]["ScratchSize"] <= 8, f"{name}: register spills"
-        assert k["meta"]["Occupancy"] >= (1 if passes_and_d(name) == ((DKDV,), 128) else 2), f"{name}: waves per SIMD"
+        alone = passes_and_d(name) == ((DKDV,), 128) or ("half128" in name and passes_and_d(name)[0] != (FWD,))
+        assert k["meta"]["Occupancy"] >= (1 if alone else 2), f"{name}: waves per SIMD"
 
 
 def test_hot_loops_use_the_matrix_and_transcendental_pipes(kernels):
