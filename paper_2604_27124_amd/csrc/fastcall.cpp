@@ -75,7 +75,10 @@ void *current_stream() { return static_cast<void *>(c10::hip::getCurrentHIPStrea
 template <class T>
 T *data(const at::Tensor &t) { return static_cast<T *>(t.data_ptr()); }
 
-PyObject *none() { Py_RETURN_NONE; }
+PyObject *none() {                 // with no Python error behind it, which what threw may have left
+    PyErr_Clear();
+    Py_RETURN_NONE;
+}
 
 struct WithoutGil {                // other threads of the interpreter run while memory is found and the launch is made
     PyThreadState *state = PyEval_SaveThread();
@@ -120,11 +123,13 @@ PyObject *bwd(PyObject *, PyObject *const *args, Py_ssize_t n) {
         }
         if (rc) return none();
         PyObject *out = PyTuple_New(3);
-        if (!out) return nullptr;
-        PyTuple_SET_ITEM(out, 0, THPVariable_Wrap(std::move(dq)));
-        PyTuple_SET_ITEM(out, 1, THPVariable_Wrap(std::move(dk)));
-        PyTuple_SET_ITEM(out, 2, THPVariable_Wrap(std::move(dv)));
-        return out;
+        at::Tensor *const grads[3] = {&dq, &dk, &dv};
+        for (int i = 0; out && i < 3; ++i) {
+            PyObject *const t = THPVariable_Wrap(std::move(*grads[i]));
+            if (t) PyTuple_SET_ITEM(out, i, t);
+            else Py_CLEAR(out);
+        }
+        return out;                // nullptr with the error that PyTuple_New or THPVariable_Wrap has set
     } catch (...) {
         return none();
     }
