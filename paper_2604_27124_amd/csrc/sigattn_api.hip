@@ -234,7 +234,8 @@ size_t onepass_bytes(int B, int N, int H) {            // sums of dQ in fp32, wh
 //   N = 1024      1.03 0.96 0.88 0.69     1.14 1.22 1.04 0.93     1.31 1.15 1.17 0.95     1.26 1.18 1.16 1.18     1.25 1.24 1.21 1.20
 //   N = 2048      1.04 0.96 0.88 0.90     1.25 1.22 1.06 0.97     1.28 1.17 1.11 0.99     1.26 1.21 1.21 1.19     1.28 1.27 1.24 1.25
 //   N = 4096      1.04 0.96 0.81 1.03     1.15 1.16 1.01 1.12     1.26 1.17 1.11 1.13     1.26 1.22 1.19 1.16     1.27 1.26 1.24 1.23
-// So below 768 ragged batches lose what full ones gain, and at N <= 512 they still do at 2000.  The host does not know the lengths:
+// So below 768 ragged batches lose what full ones gain, and at N <= 512 they still do at 1536 (from 3072 to 12288 tiles, 2 to 32
+// heads, N = 460 and 512 0.94 to 1.29).  The host does not know the lengths:
 // a batch of one long sequence among others of a sixteenth of it leaves most CUs without a tile, and one pass takes longer
 // (us, two / one: B = 16, N = 1024 38 / 60; B = 8, N = 2048 67 / 114; B = 8, N = 4096 214 / 252; not from N = 8192 on, 759 / 722 at B = 4;
 // H = 2, where the long one has fewest tiles: B = 85, N = 1406 33 / 87; with lognormal lengths B = 19, N = 5892 382 / 444, over 21
